@@ -118,11 +118,12 @@ int psfd_plan_footprint(const psfd_plan* plan, size_t* device_bytes);
  * the negated wavevector); with PSFD_APPLY_REFLECT, K is replaced by the coupled
  * M = K + R_vol T_R K_top (free space plus the multilayer response of eq. (9)). d_deps [nz][ny][nx], d_x and d_y [3][nz][ny][nx], all of
  * `dtype` (complex64 or complex128), device memory; d_y must not alias d_x.
- * Uses a plan-owned scratch field (allocated on first use). On 128 x 128 planes
- * with nz 32 or 64 the transverse transforms run split four ways over y (rows
- * y = 4 r + q) and the z pencil combines the quarter spectra; the environment
- * variable PSFD_QUARTER_PLANES=0 selects the one-block-per-plane (FP32) or
- * strip (FP64) transforms instead (same results to rounding). */
+ * Uses a plan-owned scratch field (allocated on first use). On planes of 1024 and
+ * more values with both sides of 16 and more (256 x 256 in FP32 only) and nz >= 8
+ * the transverse transforms run split four ways over y (rows y = 4 r + q) and
+ * the z pencil combines the quarter spectra; the environment variable
+ * PSFD_QUARTER_PLANES=0 selects the one-block-per-plane or strip transforms
+ * instead (same results to rounding). */
 int psfd_apply(psfd_plan* plan, const void* d_deps, const void* d_x, void* d_y, int dtype, int flags,
                void* stream);
 

@@ -422,8 +422,16 @@ static TileArgs tile_base(const Group& g, const void* tw, const TileShape& t) {
 bool quarter_planes(const Group& g, size_t esz) {
   const Shape& sh = g.sh;
   if ((esz != 8 && esz != 16) || env_int("PSFD_QUARTER_PLANES", 1) == 0) return false;
-  const ZCfg z = z_config(sh, esz);
-  return qplane_shape(sh.nx, sh.ny, sh.nz, sh.pz, z.bx, z.nthr, esz);
+  return qplane_bx(sh.nx, sh.ny, sh.nz, esz) != 0;
+}
+
+// the quarter-layout pencil blocks of a shape that takes them
+static ZCfg zq_config(const Shape& sh, size_t esz) {
+  ZCfg z{};
+  z.bx = qplane_bx(sh.nx, sh.ny, sh.nz, esz);
+  z.nthr = pencil_threads_ct(ilog2i(sh.pz), z.bx);
+  z.lds = pencil_lds(sh, z.bx, z.nthr, esz);
+  return z;
 }
 
 template <class T>
@@ -471,11 +479,11 @@ void apply_stage(Group& g, int stage, const T* deps, VecRef in, VecRef out, T* w
     }
   } else if (stage == 1) {
     // z: pad, FFT, kernel, IFFT, restrict (in place)
-    const ZCfg z = z_config(sh, sizeof(T));
+    const ZCfg z = qp ? zq_config(sh, sizeof(T)) : z_config(sh, sizeof(T));
     PencilArgs p;
     std::memset(&p, 0, sizeof(p));
     p.nx = sh.nx; p.ny = sh.ny; p.nz = sh.nz; p.pz = sh.pz; p.log2pz = ilog2i(sh.pz);
-    p.bx = z.bx; p.pitch = sh.pz + 1; p.nblk_x = qp ? sh.nx / 4 : sh.nx / z.bx; p.yq = qp;
+    p.bx = z.bx; p.pitch = sh.pz + 1; p.nblk_x = (qp ? 4 : 1) * sh.nx / z.bx; p.yq = qp;
     p.w = wsr; p.tab = g.tab; p.tab_stride = g.tab_stride; p.tw = tw; p.transpose = transpose; p.reflect = refl;
     p.active = active;
     if (gt) p.gv = *gt;  // the pending Givens step, and the scale of the input from its partials

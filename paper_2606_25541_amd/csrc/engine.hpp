@@ -169,8 +169,7 @@ void apply_stage(Group& g, int stage, const T* deps, VecRef in, VecRef out, T* w
                  int refl, const int* active, hipStream_t s, const double* in_scale = nullptr,
                  long long scale_stride = 0, const GivensTask* gt = nullptr, bool qp = false);
 // whether the operator apply of this group's shape takes the quarter-plane
-// kernels (FP32 128 x 128 planes with the compile-time pencil; PSFD_QUARTER_PLANES=0
-// turns them off)
+// kernels (qplane_bx; PSFD_QUARTER_PLANES=0 turns them off)
 bool quarter_planes(const Group& g, size_t esz);
 
 struct SolveStats {

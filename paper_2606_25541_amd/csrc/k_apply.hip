@@ -449,175 +449,6 @@ __global__ void __launch_bounds__(plane_threads(LN)) k_plane(TileArgs a) {
 }
 
 // -------------------------------------------------------------------------
-// Quarter-plane kernels (N x N planes, N = 128, and 256 in FP32; operator
-// apply). The transverse transform of a plane is split four ways over y: block
-// q of a plane takes the rows y = 4 r + q (r < N / 4), transforms them along x
-// (N points) and along r (N / 4 points), and stores the quarter spectrum times
-// its twiddle, Y'_q(ky', kx) = W_N^(q ky') Y_q(ky', kx), ky' < N / 4. The full
-// spectrum is the radix-4 decimation-in-time combine
-//   X(ky' + (N / 4) m, kx) = sum_q W4^(q m) Y'_q(ky', kx),
-// a twiddle-free 4-point DFT that the z-pencil kernel takes on load. Back the
-// same way: the pencil stores Z'_q = sum_m W4^(-q m) X(ky' + (N / 4) m), and
-// block q multiplies by W_N^(-q ky') and transforms along r and x back to the
-// rows y = 4 r + q. At N = 128, four blocks per plane (768 at 192 planes) keep
-// every CU busy with three resident blocks whose loads and FFT passes overlap;
-// one block per plane leaves 64 of 256 CUs idle and runs each CU's load,
-// transform and store one after the other. At N = 256 (FP32) a quarter plane
-// is one block per CU, and the transform is one pass through HBM where the
-// row and column strips take two.
-// Layout between the kernels, per plane: the four quarter spectra interleaved
-// in 32-byte pieces, (q, ky', kx) at qp_index<N>(ky', kx, q), so that the 16
-// values a pencil block takes at one (component, z) form one 128-byte line.
-// -------------------------------------------------------------------------
-// threads of a quarter-plane block: 16 values each in FP32 (rows of 128 by radix
-// 16 and 8, of 256 by 16 and 16), 8 in FP64 (radix 8, 8 and 2); the column
-// passes take radix 8, then 4 (N / 4 = 32) or 8 (N / 4 = 64)
-template <class T, int LN> struct QpShape {
-  static constexpr int N = 1 << LN, ROWS = N / 4;
-  static constexpr int NT = sizeof(T) == 16 ? 512 : (LN == 7 ? 256 : 1024), KT = ROWS * N / NT;
-  static constexpr int LRM_ROWS = sizeof(T) == 8 ? 4 : 3;
-  static constexpr int LRL = (LN - 3) % 3 + 1, RL = 1 << LRL;  // last column pass: radix RL
-};
-__host__ __device__ constexpr size_t qplane_lds(int ln, size_t esz) {
-  return ((size_t)((1 << ln) / 4) * ((1 << ln) + 1) + (1 << ln) + (1 << ln) / 4) * esz;
-}
-template <int N> PSFD_D int qp_index(int kyq, int kx, int q) { return kyq * (4 * N) + (kx >> 2) * 16 + 4 * q + (kx & 3); }
-
-template <class T, bool INV, int LD, int ST, int LN>
-__global__ void __launch_bounds__((QpShape<T, LN>::NT)) k_qplane(TileArgs a) {
-  typedef QpShape<T, LN> S;
-  constexpr int N = S::N, QP_ROWS = S::ROWS, P = N + 1, NT = S::NT, KT = S::KT, TS = NT / N;
-  static_assert(KT * NT == QP_ROWS * N && NT % N == 0, "quarter-plane thread split");
-  static_assert(!INV || LD == LD_PLAIN, "inverse: plain load");
-  static_assert(INV || (LD == LD_VX && ST == ST_PLAIN), "forward: contrast multiply, plain store");
-  extern __shared__ double2 smem_d[];
-  T* lds = reinterpret_cast<T*>(smem_d);
-  T* twl = lds + QP_ROWS * P;  // W_N^k, k < N
-  T* twl32 = twl + N;          // W_(N/4)^k = W_N^(4 k), k < N / 4
-  const int b = blockIdx.y;
-  if (a.active && !a.active[b]) return;
-  // block order: with 8 | nz, XCD x (= hw mod 8) takes the planes z = x mod 8 of
-  // all three components and their four quarters, so the three blocks that read
-  // one contrast plane share an L2, and so do the four that write (or read) one
-  // 128-byte line of the layout
-  int plane, q;
-  {
-    const int hw = blockIdx.x;
-    if ((a.nz & 7) == 0) {
-      const int xc = hw & 7, i = hw >> 3, t = i >> 2, c = t % 3, zz = t / 3;
-      q = i & 3;
-      plane = c * a.nz + xc + 8 * zz;
-    } else {
-      plane = hw >> 2;
-      q = hw & 3;
-    }
-  }
-  const int z = plane % a.nz;
-  const long long poff = (long long)plane * N * N;
-  const int tid = threadIdx.x;
-  typedef typename real_of<T>::type R;
-  const T* twg = reinterpret_cast<const T*>(a.tw) + N;
-  const T tw0 = twg[tid & (N - 1)];
-  const T tw1 = twg[(tid & (QP_ROWS - 1)) * 4];
-  // the twiddle loads ahead of the data loads: their LDS writes wait for them alone
-  __builtin_amdgcn_sched_barrier(0);
-  const T* in = vref<T>(a.in, b) + poff;
-  const T* vol = INV ? nullptr : vref<T>(a.vol, b) + (long long)z * N * N;
-  const T* aux = ST == ST_AXPBY ? vref<T>(a.aux, b) + poff : nullptr;
-  // the column transform's last pass (radix RL, stride PL = N / 4 / RL = 8)
-  // leaves its results in registers: butterfly i of the thread (column
-  // s = tid mod N, index t = tid / N + (NT / N) i) forms rows r = t + PL j of
-  // that column
-  constexpr int RL = S::RL, PL = QP_ROWS / RL, NBL = KT / RL;
-  static_assert(PL == 8 && NBL * RL == KT, "quarter-plane last column pass");
-  T va[KT], vb[INV ? 1 : KT], xa[ST == ST_AXPBY ? KT : 1];
-#pragma unroll
-  for (int k = 0; k < KT; ++k) {
-    const int i = tid + k * NT, r = i >> LN, x = i & (N - 1);
-    if constexpr (!INV) {
-      va[k] = in[(4 * r + q) * N + x];
-      vb[k] = vol[(4 * r + q) * N + x];
-    } else {
-      va[k] = in[qp_index<N>(r, x, q)];
-    }
-  }
-  if constexpr (ST == ST_AXPBY) {
-#pragma unroll
-    for (int i = 0; i < NBL; ++i)
-#pragma unroll
-      for (int j = 0; j < RL; ++j) {
-        const int r = (tid >> LN) + TS * i + PL * j, x = tid & (N - 1);
-        xa[i * RL + j] = aux[(4 * r + q) * N + x];
-      }
-  }
-  const double* tab = a.tab + (long long)b * a.tab_stride;
-  R ks = (R)1;
-  if constexpr (!INV) ks = (R)tab[TS_K0SQ] * (a.in_scale ? (R)a.in_scale[(long long)b * a.scale_stride] : (R)1);
-  if (tid < N) twl[tid] = tw0;
-  if (tid < QP_ROWS) twl32[tid] = tw1;
-  // the inverse multiplies by W128^(-q ky') on the way into LDS
-  if constexpr (INV) __syncthreads();
-#pragma unroll
-  for (int k = 0; k < KT; ++k) {
-    const int i = tid + k * NT, r = i >> LN;
-    T v;
-    if constexpr (INV) v = cmulc(va[k], twl[q * r]);
-    else v = cscale(cmul(vb[k], va[k]), ks);
-    lds[r * P + (i & (N - 1))] = v;
-  }
-  __syncthreads();
-  typedef FftCT<LN, QP_ROWS, P, 1, NT> Rows;  // N / 4 rows of N points
-  typedef FftCT<LN - 2, N, 1, P, NT> Cols;     // N columns of N / 4 points
-  lds_fft_tab<T, INV, true, KT, Rows, false, false, S::LRM_ROWS>(lds, Rows(), twl, tid);
-  T res[KT];
-  lds_fft_tab_regout<T, INV, true, KT, Cols, false, 3>(lds, Cols(), twl32, tid, res);
-  T* out = vref<T>(a.out, b) + poff;
-  const R al = (R)a.alpha, ga = (R)a.gamma;
-#pragma unroll
-  for (int i = 0; i < NBL; ++i)
-#pragma unroll
-    for (int j = 0; j < RL; ++j) {
-      const int r = (tid >> LN) + TS * i + PL * j, x = tid & (N - 1);
-      T v = res[i * RL + j];
-      if constexpr (!INV) {
-        out[qp_index<N>(r, x, q)] = cmul(v, twl[q * r]);
-      } else {
-        if constexpr (ST == ST_AXPBY) {
-          const T xv = xa[ST == ST_AXPBY ? i * RL + j : 0];
-          v.x = al * xv.x + ga * v.x;
-          v.y = al * xv.y + ga * v.y;
-        }
-        out[(4 * r + q) * N + x] = v;
-      }
-    }
-}
-
-
-template <class T, bool INV, int LD, int ST>
-void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s) {
-  const bool ok = a.nx == a.ny && (a.nx == 128 || (a.nx == 256 && sizeof(T) == 8));
-  if (!ok || a.gv.st || nplanes != 3 * a.nz) {
-    std::fprintf(stderr, "psfd: internal error: quarter-plane launch on an unsupported shape\n");
-    std::abort();
-  }
-  auto go = [&](auto kern, int ln, int nt) {
-    const size_t l = qplane_lds(ln, sizeof(T));
-    allow_lds(reinterpret_cast<const void*>(kern), l);
-    hipLaunchKernelGGL(kern, dim3(4 * nplanes, nbatch), dim3(nt), l, s, a);
-  };
-  if constexpr (sizeof(T) == 8) {
-    if (a.nx == 256) return go(k_qplane<T, INV, LD, ST, 8>, 8, QpShape<T, 8>::NT);
-  }
-  go(k_qplane<T, INV, LD, ST, 7>, 7, QpShape<T, 7>::NT);
-}
-template void launch_qplane<float2, false, LD_VX, ST_PLAIN>(const TileArgs&, int, int, hipStream_t);
-template void launch_qplane<float2, true, LD_PLAIN, ST_PLAIN>(const TileArgs&, int, int, hipStream_t);
-template void launch_qplane<float2, true, LD_PLAIN, ST_AXPBY>(const TileArgs&, int, int, hipStream_t);
-template void launch_qplane<double2, false, LD_VX, ST_PLAIN>(const TileArgs&, int, int, hipStream_t);
-template void launch_qplane<double2, true, LD_PLAIN, ST_PLAIN>(const TileArgs&, int, int, hipStream_t);
-template void launch_qplane<double2, true, LD_PLAIN, ST_AXPBY>(const TileArgs&, int, int, hipStream_t);
-
-// -------------------------------------------------------------------------
 // Strip kernel: for square N x N planes too large for LDS, the x-FFT of
 // TY = 4096 / N full rows (ROWS) or the y-FFT of 16 full columns of one plane,
 // with the shapes fixed at compile time; 8 elements per thread, twiddles in
@@ -866,13 +697,6 @@ PSFD_D T window_factor_fast(double2 beta, double2 beta2, double2 num, double kap
 // the global load/store touch consecutive LDS words across a wavefront.
 // At most 8 values per thread in the pencil FFTs (the launch gives 3 bx pz / 8
 // threads, at most 768), which halves the register arrays of the FP32 passes.
-// Threads of a pencil block with bx columns and padded length 2^LPZ: at most 8
-// values per thread in the FFT passes, at least four readout partial sums per
-// sequence (the host's pencil_threads gives the same count).
-__host__ __device__ constexpr int pencil_threads_ct(int lpz, int bx) {
-  return (3 * bx * (1 << lpz) / 8 + 63) / 64 * 64 > (12 * bx + 63) / 64 * 64 ? (3 * bx * (1 << lpz) / 8 + 63) / 64 * 64
-                                                                            : (12 * bx + 63) / 64 * 64;
-}
 
 // Quarter-spectrum combine of the pencil (quarter-plane layout): a 4-point DFT
 // across the four lanes of a quad, lane q holding input q. Its radix-2 stages
@@ -912,20 +736,21 @@ template <class T> PSFD_D T quad_dft4(T v, int q, bool inv) {
   if (q == 3) { r.x = -v.y; r.y = v.x; v = r; }  // times +i
   return quad_bfly<DPP_QUAD_SWAP2>(v, s2);
 }
-// pencil column c of a quarter-layout block: kx = kx0 + c / 4 and quarter
-// q = c mod 4 on load (position 4 q + c / 4 of the block's 16-value piece), row
-// ky' + (ny / 4) brev(q) after the combine
+// pencil column c of a quarter-layout block of BX columns (BX / 4 kx in their 4
+// quarters): kx = kx0 + c / 4 and quarter q = c mod 4 on load (position
+// 4 q + c / 4 from the block's first value), row ky' + (ny / 4) brev(q) after
+// the combine
 PSFD_D int qp_pos(int c) { return ((c & 3) << 2) | (c >> 2); }
 PSFD_D int brev2(int q) { return ((q & 1) << 1) | (q >> 1); }
 
 // LPZ > 0: BXC columns and padded length 2^LPZ fixed at compile time (the FFT
 // index arithmetic folds to constants); LPZ = 0: shapes from the arguments.
 // YQ: the workspace holds the quarter-plane layout (see k_qplane): a block
-// takes 4 kx of the quarter-spectrum row ky' in its 4 quarters, which the
-// combine on load turns into the 16 columns kx0 + kx, ky' + (ny / 4) m, and
+// takes BXC / 4 kx of the quarter-spectrum row ky' in its 4 quarters, which the
+// combine on load turns into the BXC columns kx0 + kx, ky' + (ny / 4) m, and
 // the inverse combine on store back into quarters.
 template <class T, int LPZ, int BXC, bool YQ>
-__global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
+__global__ void __launch_bounds__(LPZ ? pencil_threads_ct(LPZ ? LPZ : 4, BXC) : 768) k_pencil(PencilArgs a) {
   extern __shared__ double2 smem_d[];
   T* lds = reinterpret_cast<T*>(smem_d);
   typedef typename real_of<T>::type R;
@@ -939,15 +764,15 @@ __global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
   }
   if (a.active && !a.active[b]) return;
   const int bx = LPZ ? BXC : a.bx, pz = LPZ ? (1 << LPZ) : a.pz, nz = pz / 2, nx = a.nx, ny = a.ny;
-  static_assert(!YQ || (LPZ > 0 && BXC == 16), "quarter layout: compile-time pencils");
+  static_assert(!YQ || LPZ > 0, "quarter layout: compile-time pencils");
   const int ky = blockIdx.x / a.nblk_x;  // YQ: the quarter-spectrum row ky'
-  const int kx0 = (blockIdx.x - ky * a.nblk_x) * (YQ ? 4 : bx);
+  const int kx0 = (blockIdx.x - ky * a.nblk_x) * (YQ ? BXC / 4 : bx);
   const int tid = threadIdx.x, nthr = LPZ ? pencil_threads_ct(LPZ, BXC) : (int)blockDim.x;
   const int LS = 3 * bx;
   const int lbx = LPZ ? (BXC == 16 ? 4 : BXC == 8 ? 3 : 2) : ilog2i(bx);
   T* w = vref<T>(a.w, b);
   // The data half (z < nz) is LDS elements [0, nz LS): i = z LS + c bx + kxl, at
-  // most 4 per thread (3 pz bx <= 8 nthr). Loads are unconditional (clamped index)
+  // most 4 (compile-time shapes: VT) per thread (3 pz bx <= 8 nthr). Loads are unconditional (clamped index)
   // and all issued before the LDS writes; the padded half (z >= nz) is not stored.
   const int nval = nz * LS;
   // compile-time shapes: nthr is a multiple of LS, so element i = tid + k nthr
@@ -955,23 +780,29 @@ __global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
   // k; its global offset (32-bit: a field has fewer than 2^31 elements) then
   // advances by a constant
   constexpr bool CT = LPZ > 0;
-  static_assert(!CT || ((BXC == 16 || BXC == 8 || BXC == 4) && pencil_threads_ct(LPZ, BXC) % (3 * BXC) == 0),
+  constexpr int ZSTEP = CT ? pencil_threads_ct(LPZ, BXC) / (3 * BXC) : 1;
+  constexpr int VT = CT ? (1 << LPZ) / 2 / ZSTEP : 4;  // values per thread (data half)
+  static_assert(!CT || ((BXC == 16 || (BXC == 8 && LPZ == 8)) && pencil_threads_ct(LPZ, BXC) == ZSTEP * 3 * BXC &&
+                        VT * ZSTEP * 2 == (1 << LPZ) && (VT == 4 || VT == 2)),
                 "pencil thread split");
   const int ck = tid & (bx - 1);
-  const int zstep = CT ? nthr / LS : 0;
+  const int zstep = CT ? pencil_threads_ct(LPZ, BXC) / (3 * BXC) : 0;
   const int c0 = CT ? (tid >> lbx) % 3 : 0, z0 = CT ? tid / LS : 0;
-  const int goff0 = YQ ? (c0 * nz + z0) * ny * nx + ky * 4 * nx + kx0 * 4 + qp_pos(ck)
+  // first value of the block in the quarter-plane layout (8 columns: half a
+  // piece of 16, shared with the neighbouring block)
+  const int kyx0 = ky * 4 * nx + (kx0 >> 2) * 16 + (kx0 & 3);
+  const int goff0 = YQ ? (c0 * nz + z0) * ny * nx + kyx0 + qp_pos(ck)
                       : ((c0 * nz + z0) * ny + ky) * nx + kx0 + ck,
             gstep = zstep * ny * nx;
   // compile-time shapes: the data stays in registers, where the forward
   // transform's first pass and the readout partial sums take it (elements
   // z0 + k zstep of sequence (c0, ck) are exactly that pass's inputs)
-  T buf[4];
+  T buf[VT];
   {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < VT; ++k) {
       if constexpr (CT) {
-        buf[k] = w[goff0 + min(k, (nval - 1 - tid) / nthr) * gstep];
+        buf[k] = w[goff0 + k * gstep];
       } else {
         const int i = min(tid + k * nthr, nval - 1);
         const int kxl = i & (bx - 1), rest = i >> lbx;
@@ -983,7 +814,7 @@ __global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
     // (the 16 lanes of a quad group share their component and planes)
     if constexpr (YQ) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) buf[k] = quad_dft4<T>(buf[k], tid & 3, false);
+      for (int k = 0; k < VT; ++k) buf[k] = quad_dft4<T>(buf[k], tid & 3, false);
     }
     if constexpr (!CT) {
 #pragma unroll
@@ -1085,7 +916,7 @@ __global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
   // readout partial sums over z: thread (ch, sq) takes planes ch, ch + nch, ...
   // (read before the forward transform's first barrier, summed after its last)
   const int nch = nthr / LS;
-  T ph4[4];  // compile-time shapes: the phases of the thread's planes z0 + k zstep, kept for the store
+  T ph4[VT];  // compile-time shapes: the phases of the thread's planes z0 + k zstep, kept for the store
   if (a.reflect && tid < nch * LS) {
     const int sq = tid % LS, ch = tid / LS;
     const int kxl = sq & (bx - 1);
@@ -1093,7 +924,7 @@ __global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
     if constexpr (CT) {
       // (ch, sq) = (z0, tid mod LS): this thread's own data, planes z0 + k zstep
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < VT; ++k) {
         ph4[k] = phase_at(ch + k * nch, kxl);
         acc = cadd(acc, cmul(ph4[k], buf[k]));
       }
@@ -1117,13 +948,19 @@ __global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
   const T* tw = reinterpret_cast<const T*>(a.tw);
   typedef FftCT<LPZ, 3 * BXC, 1, 3 * BXC, pencil_threads_ct(LPZ, BXC)> ZCT;
   if constexpr (LPZ > 0) {
-    // radix 8 first, from the registers (its inputs t + pz/8 j, j < 4, of
-    // sequence tid mod LS, t = tid / LS, are buf[j]), then the last pass
-    static_assert(LPZ == 6 || LPZ == 7, "pencil lengths with a register first pass");
-    stockham_pass_regin<T, 8, false, true, 8, ZCT, true>(lds, ZCT(), tid, buf);
+    // first pass of radix 2 VT from the registers (its inputs t + pz / (2 VT) j,
+    // j < VT, of sequence tid mod LS, t = tid / LS, are buf[j]), then the others:
+    // one of radix 16, 8 or 4, and for pz = 256 radix 8 and 4
+    constexpr int RF = 2 * VT, LRF = VT == 4 ? 3 : 2, E = 2 * VT, REM = LPZ - LRF;
+    stockham_pass_regin<T, RF, false, true, E, ZCT, true>(lds, ZCT(), tid, buf);
     __syncthreads();
-    if constexpr (LPZ == 7) pass_r<T, false, true, 8, ZCT, false, false, 16>(lds, ZCT(), 3, twl, tid, false, true);
-    else pass_r<T, false, true, 8, ZCT, false, false, 8>(lds, ZCT(), 3, twl, tid, false, true);
+    if constexpr (REM <= 4) {
+      pass_r<T, false, true, E, ZCT, false, false, (1 << REM)>(lds, ZCT(), LRF, twl, tid, false, true);
+    } else {
+      static_assert(REM == 5 && VT == 4, "pencil passes");
+      pass_r<T, false, true, E, ZCT, false, false, 8>(lds, ZCT(), LRF, twl, tid, false, false);
+      pass_r<T, false, true, E, ZCT, false, false, 4>(lds, ZCT(), LRF + 3, twl, tid, false, true);
+    }
   } else {
     lds_fft<T, false, true, 8, true, false>(lds, a.log2pz, LS, 1, LS, tw, tid, nthr);
   }
@@ -1191,18 +1028,19 @@ __global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
   const int nst = 3 * nz * bx;
   if constexpr (CT) {
     // the inverse transform's last pass leaves the kept half in registers, and
-    // the thread that forms output t + 16 j of sequence s stores it: last pass
-    // of radix R (8 for pz = 128, 4 for pz = 64) has stride pz / R = 16 and
-    // 8 / R butterflies b = tid + i nthr per thread, b = t LS + s
-    T out[4];
-    lds_fft_tab_regout<T, true, true, 8, ZCT, true, 4>(lds, ZCT(), twl, tid, out);
+    // the thread that forms output t + PL j of sequence s stores it: last pass
+    // of radix RL (8 for pz = 128, else 4) with stride PL = pz / RL and
+    // 2 VT / RL butterflies b = tid + i nthr per thread, b = t LS + s
+    T out[VT];
+    constexpr int LRM = LPZ == 6 || LPZ == 7 ? 4 : LPZ == 4 ? 2 : 3;
+    lds_fft_tab_regout<T, true, true, 2 * VT, ZCT, true, LRM>(lds, ZCT(), twl, tid, out);
     const R scl = gvb ? sclw : (R)1;
-    constexpr int RL = LPZ == 7 ? 8 : 4, NBL = 8 / RL, PL = (1 << LPZ) / RL;
-    static_assert(LPZ == 6 || LPZ == 7, "pencil lengths with a register last pass");
+    constexpr int RL = LPZ == 7 ? 8 : 4, NBL = 2 * VT / RL, PL = (1 << LPZ) / RL;
+    static_assert((LPZ - 1) % LRM + 1 == (RL == 8 ? 3 : 2), "radix of the last pass");
     // output plane t + PL j of butterfly i is the thread's loaded plane z0 + k zstep,
     // k = i + j PL / zstep (t = z0 + i zstep): its phase is ph4[k]
-    constexpr int ZST = pencil_threads_ct(LPZ, BXC) / (3 * BXC);
-    static_assert(PL % ZST == 0 && (NBL - 1) + (RL / 2 - 1) * (PL / ZST) < 4, "store planes are the loaded planes");
+    constexpr int ZST = ZSTEP;
+    static_assert(PL % ZST == 0 && (NBL - 1) + (RL / 2 - 1) * (PL / ZST) < VT, "store planes are the loaded planes");
 #pragma unroll
     for (int i = 0; i < NBL; ++i) {
       const int bfl = tid + i * nthr, t = bfl / LS, sq = bfl - t * LS;
@@ -1217,7 +1055,7 @@ __global__ void __launch_bounds__(768) k_pencil(PencilArgs a) {
         if constexpr (YQ) {
           // back to quarter spectra across the quad (kxl = tid mod 16)
           v = quad_dft4<T>(v, kxl & 3, true);
-          w[(c * nz + z) * ny * nx + ky * 4 * nx + kx0 * 4 + qp_pos(kxl)] = v;
+          w[(c * nz + z) * ny * nx + kyx0 + qp_pos(kxl)] = v;
         } else {
           w[((c * nz + z) * ny + ky) * nx + kx0 + kxl] = v;
         }
@@ -1248,25 +1086,24 @@ void launch_pencil(const PencilArgs& a, int nbatch, int nthr, size_t lds, hipStr
     allow_lds(reinterpret_cast<const void*>(kern), lds);
     hipLaunchKernelGGL(kern, grid, dim3(nthr), lds, s, a);
   };
+  auto is = [&](int lpz, int bx) { return a.bx == bx && a.pz == 1 << lpz && nthr == pencil_threads_ct(lpz, bx); };
   if (a.yq) {
-    if (a.bx == 16 && a.pz == 128 && nthr == pencil_threads_ct(7, 16)) return go(k_pencil<T, 7, 16, true>);
-    if (a.bx == 16 && a.pz == 64 && nthr == pencil_threads_ct(6, 16)) return go(k_pencil<T, 6, 16, true>);
+    if (is(4, 16)) return go(k_pencil<T, 4, 16, true>);
+    if (is(5, 16)) return go(k_pencil<T, 5, 16, true>);
+    if (is(6, 16)) return go(k_pencil<T, 6, 16, true>);
+    if (is(7, 16)) return go(k_pencil<T, 7, 16, true>);
+    if (is(8, 8)) return go(k_pencil<T, 8, 8, true>);
     std::fprintf(stderr, "psfd: internal error: quarter-plane pencil on an unsupported shape\n");
     std::abort();
   }
-  if (a.bx == 16 && a.pz == 128 && nthr == pencil_threads_ct(7, 16)) return go(k_pencil<T, 7, 16, false>);
-  if (a.bx == 16 && a.pz == 64 && nthr == pencil_threads_ct(6, 16)) return go(k_pencil<T, 6, 16, false>);
+  if (is(4, 16)) return go(k_pencil<T, 4, 16, false>);
+  if (is(5, 16)) return go(k_pencil<T, 5, 16, false>);
+  if (is(6, 16)) return go(k_pencil<T, 6, 16, false>);
+  if (is(7, 16)) return go(k_pencil<T, 7, 16, false>);
   go(k_pencil<T, 0, 16, false>);
 }
 template void launch_pencil<float2>(const PencilArgs&, int, int, size_t, hipStream_t);
 template void launch_pencil<double2>(const PencilArgs&, int, int, size_t, hipStream_t);
-
-// the operator apply's shapes that take the quarter-plane kernels and the
-// quarter-layout pencil (FP32 128 x 128 planes, compile-time pencil)
-bool qplane_shape(int nx, int ny, int nz, int pz, int bx, int nthr, size_t esz) {
-  return nx == ny && (nx == 128 || (nx == 256 && esz == 8)) && nz > 0 && bx == 16 &&
-         ((pz == 128 && nthr == pencil_threads_ct(7, 16)) || (pz == 64 && nthr == pencil_threads_ct(6, 16)));
-}
 
 // -------------------------------------------------------------------------
 // Per-order kernels of the background-field outer loop (FP64)

@@ -92,7 +92,7 @@ struct PencilArgs {
   const int* active;
   GivensTask gv;         // optional (gv.st null: none): the pending Givens step in one extra
                          // block; the other blocks scale the input by the new vector's scale
-  int yq;                // w in the quarter-plane layout of launch_qplane (nblk_x = nx / 4)
+  int yq;                // w in the quarter-plane layout of launch_qplane (nblk_x = 4 nx / bx)
 };
 
 struct TileShape { int tx, ty, do_x, do_y, nthr; size_t lds; int pitch; };
@@ -129,15 +129,21 @@ bool tile_takes_dots(const TileArgs& a, size_t esz);
 bool tile_takes_update(const TileArgs& a, size_t esz);
 template <class T>
 void launch_pencil(const PencilArgs& a, int nbatch, int nthr, size_t lds, hipStream_t s);
-// Quarter-plane transverse kernels of the operator apply on 128 x 128 planes
-// (and 256 x 256 in FP32): forward (LD_VX, ST_PLAIN) into the quarter-plane layout, inverse
-// (LD_PLAIN, ST_PLAIN or ST_AXPBY) from it; nplanes = 3 nz, no GivensTask.
-// The pencil between them runs with PencilArgs::yq.
+// Quarter-plane transverse kernels of the operator apply (planes of 16 .. 256 on
+// both sides, of 1024 and more values, whose quarter fits LDS): forward (LD_VX, ST_PLAIN) into the
+// quarter-plane layout, inverse (LD_PLAIN, ST_PLAIN or ST_AXPBY) from it;
+// nplanes = 3 nz, no GivensTask. The pencil between them runs with PencilArgs::yq.
 template <class T, bool INV, int LD, int ST>
 void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s);
-// whether a shape (and its pencil's columns bx and threads) takes them: 128 x 128
-// planes, and 256 x 256 in FP32 (esz 8)
-bool qplane_shape(int nx, int ny, int nz, int pz, int bx, int nthr, size_t esz);
+// Columns of the quarter-layout pencil blocks of a shape; 0: the shape takes
+// the natural layout (planes too small or beyond LDS, nz < 8).
+int qplane_bx(int nx, int ny, int nz, size_t esz);
+// Threads of a compile-time pencil block of bx columns (a multiple of its 3 bx
+// sequences) and padded length 2^lpz: 8 values per thread in the FFT passes,
+// at least four readout partial sums per sequence.
+__host__ __device__ constexpr int pencil_threads_ct(int lpz, int bx) {
+  return 3 * bx * (1 << lpz) / 8 > 12 * bx ? 3 * bx * (1 << lpz) / 8 : 12 * bx;
+}
 
 // per-order readouts of the source density spectra (FP64):
 // adn = (i dz / 2 beta) P- sum_k exp(i beta z_k) f_q(z_k) / (NxNy), aup likewise at z = T.

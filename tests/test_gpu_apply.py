@@ -117,6 +117,39 @@ def test_quarter_planes_match_full_planes(n, nz, dtype, monkeypatch):
         assert rel(a, b) < tol, (v, rel(a, b))
 
 
+# every plane side and padded z length the quarter-plane kernels and their
+# pencils are built for, at the edges of the rule that selects them: 1024-value
+# planes, 16 on either side, the largest quarters of
+# each precision, nz = 8 and 128
+# (8 columns per pencil block), and planes just below the rule (16 x 32)
+QUARTER_SHAPES = [(32, 32, 8), (32, 32, 64), (64, 16, 16), (16, 64, 32), (16, 32, 16), (256, 16, 8), (16, 256, 64),
+                  (64, 64, 128), (64, 128, 16), (128, 64, 8), (32, 256, 32), (256, 128, 8), (128, 256, 16)]
+
+
+@pytest.mark.parametrize("shape", QUARTER_SHAPES)
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_quarter_planes_on_any_planes(shape, dtype):
+    """Plain, K-only, coupled and coupled transposed applies against the oracle."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    nx, ny, nz = shape
+    say("quarter planes", shape, dtype)
+    p = make(nx, ny, nz, phi=10.0, pol=1)
+    de = clips.manhattan(nx, ny, nz, p.lx_nm, p.ly_nm, seed=nx + 3 * nz)
+    x = clips.random_complex((3, nz, ny, nx), seed=31)
+    S = O.Setup(p)
+    f = O.potential(S, de)[None] * x
+    refs = [({}, O.apply_A(S, de, x)), ({"k_only": True}, O.conv_K(S, f)), ({"reflect": True}, x - O.apply_M(S, f)),
+            ({"reflect": True, "transpose": True}, x - O.apply_M_T(S, f))]
+    td = torch.complex128 if dtype == "c128" else torch.complex64
+    plan = api.Plan(p)
+    dd, xx = torch.from_numpy(de).to(dev, td), torch.from_numpy(x).to(dev, td)
+    for flags, ref in refs:
+        y = plan.psfd_apply(dd, xx, **flags).cpu().numpy()
+        tol = 1e-12 if dtype == "c128" else 3e-6
+        assert rel(y, ref) < tol * (3 if "k_only" in flags else 1), (flags, rel(y, ref))
+
+
 def test_apply_is_deterministic():
     from paper_2606_25541_amd import api
     dev = device()
