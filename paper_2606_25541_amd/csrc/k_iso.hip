@@ -122,6 +122,109 @@ __global__ void k_iso_lines(IsoLines a) {
   }
 }
 
+// The same line pass with the length fixed at compile time, n = R1 R2 points in
+// two register DFTs around one exchange through LDS (the passes of lds_fft take
+// three or more): thread t < R2 of a line loads elements t + R2 j, transforms
+// them over j (R1 points, its zero half neither read nor formed), and the
+// thread of residue k1 (k1 = t + R2 i) transforms over t with the twiddles
+// W_n^(t k1) into elements k1 + R1 k2, which it stores itself. Loads and stores
+// go straight between registers and global memory: contiguous lines put a
+// line's threads on consecutive lanes, strided lines (SFL) the block's lines.
+// Every load is issued before the exchange, and the twiddles (table [t][k1])
+// come from LDS. The passes are bound by memory: at 128 x 128 x 64 in FP32 the x
+// rows went from 24.7 to 13.7 us (6.1 TB/s), the y columns from 35.1 to 24.1
+// (6.3), back from 33.7 to 23.9 and from 25.5 to 15.6 (6.4); FP64 39 -> 26,
+// 56 -> 47, 63 -> 47, 53 -> 31 us.
+template <class T, int LN, bool SFL> struct LineShape {
+  static constexpr int LB = sizeof(T) == 8 ? 16 : 8;
+  static constexpr int N = 1 << LN, R1 = 1 << ((LN + 1) / 2), R2 = N / R1, K = R1 / R2, NT = LB * R2;
+  static constexpr int LLB = LB == 16 ? 4 : 3, LR2 = LN / 2;
+  // LDS position of (line s, t, k1): lines interleaved, or one line after the
+  // other with an odd stride between the k1, either way consecutive (or odd
+  // strides of) words across the lanes that write and read together
+  static constexpr int LINE = SFL ? 1 : R1 * (R2 + 1), EK = SFL ? R2 * LB : R2 + 1, ET = SFL ? LB : 1;
+  static constexpr int ELEMS = SFL ? N * LB : LB * R1 * (R2 + 1);
+  static constexpr size_t lds() { return (size_t)(ELEMS + N) * sizeof(T); }
+};
+
+template <class T, bool INV, int MODE, bool SFL, bool ZIN, bool ZOUT, int LN>
+__global__ void __launch_bounds__((LineShape<T, LN, SFL>::NT)) k_iso_line(IsoLines a) {
+  typedef LineShape<T, LN, SFL> S;
+  typedef typename real_of<T>::type R;
+  constexpr int R1 = S::R1, R2 = S::R2, K = S::K, NT = S::NT, N = S::N, LB = S::LB;
+  constexpr int NI = ZIN ? R1 / 2 : R1, NO = ZOUT ? R2 / 2 : R2;
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* lds = reinterpret_cast<T*>(smem);
+  T* tw2 = lds + S::ELEMS;  // W_n^(t k1) at t R1 + k1
+  const int tid = threadIdx.x;
+  long long blk = blockIdx.x;
+  if (MODE == LN_VLOAD) {  // component order of the blocks as in k_iso_lines
+    const unsigned nb = gridDim.x, q = xcd_order(blockIdx.x, nb);
+    blk = (long long)(q % 3u) * (nb / 3u) + q / 3u;
+  }
+  const int s = SFL ? tid & (LB - 1) : tid >> S::LR2, t = SFL ? tid >> S::LLB : tid & (R2 - 1);
+  const long long l = blk * LB + s;
+  const T* src = (const T*)a.src + line_base(l, a.lcin_s, a.sin_s, a.sout_s);
+  T u[R1], d[MODE == LN_VLOAD ? NI : 1];
+#pragma unroll
+  for (int j = 0; j < NI; ++j) u[j] = src[(t + R2 * j) * a.es];
+  if constexpr (MODE == LN_VLOAD) {
+    const T* dp = (const T*)a.deps + ((l & ((1LL << a.lvmod) - 1)) << (LN - 1));
+#pragma unroll
+    for (int j = 0; j < NI; ++j) d[j] = dp[t + R2 * j];
+  }
+  const long long ob = line_base(l, a.lcin_d, a.sin_d, a.sout_d);
+  T xi[MODE == LN_AXPY ? K * NO : 1];
+  if constexpr (MODE == LN_AXPY) {
+    const T* xin = (const T*)a.xin + ob;
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+      for (int k = 0; k < NO; ++k) xi[i * NO + k] = xin[(t + R2 * i + R1 * k) * a.es];
+  }
+  {
+    const T* tg = (const T*)a.tw + N;
+#pragma unroll
+    for (int i = 0; i < (N + NT - 1) / NT; ++i) {
+      const int e = tid + i * NT;
+      if (N % NT == 0 || e < N) tw2[e] = tg[(e / R1) * (e % R1)];
+    }
+  }
+  if constexpr (MODE == LN_VLOAD) {
+    const R vs = (R)a.vscale;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) u[j] = cmul(u[j], cscale(d[j], vs));
+  }
+  if constexpr (ZIN) dft_r_half<T, R1, INV>(u);
+  else dft_r<T, R1, INV>(u);
+  T* base = lds + s * S::LINE;
+#pragma unroll
+  for (int k = 0; k < R1; ++k) base[k * S::EK + t * S::ET] = u[k];
+  __syncthreads();
+  T* dst = (T*)a.dst + ob;
+  const R sc = (R)a.scale;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const int k1 = t + R2 * i;
+    T v[R2];
+#pragma unroll
+    for (int h = 0; h < R2; ++h) {
+      v[h] = base[k1 * S::EK + h * S::ET];
+      if (h > 0) {
+        const T w = tw2[h * R1 + k1];
+        v[h] = INV ? cmulc(v[h], w) : cmul(v[h], w);
+      }
+    }
+    dft_r<T, R2, INV>(v);
+#pragma unroll
+    for (int k = 0; k < NO; ++k) {
+      const long long o = (k1 + R1 * k) * a.es;
+      if (MODE == LN_AXPY) dst[o] = csub(xi[MODE == LN_AXPY ? i * NO + k : 0], cscale(v[k], sc));
+      else dst[o] = v[k];
+    }
+  }
+}
+
 // Z_MUL: a block takes lb adjacent kx of one ky, all three
 // components: 3 lb sequences of length 2nz interleaved in LDS.
 struct IsoZ {
@@ -463,6 +566,15 @@ void line_shape(int ln, long long nlines, int e, int& lb, int& nthr) {
   nthr = std::min(1024, std::max(64, (els / e + 63) / 64 * 64));
 }
 
+template <class T, bool INV, int MODE, bool SFL, bool ZIN, bool ZOUT, int LN>
+Status run_line(const IsoLines& a, hipStream_t s) {
+  typedef LineShape<T, LN, SFL> S;
+  auto fn = k_iso_line<T, INV, MODE, SFL, ZIN, ZOUT, LN>;
+  if (S::lds() > 65536) ISOCHK(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::lds()));
+  hipLaunchKernelGGL(fn, dim3((unsigned)(a.nlines / S::LB)), dim3(S::NT), S::lds(), s, a);
+  return Status();
+}
+
 template <class T, bool INV, int MODE, bool SFL, bool ZIN, bool ZOUT>
 Status run_lines(IsoLines a, hipStream_t s) {
   int lb, nthr;
@@ -475,6 +587,24 @@ Status run_lines(IsoLines a, hipStream_t s) {
   if (bytes > 65536) ISOCHK(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
   hipLaunchKernelGGL(fn, dim3((unsigned)(a.nlines / lb)), dim3(nthr), bytes, s, a);
   return Status();
+}
+
+// One pass of the apply: the compile-time kernel for padded lengths 16 .. 256 when
+// its blocks of lines divide each component's lines (the pass has 3 nz ny or
+// 6 nz nx of them), else the run-time kernel (lengths below 16, where a block of
+// 16 lines would be under a wavefront, and grids of a few lines).
+template <class T, bool INV, int MODE, bool SFL, bool ZIN, bool ZOUT>
+Status apply_lines(const IsoLines& a, hipStream_t s) {
+  if ((a.nlines / 3) % (sizeof(T) == 8 ? 16 : 8) == 0) {
+    switch (a.ln) {
+      case 4: return run_line<T, INV, MODE, SFL, ZIN, ZOUT, 4>(a, s);
+      case 5: return run_line<T, INV, MODE, SFL, ZIN, ZOUT, 5>(a, s);
+      case 6: return run_line<T, INV, MODE, SFL, ZIN, ZOUT, 6>(a, s);
+      case 7: return run_line<T, INV, MODE, SFL, ZIN, ZOUT, 7>(a, s);
+      case 8: return run_line<T, INV, MODE, SFL, ZIN, ZOUT, 8>(a, s);
+    }
+  }
+  return run_lines<T, INV, MODE, SFL, ZIN, ZOUT>(a, s);
 }
 
 // in-place unnormalised 3-D FFT of C components [C][2^l0][2^l1][2^l2], FP64
@@ -547,7 +677,7 @@ Status apply_t(psfd_iso_plan* p, const T* deps, const T* x, T* y, T* W, int stag
     b.lcin_s = 0; b.sin_s = 0; b.sout_s = nx;
     b.lcin_d = ly; b.sin_d = 2 * nx; b.sout_d = plane;
     b.lvmod = lz + ly;
-    st = run_lines<T, false, LN_VLOAD, false, true, false>(b, s);
+    st = apply_lines<T, false, LN_VLOAD, false, true, false>(b, s);
     if (!st.ok()) return st;
   }
   if (stage < 0 || stage == 1) {  // columns y < ny -> 2ny
@@ -555,7 +685,7 @@ Status apply_t(psfd_iso_plan* p, const T* deps, const T* x, T* y, T* W, int stag
     b.src = W; b.dst = W;
     b.nlines = 3 * nz * 2 * nx; b.ln = ly + 1; b.lload = ly; b.lstore = ly + 1; b.es = 2 * nx;
     b.lcin_s = b.lcin_d = lx + 1; b.sin_s = b.sin_d = 1; b.sout_s = b.sout_d = plane;
-    st = run_lines<T, false, LN_PLAIN, true, true, false>(b, s);
+    st = apply_lines<T, false, LN_PLAIN, true, true, false>(b, s);
     if (!st.ok()) return st;
   }
   if (stage < 0 || stage == 2) {
@@ -589,7 +719,7 @@ Status apply_t(psfd_iso_plan* p, const T* deps, const T* x, T* y, T* W, int stag
     b.src = W; b.dst = W;
     b.nlines = 3 * nz * 2 * nx; b.ln = ly + 1; b.lload = ly + 1; b.lstore = ly; b.es = 2 * nx;
     b.lcin_s = b.lcin_d = lx + 1; b.sin_s = b.sin_d = 1; b.sout_s = b.sout_d = plane;
-    st = run_lines<T, true, LN_PLAIN, true, false, true>(b, s);
+    st = apply_lines<T, true, LN_PLAIN, true, false, true>(b, s);
     if (!st.ok()) return st;
   }
   if (stage < 0 || stage == 4) {  // rows 2nx -> first nx, y = x - w / (8 n)
@@ -599,7 +729,7 @@ Status apply_t(psfd_iso_plan* p, const T* deps, const T* x, T* y, T* W, int stag
     b.lcin_s = ly; b.sin_s = 2 * nx; b.sout_s = plane;
     b.lcin_d = 0; b.sin_d = 0; b.sout_d = nx;
     b.scale = 1.0 / (8.0 * (double)(nx * ny * nz));
-    st = run_lines<T, true, LN_AXPY, false, false, true>(b, s);
+    st = apply_lines<T, true, LN_AXPY, false, false, true>(b, s);
     if (!st.ok()) return st;
   }
   ISOCHK(hipGetLastError());

@@ -282,3 +282,34 @@ def test_isolated_apply_max_size():
         say("  reciprocity", dt, abs(lhs - rhs) / abs(lhs))
         assert abs(lhs - rhs) <= tol * abs(lhs)
         assert torch.equal(plan.apply(torch.zeros_like(one), a), a)
+
+
+# padded line lengths 16 .. 256 along x and y (the compile-time line passes) and
+# below (the run-time ones), z lengths from 4 to 256, flat and slab-like boxes
+LINE_SHAPES = [(8, 8, 2), (4, 8, 16), (16, 8, 32), (32, 16, 4), (64, 32, 8), (128, 64, 4), (64, 128, 16),
+               (16, 16, 128), (8, 16, 64)]
+
+
+@pytest.mark.parametrize("shape", LINE_SHAPES, ids=["%dx%dx%d" % s for s in LINE_SHAPES])
+def test_iso_line_lengths_match_the_padded_convolution(shape):
+    """The apply against NumPy's padded FFT convolution with the plan's own exported table
+    (which other tests pin): FP64 1e-12, FP32 2e-6 of the largest output, the rounding of
+    O(log N) passes per axis."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    nx, ny, nz = shape
+    say("isolated line lengths", shape)
+    plan = api.IsoPlan(nx, ny, nz, (1.5, 2.0, 2.5), 13.5, 1.0 + 0.02j, radius_nm=9.0)
+    tab, _, _ = plan.table()
+    tab = tab.cpu().numpy()
+    T = [[tab[0], tab[3], tab[4]], [tab[3], tab[1], tab[5]], [tab[4], tab[5], tab[2]]]
+    de = clips.random_complex((nz, ny, nx), seed=nx) * 0.2
+    x = clips.random_complex((3, nz, ny, nx), seed=ny)
+    f = np.fft.fftn((2 * np.pi / 13.5) ** 2 * de * x, s=(2 * nz, 2 * ny, 2 * nx), axes=(1, 2, 3))
+    w = np.stack([sum(T[i][j] * f[j] for j in range(3)) for i in range(3)])
+    ref = x - np.fft.ifftn(w, axes=(1, 2, 3))[:, :nz, :ny, :nx]
+    for dt, bar in ((torch.complex128, 1e-12), (torch.complex64, 2e-6)):
+        y = plan.apply(torch.from_numpy(de).to(dev).to(dt), torch.from_numpy(x).to(dev).to(dt))
+        err = np.abs(y.cpu().numpy() - ref).max() / np.abs(ref).max()
+        say("  ", dt, "err %.2e" % err)
+        assert err <= bar
