@@ -33,6 +33,7 @@
 #include "fft_lds.hpp"
 #include "gmres_host.hpp"
 #include "iso.hpp"
+#include "regfft.hpp"
 
 using namespace psfd;
 
@@ -227,15 +228,36 @@ __global__ void __launch_bounds__((LineShape<T, LN, SFL>::NT)) k_iso_line(IsoLin
 
 // Z_MUL: a block takes lb adjacent kx of one ky, all three
 // components: 3 lb sequences of length 2nz interleaved in LDS.
+//
+// The table is the octant kx <= nx, ky <= ny, kz <= nz of the kernel: an axis's
+// offset plane j = -n couples no two voxels of the box, and with those planes
+// zeroed xx, yy, zz are even along every axis, xy is odd in kx and ky, xz in kx
+// and kz, yz in ky and kz. A column with kx > nx (ky > ny, kz > nz) takes the
+// entries of 2nx - kx (2ny - ky, 2nz - kz) with those signs. Layout
+// [ny + 1][nz + 1][6][nxp] (entries xx, yy, zz, xy, xz, yz; nxp: nx + 1 up to a
+// multiple of 16), so that adjacent columns read adjacent words. The block order
+// (z_block) puts the up to four columns that share an entry on one XCD's L2 at
+// about the same time: the table costs HBM a quarter of its use.
 struct IsoZ {
   void* w;
-  const void* table;   // pencil-major: block (ky, kx / lb), then [nz + 1][6][lb] (kz <= nz); entries xx, yy, zz, xy, xz, yz
+  const void* table;
   int lnz, lnx2;       // log2 nz, log2 2nx
+  int ny, nxp;
   int lb, llb;
   long long plane;     // 2ny 2nx
-  long long n8;        // 8 nx ny nz
+  unsigned wbytes, tbytes;  // sizes of w and table
   const void* tw;
 };
+
+// Logical block of a z pass of nbx blocks per row: XCD x takes a contiguous run
+// of ids, whose rows ky come in the order 0, 1, 2ny - 1, 2, 2ny - 2, ..., ny
+// (a row next to its mirror). bx: the block within the row.
+PSFD_D void z_block(unsigned hw, unsigned nbx, int ny, int& ky, unsigned& bx) {
+  const unsigned lid = xcd_order(hw, nbx * 2u * (unsigned)ny);
+  const int r = (int)(lid / nbx);
+  bx = lid - (unsigned)r * nbx;
+  ky = r & 1 ? (r + 1) >> 1 : (r ? 2 * ny - (r >> 1) : 0);
+}
 
 // Each thread owns the table products of points tid + i nthr (i < ZPT) and
 // loads their six table entries before the forward z FFT, so that the loads
@@ -255,16 +277,18 @@ PSFD_D void zmul_point(T* f, int lb, const T t[6]) {
   f[2 * lb] = cadd(cadd(cmul(t[4], f0), cmul(t[5], f1)), cmul(t[2], f2));
 }
 
+// the six entries of (kx, ky, kz)
 template <class T>
-PSFD_D void zmul_entries(const T* tb, int kz, int li, int nz, int lb, T t[6]) {
-  const bool up = kz > nz;
-  const T* q = tb + (up ? 2 * nz - kz : kz) * 6 * lb + li;
+PSFD_D void zmul_entries(const T* tab, int kx, int ky, int kz, int nx, int ny, int nz, int nxp, T t[6]) {
+  typedef typename real_of<T>::type R;
+  const bool ux = kx > nx, uy = ky > ny, uz = kz > nz;
+  const T* q = tab + ((long long)(uy ? 2 * ny - ky : ky) * (nz + 1) + (uz ? 2 * nz - kz : kz)) * 6 * nxp +
+               (ux ? 2 * nx - kx : kx);
 #pragma unroll
-  for (int k = 0; k < 6; ++k) t[k] = q[k * lb];
-  if (up) {
-    t[4].x = -t[4].x; t[4].y = -t[4].y;
-    t[5].x = -t[5].x; t[5].y = -t[5].y;
-  }
+  for (int k = 0; k < 6; ++k) t[k] = q[k * nxp];
+  t[3] = cscale(t[3], (R)(ux != uy ? -1 : 1));
+  t[4] = cscale(t[4], (R)(ux != uz ? -1 : 1));
+  t[5] = cscale(t[5], (R)(uy != uz ? -1 : 1));
 }
 
 template <class T>
@@ -273,23 +297,21 @@ __global__ void k_iso_zmul(IsoZ a) {
   T* lds = reinterpret_cast<T*>(smem);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int nz = 1 << a.lnz, lb = a.lb, nsq = 3 * lb, npts = 2 * nz * lb;
-  // logical block (ky, kx / lb) in XCD order: the blocks of adjacent kx runs
-  // fill the two halves of the same 128-byte lines of W, so they are kept on
-  // one L2 (else each XCD fetches the whole line for its half)
-  const unsigned nbx = gridDim.x;
-  const unsigned lid = xcd_order(blockIdx.y * nbx + blockIdx.x, nbx * gridDim.y);
-  const long long col = ((long long)(lid / nbx) << a.lnx2) + ((long long)(lid % nbx) << a.llb);
-  // this block's table entries: one contiguous run of (nz + 1) 6 lb values,
-  // point (kz, li) entry k at (kz * 6 + k) * lb + li for kz <= nz; a point
-  // kz > nz takes kz' = 2nz - kz, with xz and yz negated (the table is even in
-  // kz, those two entries odd)
-  const T* tb = (const T*)a.table + ((long long)lid * (nz + 1) * 6 * lb);
+  // the blocks of adjacent kx runs fill the two halves of the same 128-byte
+  // lines of W, so they are kept on one L2 (else each XCD fetches the whole line
+  // for its half)
+  int ky;
+  unsigned bx;
+  z_block(blockIdx.x, (1u << a.lnx2) >> a.llb, a.ny, ky, bx);
+  const int kx0 = (int)(bx << a.llb), nx = 1 << (a.lnx2 - 1);
+  const long long col = ((long long)ky << a.lnx2) + kx0;
+  const T* tb = (const T*)a.table;
   constexpr int ZPT = Zpt<T>::v;
   T tt[ZPT > 0 ? ZPT : 1][6];
 #pragma unroll
   for (int i = 0; i < ZPT; ++i) {
     const int p = tid + i * nthr;
-    if (p < npts) zmul_entries(tb, p >> a.llb, p & (lb - 1), nz, lb, tt[i]);
+    if (p < npts) zmul_entries(tb, kx0 + (p & (lb - 1)), ky, p >> a.llb, nx, a.ny, nz, a.nxp, tt[i]);
   }
   T* w = (T*)a.w;
   for (int idx = tid; idx < nz * nsq; idx += nthr) {
@@ -306,7 +328,7 @@ __global__ void k_iso_zmul(IsoZ a) {
   }
   for (int p = tid + ZPT * nthr; p < npts; p += nthr) {
     T t[6];
-    zmul_entries(tb, p >> a.llb, p & (lb - 1), nz, lb, t);
+    zmul_entries(tb, kx0 + (p & (lb - 1)), ky, p >> a.llb, nx, a.ny, nz, a.nxp, t);
     zmul_point(lds + (p >> a.llb) * nsq + (p & (lb - 1)), lb, t);
   }
   __syncthreads();
@@ -318,8 +340,8 @@ __global__ void k_iso_zmul(IsoZ a) {
   }
 }
 
-// The same pass with the shape fixed at compile time (FFT length 2^LZ2, LB
-// columns, NT threads): every global load of a thread is issued before its
+// The pass-by-pass kernel with the shape fixed at compile time (FFT length 2^LZ2, LB
+// columns, NT threads; FP64, nz = 64): every global load of a thread is issued before its
 // first LDS write, the twiddles are staged in LDS so that no FFT pass waits on
 // the vector-memory counter of the table entries in flight, and the FFT index
 // arithmetic folds to constants.
@@ -332,10 +354,12 @@ __global__ void __launch_bounds__(NT) k_iso_zmul_ct(IsoZ a) {
   static_assert(NV * NT == NZ * NSQ && (1 << LLB) == LB, "z pass split");
   T* twl = lds + (2 * NZ) * NSQ;
   const int tid = threadIdx.x;
-  const unsigned nbx = gridDim.x;
-  const unsigned lid = xcd_order(blockIdx.y * nbx + blockIdx.x, nbx * gridDim.y);
-  const long long col = ((long long)(lid / nbx) << a.lnx2) + ((long long)(lid % nbx) << LLB);
-  const T* tb = (const T*)a.table + ((long long)lid * (NZ + 1) * 6 * LB);
+  int ky;
+  unsigned bx;
+  z_block(blockIdx.x, (1u << a.lnx2) >> LLB, a.ny, ky, bx);
+  const int kx0 = (int)(bx << LLB), nx = 1 << (a.lnx2 - 1);
+  const long long col = ((long long)ky << a.lnx2) + kx0;
+  const T* tb = (const T*)a.table;
   const T* twg = (const T*)a.tw + 2 * NZ;
   const T tw0 = twg[tid & (2 * NZ - 1)];
   __builtin_amdgcn_sched_barrier(0);
@@ -352,7 +376,7 @@ __global__ void __launch_bounds__(NT) k_iso_zmul_ct(IsoZ a) {
 #pragma unroll
   for (int i = 0; i < ZPT; ++i) {
     const int pt = tid + i * NT;
-    if (pt < NPTS) zmul_entries(tb, pt >> LLB, pt & (LB - 1), NZ, LB, tt[i]);
+    if (pt < NPTS) zmul_entries(tb, kx0 + (pt & (LB - 1)), ky, pt >> LLB, nx, a.ny, NZ, a.nxp, tt[i]);
   }
   if (tid < 2 * NZ) twl[tid] = tw0;
 #pragma unroll
@@ -371,7 +395,7 @@ __global__ void __launch_bounds__(NT) k_iso_zmul_ct(IsoZ a) {
   }
   for (int pt = tid + ZPT * NT; pt < NPTS; pt += NT) {
     T t[6];
-    zmul_entries(tb, pt >> LLB, pt & (LB - 1), NZ, LB, t);
+    zmul_entries(tb, kx0 + (pt & (LB - 1)), ky, pt >> LLB, nx, a.ny, NZ, a.nxp, t);
     zmul_point(lds + (pt >> LLB) * NSQ + (pt & (LB - 1)), LB, t);
   }
   __syncthreads();
@@ -387,6 +411,132 @@ __global__ void __launch_bounds__(NT) k_iso_zmul_ct(IsoZ a) {
     const int idx = tid + k * NT, li = idx & (LB - 1), r = idx >> LLB;
     const int iz = r / 3, c = r - 3 * iz;
     ((T*)a.w)[(long long)(c * NZ + iz) * a.plane + col + li] = v[k];
+  }
+}
+
+// The z pass in registers (16 columns per block, padded length n = R1 R2).
+// R2 threads per column: thread t loads planes t + R2 j of the three components
+// and transforms each over j (R1 points, zero half not read); one exchange
+// through LDS; the thread of residue k1 (k1 = t + R2 i) transforms over t and
+// then holds kz = k1 + R1 k2 of ALL three components, multiplies them by the
+// 3 x 3 table in registers, transforms back over k2 and exchanges in place; the
+// last DFT's kept half are the planes the thread loaded. Two exchanges in all,
+// where the pass-by-pass kernel above takes six LDS round trips and the product
+// another. At 128 x 128 x 64 in FP32 it is bound by the 252 MB it moves and by its
+// VALU work (about 2.4k instructions per wavefront) alike: 61 us, 4.1 TB/s.
+template <int LZ2> struct ZregShape {
+  static constexpr int LB = 16, N = 1 << LZ2, NZ = N / 2, R1 = 1 << ((LZ2 + 1) / 2), R2 = N / R1, K = R1 / R2, H = R1 / 2;
+  static constexpr int NT = LB * R2;
+  template <class T> static constexpr int lds() { return (N * LB + N) * (int)sizeof(T); }
+};
+
+template <class T, int LZ2>
+__global__ void __launch_bounds__((ZregShape<LZ2>::NT), 2) k_iso_zreg(IsoZ a) {
+  typedef ZregShape<LZ2> S;
+  typedef typename real_of<T>::type R;
+  constexpr int LB = S::LB, N = S::N, NZ = S::NZ, R1 = S::R1, R2 = S::R2, K = S::K, H = S::H, NT = S::NT;
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* buf = reinterpret_cast<T*>(smem);
+  T* twl = buf + N * LB;
+  const int tid = threadIdx.x, li = tid & (LB - 1), t = tid >> 4;
+  int ky;
+  unsigned bx;
+  z_block(blockIdx.x, (1u << a.lnx2) / LB, a.ny, ky, bx);
+  const int nx = 1 << (a.lnx2 - 1), kx = (int)bx * LB + li;
+  const unsigned plane = (unsigned)a.plane * (unsigned)sizeof(T);
+  const LaneBuf w(a.w, a.wbytes), tb(a.table, a.tbytes);
+  const unsigned goff = t * plane + (unsigned)((ky << a.lnx2) + kx) * (unsigned)sizeof(T);
+  auto at = [&](int c, int j) { return (unsigned)(c * NZ + R2 * j) * plane; };
+  T v[3][H];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int j = 0; j < H; ++j) w.load(v[c][j], goff, at(c, j));
+  {
+    const T* tg = (const T*)a.tw + N;
+#pragma unroll
+    for (int i = 0; i < (N + NT - 1) / NT; ++i)
+      if (N % NT == 0 || tid + i * NT < N) twl[tid + i * NT] = tg[tid + i * NT];
+  }
+  // table rows: entry k of (kx', ky', kz') at (ky' (nz + 1) + kz') 6 rs + k rs + kx',
+  // rs = nxp values; kz' = l = t + l0, or 2nz - l for the upper half
+  const unsigned rs = (unsigned)a.nxp * (unsigned)sizeof(T), row = 6u * rs;
+  const unsigned ky0 = (unsigned)(ky > a.ny ? 2 * a.ny - ky : ky) * (NZ + 1) * row;
+  const unsigned kxo = (unsigned)(kx > nx ? 2 * nx - kx : kx) * (unsigned)sizeof(T);
+  const unsigned tlo = kxo + t * row, thi = kxo + (R2 - t) * row;
+  // signs of the mirrored columns: component x changes its sign with kx, y with
+  // ky (on load and store; the product then takes the octant's entries)
+  const R sx = kx > nx ? (R)-1 : (R)1, sy = ky > a.ny ? (R)-1 : (R)1;
+  T X[3][K][R2];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    T u[R1];
+#pragma unroll
+    for (int j = 0; j < H; ++j) u[j] = c == 0 ? cscale(v[c][j], sx) : c == 1 ? cscale(v[c][j], sy) : v[c][j];
+    dft_r_half<T, R1, false>(u);
+    if (c > 0) __syncthreads();  // the previous component has been read
+#pragma unroll
+    for (int k = 0; k < R1; ++k) buf[(k * R2 + t) * LB + li] = u[k];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const int k1 = t + R2 * i;
+#pragma unroll
+      for (int s = 0; s < R2; ++s) {
+        T x = buf[(k1 * R2 + s) * LB + li];
+        if (s > 0) x = cmul(x, twl[s * k1]);
+        X[c][i][s] = x;
+      }
+      dft_r<T, R2, false>(X[c][i]);
+#pragma unroll
+      for (int s = 0; s < R2; ++s) pin(X[c][i][s]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+#pragma unroll
+    for (int k2 = 0; k2 < R2; ++k2) {
+      const int l0 = R2 * i + R1 * k2;  // kz = t + l0
+      T e[6];
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        if (l0 < NZ) tb.load(e[k], tlo, ky0 + l0 * row + k * rs);
+        else tb.load(e[k], thi, ky0 + (N - R2 - l0) * row + k * rs);
+      }
+      // xz and yz change their sign for kz > nz (at l0 = nz: t > 0)
+      if (l0 >= NZ) {
+        const R sz = l0 == NZ && t == 0 ? (R)1 : (R)-1;
+        e[4] = cscale(e[4], sz);
+        e[5] = cscale(e[5], sz);
+      }
+      const T f0 = X[0][i][k2], f1 = X[1][i][k2], f2 = X[2][i][k2];
+      X[0][i][k2] = cadd(cadd(cmul(e[0], f0), cmul(e[3], f1)), cmul(e[4], f2));
+      X[1][i][k2] = cadd(cadd(cmul(e[3], f0), cmul(e[1], f1)), cmul(e[5], f2));
+      X[2][i][k2] = cadd(cadd(cmul(e[4], f0), cmul(e[5], f1)), cmul(e[2], f2));
+#pragma unroll
+      for (int c = 0; c < 3; ++c) pin(X[c][i][k2]);
+    }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const int k1 = t + R2 * i;
+      dft_r<T, R2, true>(X[c][i]);
+#pragma unroll
+      for (int s = 0; s < R2; ++s) {
+        T x = X[c][i][s];
+        if (s > 0) x = cmulc(x, twl[s * k1]);
+        buf[(k1 * R2 + s) * LB + li] = x;
+      }
+    }
+    __syncthreads();
+    T u[R1];
+#pragma unroll
+    for (int k = 0; k < R1; ++k) u[k] = buf[(k * R2 + t) * LB + li];
+    dft_r<T, R1, true>(u);
+#pragma unroll
+    for (int j = 0; j < H; ++j) w.store(c == 0 ? cscale(u[j], sx) : c == 1 ? cscale(u[j], sy) : u[j], goff, at(c, j));
   }
 }
 
@@ -475,38 +625,34 @@ __global__ void k_iso_restrict(const double2* __restrict__ g, double2* __restric
   t[idx] = cscale(g[src], scale);
 }
 
-// the table in the z-pencil order of the apply: for block (ky, kb) of lb
-// adjacent kx, [nz + 1][6][lb] (kz = 0 .. nz), from the natural [6][2nz][2ny][2nx]
+// the octant table of the apply, [ny + 1][nz + 1][6][nxp] (columns beyond nx
+// zero), from the natural [6][2nz][2ny][2nx]
 template <class T>
-__global__ void k_iso_pencil_table(const double2* __restrict__ nat, T* __restrict__ out, int lz, int ly, int lx,
-                                   int llb) {
+__global__ void k_iso_octant_table(const double2* __restrict__ nat, T* __restrict__ out, int lz, int ly, int lx,
+                                   int nxp) {
   const long long n8 = 8LL << (lz + ly + lx);
-  const int nz1 = (1 << lz) + 1;
-  const long long tot = 6LL * nz1 * (4LL << (ly + lx));
+  const int nz1 = (1 << lz) + 1, ny1 = (1 << ly) + 1;
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= tot) return;
-  const int lb = 1 << llb;
-  const int li = (int)(idx & (lb - 1));
-  const long long r = idx >> llb;
+  if (idx >= 6LL * nz1 * ny1 * nxp) return;
+  const int kx = (int)(idx % nxp);
+  const long long r = idx / nxp;
   const int k = (int)(r % 6);
   const long long r2 = r / 6;
-  const int kz = (int)(r2 % nz1);
-  const long long blk = r2 / nz1;                 // ky * (2nx / lb) + kb
-  const int nkb = (2 << lx) >> llb;
-  const long long ky = blk / nkb, kb = blk - ky * nkb;
-  const long long src = k * n8 + (((long long)kz << (ly + 1)) + ky) * (2LL << lx) + (kb << llb) + li;
-  out[idx] = from_d<T>(nat[src]);
+  const int kz = (int)(r2 % nz1), ky = (int)(r2 / nz1);
+  const long long src = k * n8 + (((long long)kz << (ly + 1)) + ky) * (2LL << lx) + kx;
+  out[idx] = kx <= (1 << lx) ? from_d<T>(nat[src]) : cmake<T>(0, 0);
 }
 
-// zero the offset plane jz = -nz (index nz on the 2n grid) of the samples
-// [6][2nz][2ny][2nx]: it couples no two voxels of the box, and without it the
-// samples are even (xx, yy, zz, xy) or odd (xz, yz) in jz
-__global__ void k_iso_zero_zplane(double2* __restrict__ k, int lz, int ly, int lx) {
-  const long long pl = 4LL << (ly + lx);
+// zero the offset planes j = -n of every axis (index n on the 2n grid) of the
+// samples [6][2nz][2ny][2nx]: they couple no two voxels of the box, and without
+// them the samples are even or odd along each axis
+__global__ void k_iso_zero_planes(double2* __restrict__ k, int lz, int ly, int lx) {
+  const long long per = 8LL << (lz + ly + lx);
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= 6 * pl) return;
-  const long long c = idx / pl, e = idx - c * pl;
-  k[c * (8LL << (lz + ly + lx)) + ((long long)1 << lz) * pl + e] = make_double2(0.0, 0.0);
+  if (idx >= 6 * per) return;
+  const long long r = idx % per;
+  const int jx = (int)(r & ((2 << lx) - 1)), jy = (int)((r >> (lx + 1)) & ((2 << ly) - 1)), jz = (int)(r >> (lx + ly + 2));
+  if (jx == 1 << lx || jy == 1 << ly || jz == 1 << lz) k[idx] = make_double2(0.0, 0.0);
 }
 
 constexpr int KB = 256;      // threads per block of the elementwise kernels
@@ -535,8 +681,9 @@ struct psfd_iso_plan {
   double R = 0.0, k0 = 0.0;
   int device = 0;
   double2* tab64 = nullptr;  // [6][2nz][2ny][2nx]
-  double2* ptab64 = nullptr; // tab64 in the z-pencil order of the FP64 apply
-  float2* ptab32 = nullptr;  // FP32 rounding, in the z-pencil order of the FP32 apply
+  double2* ptab64 = nullptr; // octant table of the FP64 apply
+  float2* ptab32 = nullptr;  // its FP32 rounding
+  int nxp = 0;               // row length of the octant tables
   double2* tw64 = nullptr;   // tw[m + i] = exp(-2 pi i i / m), m = 2 .. ISO_TW_MAX
   float2* tw32 = nullptr;
   void* work[2] = {nullptr, nullptr};  // W [3][nz][2ny][2nx] per dtype (C64, C128)
@@ -693,22 +840,53 @@ Status apply_t(psfd_iso_plan* p, const T* deps, const T* x, T* y, T* W, int stag
     z.w = W; z.table = tab_of<T>(p); z.lnz = lz; z.lnx2 = lx + 1;
     z.lb = z_lb<T>((int)nz, (int)nx);
     z.llb = ilog2_exact(z.lb);
-    z.plane = plane; z.n8 = 8 * nx * ny * nz; z.tw = tw;
+    z.plane = plane; z.ny = (int)ny; z.nxp = p->nxp; z.tw = tw;
+    z.wbytes = (unsigned)(3 * nz * plane * sizeof(T));
+    z.tbytes = (unsigned)(6 * (nz + 1) * (ny + 1) * p->nxp * sizeof(T));
     const int els = (int)(2 * nz) * 3 * z.lb;
     const int npts = (int)(2 * nz) * z.lb;
     const int pre = Zpt<T>::v ? (npts / std::max(1, Zpt<T>::v) + 63) / 64 * 64 : 64;
     const int nthr = std::min(1024, std::max({64, (els / ZFE + 63) / 64 * 64, pre}));
     if (els > ZFE * nthr) return bad(PSFD_ERR_UNSUPPORTED_SIZE, "z pencil tile exceeds the FFT budget");
     const size_t bytes = (size_t)els * sizeof(T);
-    const dim3 grid((unsigned)(2 * nx / z.lb), (unsigned)(2 * ny));
-    // compile-time shapes for the 64-plane grids at the measured block widths
-    constexpr int LBC = sizeof(T) == 8 ? 8 : 4, NTC = sizeof(T) == 8 ? 512 : 192;
-    if (lz == 6 && z.lb == LBC && nthr == NTC && env_int_iso("PSFD_ISO_ZCT", 1)) {
-      auto fc = k_iso_zmul_ct<T, 7, LBC, NTC>;
-      const size_t bc = bytes + (size_t)128 * sizeof(T);
-      if (bc > 65536) ISOCHK(hipFuncSetAttribute((const void*)fc, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bc));
-      hipLaunchKernelGGL(fc, grid, dim3(NTC), bc, s, z);
-    } else {
+    const dim3 grid((unsigned)(2 * nx / z.lb * 2 * ny));
+    auto reg = [&](auto lz2) {
+      constexpr int LZ2 = decltype(lz2)::value;
+      typedef ZregShape<LZ2> S;
+      const int bz = S::template lds<T>();
+      hipLaunchKernelGGL((k_iso_zreg<T, LZ2>), dim3((unsigned)(2 * nx / S::LB * 2 * ny)), dim3(S::NT), (size_t)bz, s, z);
+      return true;
+    };
+    // the register kernel where its 16-column blocks and lengths apply: nz 8 .. 128
+    // in FP32, 8 .. 32 in FP64 (at nz = 64 a thread would hold 48 complex128
+    // values); there the 64-plane pass-by-pass kernel with compile-time shapes
+    // (4 columns and 192 threads, as measured). Z pass, register against
+    // pass-by-pass kernel (us): 128 x 128 x 64 FP32 61 / 75 (with the table of 1 + nz
+    // planes of every column 85), 128 x 128 x 32 FP32 29.7 / 53, FP64 45 / 71,
+    // 64 x 64 x 16 FP32 7.6 / 9.7, FP64 9.1 / 11.4, 32 x 32 x 16 FP64 6.3 / 6.8.
+    // PSFD_ISO_ZCT=0 selects the run-time shapes everywhere.
+    bool done = false;
+    if (env_int_iso("PSFD_ISO_ZCT", 1)) {
+      if (nx >= 8) {
+        if (lz == 3) done = reg(std::integral_constant<int, 4>());
+        if (lz == 4) done = reg(std::integral_constant<int, 5>());
+        if (lz == 5) done = reg(std::integral_constant<int, 6>());
+        if constexpr (sizeof(T) == 8) {
+          if (lz == 6) done = reg(std::integral_constant<int, 7>());
+          if (lz == 7) done = reg(std::integral_constant<int, 8>());
+        }
+      }
+      if constexpr (sizeof(T) == 16) {
+        if (!done && lz == 6 && z.lb == 4 && nthr == 192) {
+          auto fc = k_iso_zmul_ct<T, 7, 4, 192>;
+          const size_t bc = bytes + (size_t)128 * sizeof(T);
+          if (bc > 65536) ISOCHK(hipFuncSetAttribute((const void*)fc, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bc));
+          hipLaunchKernelGGL(fc, grid, dim3(192), bc, s, z);
+          done = true;
+        }
+      }
+    }
+    if (!done) {
       auto fn = k_iso_zmul<T>;
       if (bytes > 65536) ISOCHK(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
       hipLaunchKernelGGL(fn, grid, dim3(nthr), bytes, s, z);
@@ -801,9 +979,10 @@ Status iso_create(const psfd_iso_problem& pr, psfd_iso_plan*& out) {
   ISOCHK(hipMalloc((void**)&g, 6 * Mtot * sizeof(double2)));
   struct Free { double2* q; ~Free() { if (q) (void)hipFree(q); } } fg{g};
   ISOCHK(hipMalloc((void**)&p->tab64, 6 * n8 * sizeof(double2)));
-  const long long nhalf = 6LL * (nn[0] + 1) * 4 * nn[1] * nn[2];  // pencil tables: kz = 0 .. nz
-  ISOCHK(hipMalloc((void**)&p->ptab64, nhalf * sizeof(double2)));
-  ISOCHK(hipMalloc((void**)&p->ptab32, nhalf * sizeof(float2)));
+  p->nxp = (nn[2] + 1 + 15) / 16 * 16;
+  const long long noct = 6LL * (nn[0] + 1) * (nn[1] + 1) * p->nxp;
+  ISOCHK(hipMalloc((void**)&p->ptab64, noct * sizeof(double2)));
+  ISOCHK(hipMalloc((void**)&p->ptab32, noct * sizeof(float2)));
   double2* kev = nullptr;
   ISOCHK(hipMalloc((void**)&kev, 6 * n8 * sizeof(double2)));
   struct Free2 { double2* q; ~Free2() { if (q) (void)hipFree(q); } } fk{kev};
@@ -822,20 +1001,20 @@ Status iso_create(const psfd_iso_problem& pr, psfd_iso_plan*& out) {
   hipLaunchKernelGGL(k_iso_restrict, dim3((unsigned)((6 * n8 + 255) / 256)), dim3(256), 0, s, g, p->tab64,
                      p->ln[0], p->ln[1], p->ln[2], lo[0], lo[1], lo[2], 1.0 / (double)Mtot);
   ISOCHK(hipGetLastError());
-  // the samples with the offset plane jz = -nz zeroed: the same operator, a
-  // table even / odd in kz (the apply reads kz <= nz only)
+  // the samples with the offset planes j = -n zeroed: the same operator, a table
+  // even or odd along every axis (the apply reads its octant)
   ISOCHK(hipMemcpyAsync(kev, p->tab64, 6 * n8 * sizeof(double2), hipMemcpyDeviceToDevice, s));
-  hipLaunchKernelGGL(k_iso_zero_zplane, dim3((unsigned)((6 * n8 / (2 * nn[0]) + 255) / 256)), dim3(256), 0, s, kev,
-                     p->ln[0], p->ln[1], p->ln[2]);
+  hipLaunchKernelGGL(k_iso_zero_planes, dim3((unsigned)((6 * n8 + 255) / 256)), dim3(256), 0, s, kev, p->ln[0],
+                     p->ln[1], p->ln[2]);
   ISOCHK(hipGetLastError());
   st = fft3_c<false>(kev, 6, p->ln[0] + 1, p->ln[1] + 1, p->ln[2] + 1, p->tw64, s);
   if (!st.ok()) return st;
   st = fft3_c<false>(p->tab64, 6, p->ln[0] + 1, p->ln[1] + 1, p->ln[2] + 1, p->tw64, s);
   if (!st.ok()) return st;
-  hipLaunchKernelGGL(k_iso_pencil_table<double2>, dim3((unsigned)((nhalf + 255) / 256)), dim3(256), 0, s, kev,
-                     p->ptab64, p->ln[0], p->ln[1], p->ln[2], ilog2_exact(z_lb<double2>(nn[0], nn[2])));
-  hipLaunchKernelGGL(k_iso_pencil_table<float2>, dim3((unsigned)((nhalf + 255) / 256)), dim3(256), 0, s, kev,
-                     p->ptab32, p->ln[0], p->ln[1], p->ln[2], ilog2_exact(z_lb<float2>(nn[0], nn[2])));
+  hipLaunchKernelGGL(k_iso_octant_table<double2>, dim3((unsigned)((noct + 255) / 256)), dim3(256), 0, s, kev,
+                     p->ptab64, p->ln[0], p->ln[1], p->ln[2], p->nxp);
+  hipLaunchKernelGGL(k_iso_octant_table<float2>, dim3((unsigned)((noct + 255) / 256)), dim3(256), 0, s, kev,
+                     p->ptab32, p->ln[0], p->ln[1], p->ln[2], p->nxp);
   ISOCHK(hipGetLastError());
   ISOCHK(hipStreamSynchronize(s));
   out = p.release();
