@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <memory>
 #include <vector>
@@ -340,11 +341,32 @@ void transverse(const psfd_diff_plan& P, const Shape& sh, int nplanes, const voi
   }
 }
 
+// PSFD_DIFF_CT=0: the run-time kernels on every shape
+bool env_flag(const char* name) {
+  const char* e = std::getenv(name);
+  return !e || std::atoi(e) != 0;
+}
+
 template <class T>
 Status apply_t(psfd_diff_plan* P, const T* deps, const T* x, T* y, int precond, hipStream_t s) {
   const Shape& se = P->se;
   T* ws = (T*)(sizeof(T) == 8 ? P->ws32 : P->ws64);
   const int np = 3 * se.nz;
+  if (diff_ct_shape<T>(se.nx, se.ny, se.nz) && env_flag("PSFD_DIFF_CT")) {
+    const bool damp = precond == PSFD_PRECOND_DAMPING;
+    const double k0 = 2.0 * 3.14159265358979323846 / P->p.base.wavelength_nm;
+    const void* tw = sizeof(T) == 8 ? (const void*)P->gb->dc->tw32 : (const void*)P->gb->dc->tw64;
+    DiffPlaneArgs f{x, ws, damp ? deps : nullptr, nullptr, se.nz, P->p.zc0, P->p.ncz, k0 * k0, tw};
+    launch_diff_plane<T, false>(f, se.nx, se.ny, np + (damp ? 3 * P->p.ncz : 0), s);
+    TabLayout L{se.nx, se.ny};
+    DiffZcolArgs z{se.nx, se.ny, ws, ws + se.n3, P->p.zc0, P->p.ncz, P->gb->tab + L.off_kx(), P->gb->tab + L.off_ky(),
+                   P->zt, P->p.base.eps_bg * k0 * k0, tw};
+    launch_diff_zcol<T>(z, se.nz, damp, s);
+    DiffPlaneArgs b{ws, y, damp ? nullptr : deps, x, se.nz, P->p.zc0, P->p.ncz, k0 * k0, tw};
+    launch_diff_plane<T, true>(b, se.nx, se.ny, np, s);
+    DCHK(hipGetLastError());
+    return Status();
+  }
   transverse<T, false>(*P, se, np, x, ws, s);
   launch_diff_pencil<T>(*P, ws, DMODE_CURL, s);
   transverse<T, true>(*P, se, np, ws, y, s);
@@ -458,7 +480,8 @@ void diff_destroy(psfd_diff_plan* p) { delete p; }
 static Status ensure_ws(psfd_diff_plan* P, int dtype) {
   void*& w = dtype == PSFD_C64 ? P->ws32 : P->ws64;
   if (!w) {
-    DCHK(hipMalloc(&w, (size_t)P->se.n3 * (dtype == PSFD_C64 ? 8 : 16)));
+    // a field, and the transverse spectra of V x on the contrast planes
+    DCHK(hipMalloc(&w, (size_t)(P->se.n3 + 3 * P->se.nxny * P->p.ncz) * (dtype == PSFD_C64 ? 8 : 16)));
     P->owned.push_back(w);
   }
   return Status();

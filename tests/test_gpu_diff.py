@@ -60,6 +60,53 @@ def test_diff_apply_matches_oracle(case, precond):
         assert err <= bar
 
 
+# every z length of the compile-time kernels (one and two exchanges per transform)
+# with the plane sides at the edges of their rule: 16 and 128, the largest planes of
+# each precision (128 x 64 FP32 only), and shapes left to the run-time kernels
+# (8 x 16 planes; 32 z planes)
+CT_CASES = [
+    # nx, ny, nz (absorber), pe, pml
+    (16, 16, 16, 64, 8),
+    (64, 32, 16, 128, 24),
+    (16, 32, 32, 256, 32),
+    (32, 16, 64, 512, 60),
+    (16, 16, 32, 1024, 100),
+    (128, 16, 16, 64, 10),
+    (16, 128, 8, 64, 10),
+    (128, 64, 8, 64, 8),
+    (8, 16, 16, 64, 12),
+    (32, 32, 8, 32, 6),
+]
+
+
+@pytest.mark.parametrize("case", CT_CASES, ids=["%dx%dx%d" % (c[0], c[1], c[3]) for c in CT_CASES])
+@pytest.mark.parametrize("precond", ["none", "damping"])
+def test_diff_apply_shapes_match_oracle(case, precond, monkeypatch):
+    """Against the oracle (FP64 1e-11, FP32 2e-5 of the largest output, as above) and
+    against the run-time kernels (PSFD_DIFF_CT=0), with the contrast planes off centre."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    nx, ny, nz, pe, npml = case
+    p = problem(nx, ny, nz, 0.7 * nz, 2.0 * nx)
+    zc0 = npml + 1
+    D = Df.DiffSetup(p, pe, zc0, nz, npml)
+    plan = api.DiffPlan(p, pe, zc0, nz, npml)
+    de = clips.random_complex((nz, ny, nx), seed=nx + pe) * 0.1
+    x = clips.random_complex((3, pe, ny, nx), seed=pe + 1)
+    ref = Df.apply_diff(D, de, x, precond)
+    say("diff apply shapes", case, precond)
+    for dt, bar in ((torch.complex128, 1e-11), (torch.complex64, 2e-5)):
+        dd, xx = torch.from_numpy(de).to(dev).to(dt), torch.from_numpy(x).to(dev).to(dt)
+        y = plan.apply(dd, xx, precond=precond).cpu().numpy()
+        monkeypatch.setenv("PSFD_DIFF_CT", "0")
+        yr = plan.apply(dd, xx, precond=precond).cpu().numpy()
+        monkeypatch.delenv("PSFD_DIFF_CT")
+        scale = np.abs(ref).max()
+        say("  ", dt, "err %.2e, run-time kernels %.2e" % (np.abs(y - ref).max() / scale, np.abs(yr - ref).max() / scale))
+        assert np.abs(y - ref).max() <= bar * scale
+        assert np.abs(y - yr).max() <= bar * scale
+
+
 @pytest.mark.parametrize("precond", ["none", "damping"])
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 def test_diff_background_solve_matches_oracle(precond, prec):
