@@ -2,8 +2,17 @@
 // projections and ||w||^2 from one launch and the new norm by Pythagoras (a
 // second pass where the update leaves less than `cancel` of the norm), Givens
 // rotations and the small triangular solve on the host. Reductions run in a
-// fixed order (block partials, then one block per sum), so a solve is
+// fixed order (block partials, then one wavefront per sum), so a solve is
 // deterministic.
+//
+// A step runs on the device alone: the step kernel sums the partials, forms the
+// norm and scale the update takes, and writes them to mapped host memory; the
+// three launches of a second pass test its flag and return at once where it is not
+// needed. The host issues the next step's apply before it waits for a step's
+// scalars, so that the device never waits for the host's rotations; that apply is
+// dropped where the step ends the cycle. On a 32 x 32 x 16 isolated FP64 solve a step
+// took about 165 us of which its kernels were 45 (copies down and up, two waits and
+// their wake-ups); it takes about 55 now, 2.6 -> 0.91 ms the solve.
 #include "gmres_host.hpp"
 
 #include <algorithm>
@@ -17,7 +26,6 @@ namespace psfd {
 namespace {
 
 constexpr int KB = 256;      // threads per block
-constexpr int KNB = 1024;    // blocks of a reduction pass
 constexpr double ETA_MIXED = 1e-4;
 
 #define GMCHK(call)                                    \
@@ -33,125 +41,214 @@ Status bad(int code, const char* m) {
   return s;
 }
 
-// part[i * KNB + blk] = sum over the block's chunk of conj(V_i) w, i < nv (FP64 accumulation)
-template <class TV, class TW>
-__global__ void k_gm_dots(const TV* __restrict__ V, long long stride, const TW* __restrict__ w, long long n,
-                          double2* __restrict__ part) {
-  __shared__ double2 red[KB];
-  const int i = blockIdx.y;
-  const TV* v = V + i * stride;
-  double2 acc = make_double2(0.0, 0.0);
-  for (long long e = (long long)blockIdx.x * KB + threadIdx.x; e < n; e += (long long)KNB * KB) {
-    const double2 a = to_d(v[e]), c = to_d(w[e]);
-    acc.x += a.x * c.x + a.y * c.y;
-    acc.y += a.x * c.y - a.y * c.x;
+// part[i * GM_BLOCKS + blk] = sum over the block's chunk of conj(V_i) w, i < nv
+// (FP64 accumulation); a block takes four vectors, which share its reads of w.
+// second: only where the step kernel asked for a second pass
+template <class T>
+__global__ void __launch_bounds__(KB) k_gm_dots(const T* __restrict__ V, long long stride, int nv,
+                                                const T* __restrict__ w, long long n, double2* __restrict__ part,
+                                                const GmScalars* __restrict__ sc, bool second) {
+  __shared__ double2 red[4][KB / 64];
+  if (second && !sc->cancel) return;
+  const int i0 = blockIdx.y * 4, tid = threadIdx.x;
+  const T* v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = V + min(i0 + q, nv - 1) * stride;
+  double2 acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = make_double2(0.0, 0.0);
+  for (long long e = (long long)blockIdx.x * KB + tid; e < n; e += (long long)GM_BLOCKS * KB) {
+    const double2 c = to_d(w[e]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double2 a = to_d(v[q][e]);
+      acc[q].x += a.x * c.x + a.y * c.y;
+      acc[q].y += a.x * c.y - a.y * c.x;
+    }
   }
-  red[threadIdx.x] = acc;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      acc[q].x += __shfl_xor(acc[q].x, off, 64);
+      acc[q].y += __shfl_xor(acc[q].y, off, 64);
+    }
+    if ((tid & 63) == 0) red[q][tid >> 6] = acc[q];
+  }
   __syncthreads();
-  for (int h = KB / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + h]);
-    __syncthreads();
+  if (tid < 4 && i0 + tid < nv) {
+    double2 t = red[tid][0];
+#pragma unroll
+    for (int k = 1; k < KB / 64; ++k) t = cadd(t, red[tid][k]);
+    part[(long long)(i0 + tid) * GM_BLOCKS + blockIdx.x] = t;
   }
-  if (threadIdx.x == 0) part[(long long)i * KNB + blockIdx.x] = red[0];
 }
 
-// out[i] = sum of the KNB partials of i (one block per i, fixed order)
-__global__ void k_gm_sum(const double2* __restrict__ part, double2* __restrict__ out) {
-  __shared__ double2 red[KB];
-  const int i = blockIdx.x;
-  double2 acc = make_double2(0.0, 0.0);
-  for (int c = threadIdx.x; c < KNB; c += KB) acc = cadd(acc, part[(long long)i * KNB + c]);
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int h = KB / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + h]);
-    __syncthreads();
+// One block: the nv sums of the partials (one wavefront each, in a fixed order):
+// the projections h of a pass, then ||w||^2 before it; hn, inv and (first pass)
+// cancel as in GmScalars. What the host reads also goes to mapped host memory.
+__global__ void __launch_bounds__(1024) k_gm_step(const double2* __restrict__ part, int nv, double cancel,
+                                                  GmScalars* dev, GmScalars* host, bool second) {
+  __shared__ double2 h[GM_MAX + 2];
+  if (second && !dev->cancel) return;
+  const int lane = threadIdx.x & 63;
+  for (int i = threadIdx.x >> 6; i < nv; i += 16) {
+    double2 p[GM_BLOCKS / 64];
+#pragma unroll
+    for (int k = 0; k < GM_BLOCKS / 64; ++k) p[k] = part[(long long)i * GM_BLOCKS + lane + 64 * k];
+    double2 t = p[0];
+#pragma unroll
+    for (int k = 1; k < GM_BLOCKS / 64; ++k) t = cadd(t, p[k]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      t.x += __shfl_xor(t.x, off, 64);
+      t.y += __shfl_xor(t.y, off, 64);
+    }
+    if (lane == 0) h[i] = t;
   }
-  if (threadIdx.x == 0) out[i] = red[0];
+  __syncthreads();
+  for (int i = threadIdx.x; i < nv; i += 1024) {
+    if (second) {
+      dev->h2[i] = h[i];
+      host->h[i] = cadd(dev->h[i], h[i]);
+    } else {
+      dev->h[i] = host->h[i] = h[i];
+    }
+  }
+  if (threadIdx.x == 0) {
+    const double w2 = h[nv - 1].x;
+    double p2 = 0.0;
+    for (int i = 0; i < nv - 1; ++i) p2 += h[i].x * h[i].x + h[i].y * h[i].y;
+    const double d2 = w2 - p2;
+    const double hn = d2 == d2 ? sqrt(fmax(d2, 0.0)) : d2;  // (fmax would drop a NaN)
+    dev->hn = host->hn = hn;
+    dev->inv = hn > 0.0 ? 1.0 / hn : 1.0;
+    if (!second) {
+      dev->w2 = host->w2 = w2;
+      dev->cancel = !(hn >= cancel * sqrt(fmax(w2, 0.0)));
+    }
+  }
 }
 
-// w += sgn sum_{i < nv} coef[i] V_i (in FP64, stored in w's type)
-template <class TW, class TV>
-__global__ void k_gm_axpys(TW* __restrict__ w, const TV* __restrict__ V, long long stride,
-                           const double2* __restrict__ coef, int nv, long long n, double sgn) {
+// w = (w - sum_{i < nv} h_i V_i) inv (in FP64, stored in w's type), h and inv from
+// the step kernel. The first pass leaves the scale to the second where one follows.
+template <class T, bool SECOND>
+__global__ void __launch_bounds__(KB) k_gm_update(T* __restrict__ w, const T* __restrict__ V, long long stride,
+                                                  const GmScalars* __restrict__ sc, int nv, long long n) {
+  const bool cancel = sc->cancel != 0;
+  if (SECOND && !cancel) return;
   const long long e = (long long)blockIdx.x * KB + threadIdx.x;
   if (e >= n) return;
   double2 acc = to_d(w[e]);
+#pragma unroll 4
   for (int i = 0; i < nv; ++i) {
-    const double2 c = coef[i], v = to_d(V[i * stride + e]);
-    acc.x += sgn * (c.x * v.x - c.y * v.y);
-    acc.y += sgn * (c.x * v.y + c.y * v.x);
+    const double2 c = SECOND ? sc->h2[i] : sc->h[i], v = to_d(V[i * stride + e]);
+    acc.x -= c.x * v.x - c.y * v.y;
+    acc.y -= c.x * v.y + c.y * v.x;
   }
-  w[e] = from_d<TW>(acc);
+  w[e] = from_d<T>(cscale(acc, !SECOND && cancel ? 1.0 : sc->inv));
 }
 
-// out = a + s c (s real)
-__global__ void k_gm_comb(const double2* __restrict__ a, const double2* __restrict__ c, double s,
-                          double2* __restrict__ out, long long n) {
+// x += sum_{i < nv} coef_i V_i
+struct GmCoefs { double2 c[GM_MAX]; };
+template <class T>
+__global__ void __launch_bounds__(KB) k_gm_axpys(double2* __restrict__ x, const T* __restrict__ V, long long stride,
+                                                 GmCoefs coef, int nv, long long n) {
   const long long e = (long long)blockIdx.x * KB + threadIdx.x;
-  if (e < n) out[e] = make_double2(a[e].x + s * c[e].x, a[e].y + s * c[e].y);
+  if (e >= n) return;
+  double2 acc = x[e];
+#pragma unroll 4
+  for (int i = 0; i < nv; ++i) {
+    const double2 c = coef.c[i], v = to_d(V[i * stride + e]);
+    acc.x += c.x * v.x - c.y * v.y;
+    acc.y += c.x * v.y + c.y * v.x;
+  }
+  x[e] = acc;
 }
 
-// out = s a, converted to out's type (a may equal out)
-template <class TA, class TO>
-__global__ void k_gm_scale(const TA* a, double s, TO* out, long long n) {
+// r = b - ax and the partials of ||r||^2 (ax null: r = b)
+__global__ void __launch_bounds__(KB) k_gm_resid(const double2* __restrict__ b, const double2* __restrict__ ax,
+                                                 double2* __restrict__ r, long long n, double2* __restrict__ part) {
+  __shared__ double red[KB / 64];
+  const int tid = threadIdx.x;
+  double acc = 0.0;
+  for (long long e = (long long)blockIdx.x * KB + tid; e < n; e += (long long)GM_BLOCKS * KB) {
+    const double2 v = ax ? csub(b[e], ax[e]) : b[e];
+    r[e] = v;
+    acc += cabs2(v);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if ((tid & 63) == 0) red[tid >> 6] = acc;
+  __syncthreads();
+  if (tid == 0) {
+    double t = red[0];
+#pragma unroll
+    for (int k = 1; k < KB / 64; ++k) t += red[k];
+    part[blockIdx.x] = make_double2(t, 0.0);
+  }
+}
+
+// out = a inv in out's type, inv from the step kernel
+template <class TO>
+__global__ void __launch_bounds__(KB) k_gm_scale(const double2* __restrict__ a, const GmScalars* __restrict__ dev,
+                                                 TO* __restrict__ out, long long n) {
   const long long e = (long long)blockIdx.x * KB + threadIdx.x;
-  if (e < n) out[e] = from_d<TO>(cscale(to_d(a[e]), s));
+  if (e < n) out[e] = from_d<TO>(cscale(a[e], dev->inv));
 }
 
 template <class T>
 Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, const HostGmres& o, psfd_info& inf,
-               hipStream_t s) {
+               GmresWs& ws, hipStream_t s) {
   typedef std::complex<double> cd;
   const bool f32 = sizeof(T) == 8;
   const int m = o.m;
-  T* V = nullptr;
-  double2 *w64 = nullptr, *r64 = nullptr, *part = nullptr, *hd = nullptr;
+  // basis, A x and residual in one allocation
+  void* mem = nullptr;
   struct Free {
-    void* q[5];
-    ~Free() { for (void* a : q) if (a) (void)hipFree(a); }
-  } fr{{nullptr, nullptr, nullptr, nullptr, nullptr}};
-  GMCHK(hipMalloc((void**)&V, (size_t)(m + 1) * n * sizeof(T)));
-  fr.q[0] = V;
-  GMCHK(hipMalloc((void**)&w64, (size_t)n * sizeof(double2)));
-  fr.q[1] = w64;
-  GMCHK(hipMalloc((void**)&r64, (size_t)n * sizeof(double2)));
-  fr.q[2] = r64;
-  GMCHK(hipMalloc((void**)&part, (size_t)KNB * (m + 1) * sizeof(double2)));
-  fr.q[3] = part;
-  GMCHK(hipMalloc((void**)&hd, (size_t)(m + 1) * sizeof(double2)));
-  fr.q[4] = hd;
+    void*& q;
+    ~Free() { if (q) (void)hipFree(q); }
+  } fr{mem};
+  const size_t vbytes = ((size_t)(m + 1) * n * sizeof(T) + 255) / 256 * 256;
+  GMCHK(hipMalloc(&mem, vbytes + 2 * (size_t)n * sizeof(double2)));
+  T* V = (T*)mem;
+  double2* w64 = (double2*)((char*)mem + vbytes);
+  double2* r64 = w64 + n;
   const unsigned g1 = (unsigned)((n + KB - 1) / KB);
   const int dt = f32 ? PSFD_C64 : PSFD_C128;
-  std::vector<cd> hv(m + 1);
-  // hv[0..nv) = V_i^H x
-  auto dots = [&](auto Vb, int nv, auto x) -> Status {
-    typedef std::remove_cv_t<std::remove_pointer_t<decltype(Vb)>> TV;
-    typedef std::remove_cv_t<std::remove_pointer_t<decltype(x)>> TX;
-    hipLaunchKernelGGL((k_gm_dots<TV, TX>), dim3(KNB, nv), dim3(KB), 0, s, Vb, n, x, n, part);
-    hipLaunchKernelGGL(k_gm_sum, dim3(nv), dim3(KB), 0, s, part, hd);
+  const volatile GmScalars* hs = ws.host;
+  // the sums V_i^H w, i < nv (the last: w itself), what the step kernel makes of
+  // them, and the scalars' event
+  auto dots = [&](int nv, const T* w, bool second) {
+    hipLaunchKernelGGL(k_gm_dots<T>, dim3(GM_BLOCKS, (nv + 3) / 4), dim3(KB), 0, s, (const T*)V, n, nv, w, n, ws.part,
+                       (const GmScalars*)ws.dev, second);
+    hipLaunchKernelGGL(k_gm_step, dim3(1), dim3(1024), 0, s, ws.part, nv, o.cancel, ws.dev, ws.dhost, second);
+  };
+  // ev marks the scalars of the launches so far
+  auto mark = [&]() -> Status {
     GMCHK(hipGetLastError());
-    GMCHK(hipMemcpyAsync(hv.data(), hd, nv * sizeof(double2), hipMemcpyDeviceToHost, s));
-    GMCHK(hipStreamSynchronize(s));
+    GMCHK(hipEventRecord(ws.ev, s));
     return Status();
   };
-  // x += sgn sum_i c[i] V_i
-  auto axpys = [&](auto x, const T* Vb, const std::vector<cd>& c, int nv, double sgn) -> Status {
-    typedef std::remove_pointer_t<decltype(x)> TX;
-    GMCHK(hipMemcpyAsync(hd, c.data(), nv * sizeof(double2), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL((k_gm_axpys<TX, T>), dim3(g1), dim3(KB), 0, s, x, Vb, n, (const double2*)hd, nv, n, sgn);
-    GMCHK(hipGetLastError());
-    GMCHK(hipStreamSynchronize(s));  // c may change before the next call
+  auto wait = [&]() -> Status {
+    GMCHK(hipEventSynchronize(ws.ev));
     return Status();
   };
-  auto norm = [&](auto x, double& out) -> Status {
-    Status st = dots(x, 1, x);
-    out = std::sqrt(std::max(hv[0].real(), 0.0));
-    return st;
+  // r64 = b - ax, its norm, and v_0 = r64 / ||r64|| issued behind it
+  auto residual = [&](const double2* ax, double& beta) -> Status {
+    Status st;
+    hipLaunchKernelGGL(k_gm_resid, dim3(GM_BLOCKS), dim3(KB), 0, s, B, ax, r64, n, ws.part);
+    hipLaunchKernelGGL(k_gm_step, dim3(1), dim3(1024), 0, s, ws.part, 1, 0.0, ws.dev, ws.dhost, false);
+    if (!(st = mark()).ok()) return st;
+    hipLaunchKernelGGL(k_gm_scale<T>, dim3(g1), dim3(KB), 0, s, (const double2*)r64, (const GmScalars*)ws.dev, V, n);
+    if (!(st = wait()).ok()) return st;
+    beta = std::sqrt(std::max((double)hs->w2, 0.0));
+    if (!std::isfinite((double)hs->w2)) beta = hs->w2;
+    return Status();
   };
   Status st;
   double bnorm = 0.0;
-  if (!(st = norm(B, bnorm)).ok()) return st;
+  if (!(st = residual(nullptr, bnorm)).ok()) return st;
   if (!std::isfinite(bnorm)) return bad(PSFD_ERR_NONFINITE, "right-hand side is not finite");
   if (bnorm == 0.0) {
     GMCHK(hipMemsetAsync(X, 0, n * sizeof(double2), s));
@@ -164,8 +261,7 @@ Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, cons
   if (o.warm) {
     // r = b - A x0
     if (!(st = A(X, w64, PSFD_C128, s)).ok()) return st;
-    hipLaunchKernelGGL(k_gm_comb, dim3(g1), dim3(KB), 0, s, B, w64, -1.0, r64, n);
-    if (!(st = norm((const double2*)r64, beta)).ok()) return st;
+    if (!(st = residual(w64, beta)).ok()) return st;
     rel = beta / bnorm;
     if (!std::isfinite(rel)) return bad(PSFD_ERR_NONFINITE, "non-finite residual");
     inf.rel_residual = rel;
@@ -174,12 +270,10 @@ Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, cons
       GMCHK(hipStreamSynchronize(s));
       return Status();
     }
-    hipLaunchKernelGGL((k_gm_scale<double2, T>), dim3(g1), dim3(KB), 0, s, r64, 1.0 / beta, V, n);
   } else {
     GMCHK(hipMemsetAsync(X, 0, n * sizeof(double2), s));
-    hipLaunchKernelGGL((k_gm_scale<double2, T>), dim3(g1), dim3(KB), 0, s, B, 1.0 / beta, V, n);
   }
-  std::vector<cd> H((size_t)(m + 1) * m), g(m + 1), sn(m), h1(m + 1), y(m);
+  std::vector<cd> H((size_t)(m + 1) * m), g(m + 1), sn(m), y(m);
   std::vector<double> cs(m);
   auto Hij = [&](int i, int j) -> cd& { return H[(size_t)i * m + j]; };
   while (inf.iters < o.max_iters) {
@@ -189,25 +283,25 @@ Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, cons
     g[0] = beta;
     const double stop = std::max(o.rtol * bnorm, f32 ? ETA_MIXED * beta : 0.0);
     int k = 0;
+    bool ahead = false;  // A v_j has been issued
     for (int j = 0; j < m && inf.iters < o.max_iters; ++j) {
       // w = A v_j straight into slot j + 1; one launch gives V_{0..j}^H w and
       // ||w||^2; the norm after the update follows from Pythagoras, and a
-      // cancellation (norm ratio below cancel) takes a second pass with a
-      // computed norm
+      // cancellation (norm ratio below cancel) takes a second pass
       T* wj = V + (j + 1) * n;
-      if (!(st = A(V + j * n, wj, dt, s)).ok()) return st;
-      if (!(st = dots((const T*)V, j + 2, (const T*)wj)).ok()) return st;
-      const double w2 = hv[j + 1].real();
-      double p2 = 0.0;
-      for (int i = 0; i <= j; ++i) { h1[i] = hv[i]; Hij(i, j) = hv[i]; p2 += std::norm(hv[i]); }
-      if (!(st = axpys(wj, V, h1, j + 1, -1.0)).ok()) return st;
-      double hn = std::sqrt(std::max(w2 - p2, 0.0));
-      if (!(hn >= o.cancel * std::sqrt(std::max(w2, 0.0)))) {
-        if (!(st = dots((const T*)V, j + 1, (const T*)wj)).ok()) return st;
-        for (int i = 0; i <= j; ++i) { h1[i] = hv[i]; Hij(i, j) += hv[i]; }
-        if (!(st = axpys(wj, V, h1, j + 1, -1.0)).ok()) return st;
-        if (!(st = norm((const T*)wj, hn)).ok()) return st;
-      }
+      if (!ahead && !(st = A(V + j * n, wj, dt, s)).ok()) return st;
+      dots(j + 2, wj, false);
+      hipLaunchKernelGGL((k_gm_update<T, false>), dim3(g1), dim3(KB), 0, s, wj, (const T*)V, n,
+                         (const GmScalars*)ws.dev, j + 1, n);
+      dots(j + 2, wj, true);
+      if (!(st = mark()).ok()) return st;
+      hipLaunchKernelGGL((k_gm_update<T, true>), dim3(g1), dim3(KB), 0, s, wj, (const T*)V, n,
+                         (const GmScalars*)ws.dev, j + 1, n);
+      ahead = j + 1 < m && inf.iters + 1 < o.max_iters;
+      if (ahead && !(st = A(wj, wj + n, dt, s)).ok()) return st;
+      if (!(st = wait()).ok()) return st;
+      const double w2 = hs->w2, hn = hs->hn;
+      for (int i = 0; i <= j; ++i) Hij(i, j) = cd(hs->h[i].x, hs->h[i].y);
       if (!std::isfinite(hn) || !std::isfinite(w2)) return bad(PSFD_ERR_NONFINITE, "non-finite Krylov vector");
       Hij(j + 1, j) = hn;
       ++inf.iters;
@@ -226,7 +320,6 @@ Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, cons
       Hij(j + 1, j) = 0.0;
       g[j + 1] = -std::conj(sn[j]) * g[j];
       g[j] = cs[j] * g[j];
-      if (hn > 0.0) hipLaunchKernelGGL((k_gm_scale<T, T>), dim3(g1), dim3(KB), 0, s, wj, 1.0 / hn, wj, n);
       if (std::abs(g[j + 1]) <= stop || hn == 0.0) break;
     }
     for (int i = k - 1; i >= 0; --i) {  // back substitution
@@ -234,16 +327,15 @@ Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, cons
       for (int l = i + 1; l < k; ++l) acc -= Hij(i, l) * y[l];
       y[i] = acc / Hij(i, i);
     }
-    std::vector<cd> yk(y.begin(), y.begin() + k);
-    if (!(st = axpys(X, V, yk, k, 1.0)).ok()) return st;
+    GmCoefs yk;
+    for (int i = 0; i < k; ++i) yk.c[i] = make_double2(y[i].real(), y[i].imag());
+    hipLaunchKernelGGL(k_gm_axpys<T>, dim3(g1), dim3(KB), 0, s, X, (const T*)V, n, yk, k, n);
     // FP64 residual r = b - A x
     if (!(st = A(X, w64, PSFD_C128, s)).ok()) return st;
-    hipLaunchKernelGGL(k_gm_comb, dim3(g1), dim3(KB), 0, s, B, w64, -1.0, r64, n);
-    if (!(st = norm((const double2*)r64, beta)).ok()) return st;
+    if (!(st = residual(w64, beta)).ok()) return st;
     rel = beta / bnorm;
     if (!std::isfinite(rel)) return bad(PSFD_ERR_NONFINITE, "non-finite residual");
     if (rel <= o.rtol) { inf.status = PSFD_OK; break; }
-    hipLaunchKernelGGL((k_gm_scale<double2, T>), dim3(g1), dim3(KB), 0, s, r64, 1.0 / beta, V, n);
   }
   inf.rel_residual = rel;
   inf.mono_residual = rel;
@@ -254,14 +346,35 @@ Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, cons
 
 }  // namespace
 
+GmresWs::~GmresWs() {
+  if (part) (void)hipFree(part);
+  if (dev) (void)hipFree(dev);
+  if (host) (void)hipHostFree(host);
+  if (ev) (void)hipEventDestroy(ev);
+}
+
+static Status ws_ready(GmresWs& w) {
+  if (!w.part) GMCHK(hipMalloc((void**)&w.part, sizeof(double2) * GM_BLOCKS * (GM_MAX + 2)));
+  if (!w.dev) GMCHK(hipMalloc((void**)&w.dev, sizeof(GmScalars)));
+  if (!w.host) {
+    GMCHK(hipHostMalloc((void**)&w.host, sizeof(GmScalars), hipHostMallocCoherent | hipHostMallocMapped));
+    GMCHK(hipHostGetDevicePointer((void**)&w.dhost, w.host, 0));
+  }
+  if (!w.ev) GMCHK(hipEventCreateWithFlags(&w.ev, hipEventDisableTiming));
+  return Status();
+}
+
 Status gmres_host(long long n, const ApplyFn& A, const double2* b, double2* x, const HostGmres& o, psfd_info& info,
-                  hipStream_t s) {
-  if (!(o.rtol > 0.0) || o.m < 1 || o.m > 64 || o.max_iters < 1)
+                  GmresWs& ws, hipStream_t s) {
+  if (!(o.rtol > 0.0) || o.m < 1 || o.m > GM_MAX || o.max_iters < 1)
     return bad(PSFD_ERR_INVALID_ARG, "need rtol > 0, 1 <= restart <= 64, max_iters >= 1");
   if (o.precision != PSFD_FP64 && o.precision != PSFD_MIXED)
     return bad(PSFD_ERR_INVALID_ARG, "precision must be PSFD_FP64 or PSFD_MIXED");
   info.status = PSFD_NOT_CONVERGED;
-  return o.precision == PSFD_MIXED ? gmres_t<float2>(n, A, b, x, o, info, s) : gmres_t<double2>(n, A, b, x, o, info, s);
+  Status st = ws_ready(ws);
+  if (!st.ok()) return st;
+  return o.precision == PSFD_MIXED ? gmres_t<float2>(n, A, b, x, o, info, ws, s)
+                                   : gmres_t<double2>(n, A, b, x, o, info, ws, s);
 }
 
 }  // namespace psfd

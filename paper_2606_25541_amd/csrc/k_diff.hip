@@ -33,6 +33,7 @@ struct psfd_diff_plan {
   double* zt = nullptr;      // [kappa_d (nz_ext)][kappa (nz_ext)][inv_s (2 nz_ext)]
   void* ws32 = nullptr;      // apply workspaces (3 N_ext values)
   void* ws64 = nullptr;
+  psfd::GmresWs gm;          // small buffers of its solves
   void* plane = nullptr;     // 3 planes of the readout, complex128
   std::vector<void*> owned;
   ~psfd_diff_plan() {
@@ -576,7 +577,7 @@ Status diff_solve(psfd_diff_plan* P, const void* deps_v, void* e_v, void* orders
       if (!st.ok()) return st;
     }
     psfd_info li{};
-    st = gmres_host(se.n3, A, b, E, go, li, s);
+    st = gmres_host(se.n3, A, b, E, go, li, P->gm, s);
     if (!st.ok()) return st;
     inf.iters += li.iters;
     inf.cycles += li.cycles;

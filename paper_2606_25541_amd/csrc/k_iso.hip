@@ -686,6 +686,7 @@ struct psfd_iso_plan {
   int nxp = 0;               // row length of the octant tables
   double2* tw64 = nullptr;   // tw[m + i] = exp(-2 pi i i / m), m = 2 .. ISO_TW_MAX
   float2* tw32 = nullptr;
+  psfd::GmresWs gm;        // small buffers of its solves
   void* work[2] = {nullptr, nullptr};  // W [3][nz][2ny][2nx] per dtype (C64, C128)
   ~psfd_iso_plan() {
     for (void* q : {(void*)tab64, (void*)ptab64, (void*)ptab32, (void*)tw64, (void*)tw32, work[0], work[1]})
@@ -1096,7 +1097,7 @@ Status iso_solve(psfd_iso_plan* p, const void* deps, const void* b, void* u, dou
   if (const char* e = std::getenv("PSFD_ISO_CANCEL")) o.cancel = std::atof(e);
   psfd_info inf{};
   inf.outer_iters = 1;
-  Status st = gmres_host(3 * N, A, (const double2*)b, (double2*)u, o, inf, s);
+  Status st = gmres_host(3 * N, A, (const double2*)b, (double2*)u, o, inf, p->gm, s);
   if (info) *info = inf;
   return st;
 }
