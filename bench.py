@@ -50,10 +50,10 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 SECTIONS = ("solve", "fp64", "apply", "isolated", "batched", "serving", "adjoint", "precond", "layers", "cpu")
 # sources that decide the code of the measured kernels (hashed into the counter summary)
-KERNEL_SOURCES = ("common.hpp", "layout.hpp", "kernels.hpp", "fft_lds.hpp", "k_apply.hip", "krylov.hpp",
-                  "givens.hpp", "k_krylov.hip")
+KERNEL_SOURCES = ("common.hpp", "layout.hpp", "kernels.hpp", "fft_lds.hpp", "regfft.hpp", "qplane.hpp",
+                  "k_qplane32.hip", "k_qplane_gs.hip", "k_apply.hip", "krylov.hpp", "givens.hpp", "k_krylov.hip")
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "apply_G3_fp32_hbm_traffic.md")
-ISO_SOURCES = ("common.hpp", "fft_lds.hpp", "k_iso.hip")
+ISO_SOURCES = ("common.hpp", "fft_lds.hpp", "regfft.hpp", "k_iso.hip")
 ISO_TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "isolated_apply_G3_hbm_traffic.md")
 
 
@@ -226,15 +226,6 @@ def sec_apply(ctx, args, out):
         res[name] = {"applies_per_s": 1.0 / t_apply, "us_per_apply": 1e6 * t_apply, "apply_bytes": b_apply,
                      "apply_gbs": b_apply / t_apply / 1e9, "apply_frac_hbm": b_apply / t_apply / 1e9 / HBM_PEAK_GBS,
                      "stages": stages}
-        if name == "fp32" and prob.nx == prob.ny == 128:
-            # the operator apply runs the quarter-plane kernels (four blocks per 128 x 128 plane, the
-            # pencil on the quarter layout); the Arnoldi steps of a solve run the one-block-per-plane
-            # kernels with their fused Gram-Schmidt work, whose plain forms are timed here
-            os.environ["PSFD_QUARTER_PLANES"] = "0"
-            try:
-                res[name]["stages_full_planes"] = time_stages()
-            finally:
-                os.environ.pop("PSFD_QUARTER_PLANES", None)
     out["apply"] = res
     # kernels of the Arnoldi steps of one restart cycle (columns j = 0 .. m-1) on FP32 basis vectors,
     # through psfd_bench_gram_schmidt: the projections read v_0..v_j and w, (j + 2) 3N complex64; the
@@ -269,7 +260,7 @@ def sec_apply(ctx, args, out):
     # the dominant kernel of an Arnoldi step (largest mean time per step over a cycle): the forward
     # stage (plain at step 0; with the previous column's update at steps 1..m-1 where fused), the
     # pencil, the inverse stage (with the projections where fused) and the separate passes
-    st32 = res["fp32"].get("stages_full_planes", res["fp32"]["stages"])
+    st32 = res["fp32"]["stages"]
     cand = {"stage 1": ("k_pencil<float2,7,16> (z FFT, dyadic kernel, stack response)", st32[1]["us"],
                         st32[1]["bytes"])}
     if fused_upd:
@@ -277,20 +268,20 @@ def sec_apply(ctx, args, out):
         us0 = [st32[0]["us"]] + g0["us_per_column"][:m - 1]
         by0 = [st32[0]["bytes"]] + [(j + 3) * 3 * N * 8 + 7 * N * 8 for j in range(m - 1)]
         cand["stage 0 + update"] = (
-            "k_plane<float2,fwd,update+V*x> (Gram-Schmidt update of the previous column + transverse FFT "
+            "k_qplane<float2,fwd,update+V*x> (Gram-Schmidt update of the previous column + transverse FFT "
             "forward; plain at step 0; mean over the steps of a cycle)", sum(us0) / m, sum(by0) / m)
         # the last column takes no update pass: its Givens step works from the projections
     else:
-        cand["stage 0"] = ("k_plane<float2,fwd,V*x> (transverse FFT forward, 128x128 planes)", st32[0]["us"],
+        cand["stage 0"] = ("k_qplane<float2,fwd,V*x> (transverse FFT forward, 128x128 planes)", st32[0]["us"],
                            st32[0]["bytes"])
         cand["update"] = ("k_update<float2> (Gram-Schmidt update, mean over j = 0..m-1)", gs["update"]["us_mean"],
                           gs["update"]["bytes_mean"])
     if fused:
         cand["stage 2 + projections"] = (
-            "k_plane<float2,inv,dots> (transverse FFT inverse + Gram-Schmidt projections, mean over j = 0..m-1)",
+            "k_qplane<float2,inv,dots> (transverse FFT inverse + Gram-Schmidt projections, mean over j = 0..m-1)",
             gs["stage 2 step"]["us_mean"], gs["stage 2 step"]["bytes_mean"])
     else:
-        cand["stage 2"] = ("k_plane<float2,inv> (transverse FFT inverse)", gs["stage 2 step"]["us_mean"],
+        cand["stage 2"] = ("k_qplane<float2,inv> (transverse FFT inverse)", gs["stage 2 step"]["us_mean"],
                            gs["stage 2 step"]["bytes_mean"])
         cand["projections"] = ("k_dots<float2> (Gram-Schmidt projections, mean over j = 0..m-1)",
                                gs["projections"]["us_mean"], gs["projections"]["bytes_mean"])

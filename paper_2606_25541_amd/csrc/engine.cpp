@@ -689,28 +689,38 @@ template <class T> static T* deps_of_mut(Group& g);
 template <> float2* deps_of_mut<float2>(Group& g) { return g.deps32; }
 template <> double2* deps_of_mut<double2>(Group& g) { return g.deps64; }
 
+// Whether the forward transverse kernel of an Arnoldi step also does the
+// Gram-Schmidt update of the previous column: the quarter-plane kernels that
+// carry it (qplane_gs), with the projections in the inverse kernel, which also
+// marks the update pending, and pencil blocks large enough to run the Givens
+// task (at least GIVENS_THREADS threads, i.e. padded z lengths of 64 and more).
+// PSFD_FUSE_UPDATE=0 keeps the separate update pass; so does PSFD_FUSE_DOTS=0
+// (read per call).
+static bool fuse_update(const Group& g, size_t esz) {
+  const Shape& sh = g.sh;
+  if (env_int("PSFD_FUSE_DOTS", 1) == 0 || env_int("PSFD_FUSE_UPDATE", 1) == 0) return false;
+  return quarter_planes(g, esz) && qplane_gs(sh.nx, sh.ny, sh.nz, esz) && zq_config(sh, esz).nthr >= GIVENS_THREADS;
+}
+
 // Whether the inverse transverse kernel of an Arnoldi step also forms the
-// Gram-Schmidt projections of the vector it writes (FP32 64 x 64 and 128 x 128 square planes;
-// PSFD_FUSE_DOTS=0 keeps the separate projection pass, read per call).
+// Gram-Schmidt projections of the vector it writes: the quarter-plane kernels of
+// qplane_gs where their partials (one per block) go to the fused update or fit
+// the separate update pass, and without quarter planes (fewer than 8 z planes)
+// the FP32 64 x 64 and 128 x 128 square planes. PSFD_FUSE_DOTS=0 keeps the
+// separate projection pass (read per call).
 static bool fuse_dots(const Group& g, size_t esz) {
-  const char* e = std::getenv("PSFD_FUSE_DOTS");
-  if (e && std::atoi(e) == 0) return false;
-  const XYCfg c = xy_config(g.sh, esz);
+  const Shape& sh = g.sh;
+  if (env_int("PSFD_FUSE_DOTS", 1) == 0) return false;
+  if (quarter_planes(g, esz))
+    return qplane_gs(sh.nx, sh.ny, sh.nz, esz) && (12 * sh.nz <= DotBlocks<float2>::value || fuse_update(g, esz));
+  const XYCfg c = xy_config(sh, esz);
   return c.fused && tile_takes_dots(tile_base(g, nullptr, c.full), esz);
 }
 
-// Whether the forward transverse kernel of an Arnoldi step also does the
-// Gram-Schmidt update of the previous column (FP32 64 x 64 and 128 x 128 square planes, and
-// pencil blocks large enough to run the Givens task: at least GIVENS_THREADS
-// threads, i.e. padded z lengths of 64 and more; with the projections in the
-// inverse kernel, which also marks the update pending; PSFD_FUSE_UPDATE=0 keeps
-// the separate update pass, read per call).
-static bool fuse_update(const Group& g, size_t esz) {
-  const char* e = std::getenv("PSFD_FUSE_UPDATE");
-  if (e && std::atoi(e) == 0) return false;
-  const XYCfg c = xy_config(g.sh, esz);
-  return c.fused && tile_takes_update(tile_base(g, nullptr, c.full), esz) &&
-         z_config(g.sh, esz).nthr >= GIVENS_THREADS && fuse_dots(g, esz);
+// projection partials per value of an Arnoldi step: one per quarter-plane block
+// where the fused update sums them, else those of the projection pass
+static int dot_partials(const Group& g, size_t esz) {
+  return fuse_update(g, esz) ? 12 * g.sh.nz : esz == 8 ? DotBlocks<float2>::value : DotBlocks<double2>::value;
 }
 
 // The inverse transverse stage of an Arnoldi step: the slot vout (j + 1) =
@@ -718,7 +728,7 @@ static bool fuse_update(const Group& g, size_t esz) {
 // projection partials of the new vector (fuse_dots), false when the separate
 // projection pass must follow.
 template <class T>
-static bool arnoldi_inverse(Group& g, VecRef vout, int jh, hipStream_t s, bool qp = false) {
+static bool arnoldi_inverse(Group& g, VecRef vout, int jh, hipStream_t s, bool qp) {
   T* ws = (T*)g.wsP;
   if constexpr (std::is_same<T, float2>::value) {
     if (fuse_dots(g, sizeof(T))) {
@@ -726,8 +736,9 @@ static bool arnoldi_inverse(Group& g, VecRef vout, int jh, hipStream_t s, bool q
       const XYCfg c = xy_config(g.sh, sizeof(T));
       TileArgs a = tile_base(g, twiddles<T>(g), c.full);
       a.in = vr(ws, n3); a.out = vout; a.active = g.run;
-      a.dt = DotTask{g.basis, n3, bsv, g.st, g.dpart2, jh};
-      launch_tile<T, true, LD_PLAIN, ST_DOTS>(a, 3 * g.sh.nz, g.B, c.full.nthr, c.full.lds, s);
+      a.dt = DotTask{g.basis, n3, bsv, g.st, g.dpart2, jh, dot_partials(g, sizeof(T))};
+      if (qp) launch_qplane<T, true, LD_PLAIN, ST_DOTS>(a, 3 * g.sh.nz, g.B, s);
+      else launch_tile<T, true, LD_PLAIN, ST_DOTS>(a, 3 * g.sh.nz, g.B, c.full.nthr, c.full.lds, s);
       return true;
     }
   }
@@ -759,6 +770,7 @@ static Status bench_gs_t(Group& g, int pass, int j, const T* x, int reps, float*
   // pass 3: the forward transverse stage of step j + 1 carrying the update of
   // column j where the shape allows it (else the plain forward stage); the
   // contrast is the first N values of x
+  const bool qp = quarter_planes(g, sizeof(T));
   bool fwd_upd = false;
   TileArgs fa;
   std::memset(&fa, 0, sizeof(fa));
@@ -769,20 +781,17 @@ static Status bench_gs_t(Group& g, int pass, int j, const T* x, int reps, float*
       const XYCfg c = xy_config(g.sh, sizeof(T));
       fa = tile_base(g, twiddles<T>(g), c.full);
       fa.in = vout; fa.vol = vr(deps_of_mut<T>(g), g.sh.N); fa.out = vr(g.wsP, n3); fa.active = g.run;
-      fa.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, j + 1};
+      fa.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, j + 1, DotBlocks<T>::value};
     }
   }
   auto run_pass = [&]() {
     if (pass == 0) krylov_dots<T>(V, n3, bsv, n3, g.st, g.run, g.dpart2, 1, s, j);
     else if (pass == 1) krylov_update<T>(V, n3, bsv, n3, g.st, g.run, g.dpart2, g.part, 1, s, j, false);
-    else if (pass == 2) arnoldi_inverse<T>(g, vout, j, s);
+    else if (pass == 2) arnoldi_inverse<T>(g, vout, j, s, qp);
     else if (fwd_upd) {
-      if constexpr (std::is_same<T, float2>::value) {
-        const XYCfg c = xy_config(g.sh, sizeof(T));
-        launch_tile<T, false, LD_UPD_VX, ST_PLAIN>(fa, 3 * g.sh.nz, 1, c.full.nthr, c.full.lds, s);
-      }
+      if constexpr (std::is_same<T, float2>::value) launch_qplane<T, false, LD_UPD_VX, ST_PLAIN>(fa, 3 * g.sh.nz, 1, s);
     } else {
-      apply_stage<T>(g, 0, deps_of_mut<T>(g), vout, vout, (T*)g.wsP, 1, 0, 0, g.run, s);
+      apply_stage<T>(g, 0, deps_of_mut<T>(g), vout, vout, (T*)g.wsP, 1, 0, 0, g.run, s, nullptr, 0, nullptr, qp);
     }
   };
   run_pass();  // untimed: a kernel's first launch in the process carries set-up costs
@@ -837,6 +846,9 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
   const GivensTask gt{g.st, g.run, g.part, RED_BLOCKS, 0};
   const double* isc = &g.st[0].inv_norm;
   const long long iss = (long long)(sizeof(GState) / sizeof(double));
+  // the quarter-plane kernels and layout where the shape takes them
+  const bool qp = quarter_planes(g, sizeof(T));
+  const int nblk = dot_partials(g, sizeof(T)), nq = 12 * g.sh.nz;
   bool upd = false, upd_slots = false;
   if constexpr (std::is_same<T, float2>::value) {
     upd = lock && fuse_update(g, sizeof(T));
@@ -847,44 +859,33 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
     // instance taking the update, the scale and the Givens step only while an
     // update is pending (GState::pend), and the last column's Givens step from
     // the projections, so that a slot computes exactly what a lone solve does
-    const int np = 3 * g.sh.nz;
-    const XYCfg c = xy_config(g.sh, sizeof(T));
-    TileArgs a = tile_base(g, twiddles<T>(g), c.full);
+    TileArgs a = tile_base(g, twiddles<T>(g), xy_config(g.sh, sizeof(T)).full);
     a.in = vin; a.vol = vr(deps_of<T>(g), g.sh.N); a.out = vr((T*)g.wsP, n3); a.active = g.run;
-    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, -1};
-    if constexpr (std::is_same<T, float2>::value)
-      launch_tile<T, false, LD_UPD_SLOT, ST_PLAIN>(a, np, g.B, c.full.nthr, c.full.lds, s);
-    const GivensTask gp{g.st, g.run, g.part, np, 1};
-    apply_stage<T>(g, 1, deps_of<T>(g), vin, vout, (T*)g.wsP, 1, transpose, refl, g.run, s, nullptr, 0, &gp);
-    if (!arnoldi_inverse<T>(g, vout, jh, s)) krylov_dots<T>(V, n3, bsv, n3, g.st, g.run, g.dpart2, g.B, s, jh);
-    krylov_givens_proj(g.st, g.run, g.dpart2, g.B, s, -1);
+    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, -1, nblk};
+    if constexpr (std::is_same<T, float2>::value) launch_qplane<T, false, LD_UPD_SLOT, ST_PLAIN>(a, 3 * g.sh.nz, g.B, s);
+    const GivensTask gp{g.st, g.run, g.part, nq, 1};
+    apply_stage<T>(g, 1, deps_of<T>(g), vin, vout, (T*)g.wsP, 1, transpose, refl, g.run, s, nullptr, 0, &gp, qp);
+    arnoldi_inverse<T>(g, vout, jh, s, qp);  // with the projections (fuse_update implies fuse_dots)
+    krylov_givens_proj(g.st, g.run, g.dpart2, nblk, g.B, s, -1);
     return false;
   }
   if (upd) {
-    // the update of column jh - 1 in the forward plane kernel, which transforms
-    // slot jh unscaled; the pencil kernel scales it from the plane norm
-    // partials and runs the Givens step of column jh - 1 in one extra block
-    const int np = 3 * g.sh.nz;
-    const XYCfg c = xy_config(g.sh, sizeof(T));
-    TileArgs a = tile_base(g, twiddles<T>(g), c.full);
+    // the update of column jh - 1 in the forward transverse kernel, which transforms
+    // slot jh unscaled; the pencil kernel scales it from the norm partials of its
+    // blocks and runs the Givens step of column jh - 1 in one extra block
+    TileArgs a = tile_base(g, twiddles<T>(g), xy_config(g.sh, sizeof(T)).full);
     a.in = vin; a.vol = vr(deps_of<T>(g), g.sh.N); a.out = vr((T*)g.wsP, n3); a.active = g.run;
-    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, jh};
+    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, jh, nblk};
     // at step 0 the per-slot kernel loads slot 0 scaled (no update, as the
     // server's first step does), and no Givens step is pending
     if constexpr (std::is_same<T, float2>::value) {
-      if (jh > 0) launch_tile<T, false, LD_UPD_VX, ST_PLAIN>(a, np, g.B, c.full.nthr, c.full.lds, s);
-      else launch_tile<T, false, LD_UPD_SLOT, ST_PLAIN>(a, np, g.B, c.full.nthr, c.full.lds, s);
+      if (jh > 0) launch_qplane<T, false, LD_UPD_VX, ST_PLAIN>(a, 3 * g.sh.nz, g.B, s);
+      else launch_qplane<T, false, LD_UPD_SLOT, ST_PLAIN>(a, 3 * g.sh.nz, g.B, s);
     }
-    const GivensTask gp{g.st, g.run, g.part, np, 0};
+    const GivensTask gp{g.st, g.run, g.part, nq, 0};
     apply_stage<T>(g, 1, deps_of<T>(g), vin, vout, (T*)g.wsP, 1, transpose, refl, g.run, s, nullptr, 0,
-                   jh > 0 ? &gp : nullptr);
+                   jh > 0 ? &gp : nullptr, qp);
   }
-  // steps on planes the quarter split takes run the quarter-plane kernels,
-  // except where the one-block-per-plane kernels carry the Gram-Schmidt work
-  // (FP32 128 x 128: the update in the forward kernel, the projections in the
-  // inverse one)
-  const bool qp = !upd && quarter_planes(g, sizeof(T)) &&
-                  (std::is_same<T, double2>::value || !fuse_dots(g, sizeof(T)));
   if (!upd) {
     apply_stage<T>(g, 0, deps_of<T>(g), vin, vout, (T*)g.wsP, 1, transpose, refl, g.run, s, isc, iss,
                    lock && jh > 0 ? &gt : nullptr, qp);
@@ -897,10 +898,10 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
   // (with solve_mask the back substitution of the cycle follows in the same launch)
   if (upd && jh == g.m - 1) {
     if (solve_mask) {
-      krylov_givens_proj_solve(g.st, g.run, g.dpart2, solve_mask, g.B, s, jh);
+      krylov_givens_proj_solve(g.st, g.run, g.dpart2, nblk, solve_mask, g.B, s, jh);
       return true;
     }
-    krylov_givens_proj(g.st, g.run, g.dpart2, g.B, s, jh);
+    krylov_givens_proj(g.st, g.run, g.dpart2, nblk, g.B, s, jh);
   } else if (!upd) {
     krylov_update<T>(V, n3, bsv, n3, g.st, g.run, g.dpart2, g.part, g.B, s, jh, !lock || jh == g.m - 1);
   }

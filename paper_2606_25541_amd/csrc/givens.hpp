@@ -8,13 +8,6 @@
 
 namespace psfd {
 
-
-PSFD_D double gv_wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // ||w||^2 from the nblk (<= RED_BLOCKS) norm partials of one instance, in two
 // halves for callers with barriers of their own between them. norm_wave_sums:
 // the first GIVENS_THREADS threads take partials tid, tid + 256, ... in order
@@ -31,7 +24,7 @@ PSFD_D void norm_wave_sums(const double2* pb, int nblk, double2* gs) {
 #pragma unroll
     for (int k = 0; k < PK; ++k)
       if (tid + k * GIVENS_THREADS < nblk) acc = cadd(acc, pv[k]);
-    const double re = gv_wave_sum(acc.x), im = gv_wave_sum(acc.y);
+    const double re = lane_sum(acc.x), im = lane_sum(acc.y);
     if ((tid & 63) == 0) gs[tid >> 6] = make_double2(re, im);
   }
 }

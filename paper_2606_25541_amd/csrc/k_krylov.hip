@@ -265,9 +265,9 @@ void krylov_givens(GState* st, int* run, const double2* part, int nbatch, hipStr
 // the Givens step of the last column from its projections alone (see
 // krylov_givens_proj); the partials are summed as k_update sums them. Every
 // thread of the block calls it (the condition is uniform over the block).
-PSFD_D void givens_proj_block(GState* st, int* run, const double2* dpart, int jh) {
+PSFD_D void givens_proj_block(GState* st, int* run, const double2* dpart, int nblk, int jh) {
   __shared__ double2 hsum[MAXM + 2];
-  __shared__ double wn2s;
+  __shared__ double wn2s, h2[MAXM];
   const int b = blockIdx.x;
   const int rb = run[b], jd = jh >= 0 ? jh : st[b].j, mb = st[b].m;
   asm volatile("" ::"s"(rb), "s"(jd), "s"(mb));
@@ -277,17 +277,9 @@ PSFD_D void givens_proj_block(GState* st, int* run, const double2* dpart, int jh
   const double scv = st[b].sc[min((int)threadIdx.x, MAXM)];
   {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    constexpr int NBD = DotBlocks<float2>::value, PL = NBD / 64, NW = KB / 64;
-    const double2* pb = dpart + (long long)b * PSTR * NBD;
-    for (int i = wave; i <= cnt; i += NW) {
-      double2 pv[PL];
-#pragma unroll
-      for (int k = 0; k < PL; ++k) pv[k] = pb[(long long)i * NBD + lane + 64 * k];
-      double2 t = make_double2(0, 0);
-#pragma unroll
-      for (int k = 0; k < PL; ++k) t = cadd(t, pv[k]);
-      t.x = wave_sum(t.x);
-      t.y = wave_sum(t.y);
+    const double2* pb = dpart + (long long)b * PSTR * nblk;
+    for (int i = wave; i <= cnt; i += KB / 64) {
+      const double2 t = dots_total(pb + (long long)i * nblk, nblk);
       if (lane == 0) hsum[i] = t;
     }
   }
@@ -295,13 +287,14 @@ PSFD_D void givens_proj_block(GState* st, int* run, const double2* dpart, int jh
   // h_i = sc_i <slot_i, w>; ||w - V h||^2 = ||w||^2 - sum |h_i|^2 in a fixed order
   const double2 hv = (int)threadIdx.x < cnt ? cscale(hsum[threadIdx.x], scv) : make_double2(0, 0);
   GState& S = st[b];
-  if ((int)threadIdx.x < cnt) S.h[threadIdx.x] = hv;
+  if ((int)threadIdx.x < cnt) {
+    S.h[threadIdx.x] = hv;
+    h2[threadIdx.x] = hv.x * hv.x + hv.y * hv.y;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
     double a = 0.0;
-    for (int i = 0; i < cnt; ++i) {
-      const double2 h = cscale(hsum[i], st[b].sc[i]);
-      a += h.x * h.x + h.y * h.y;
-    }
+    for (int i = 0; i < cnt; ++i) a += h2[i];
     const double w2 = hsum[cnt].x;
     S.wn2_in = w2;
     wn2s = w2 - a > 0.0 ? w2 - a : 0.0;
@@ -310,12 +303,13 @@ PSFD_D void givens_proj_block(GState* st, int* run, const double2* dpart, int jh
   givens_impl<true>(st, run, nullptr, 0, b, hv, hsum[cnt].x, wn2s);
 }
 
-__global__ void __launch_bounds__(KB) k_givens_proj(GState* st, int* run, const double2* dpart, int jh) {
-  givens_proj_block(st, run, dpart, jh);
+__global__ void __launch_bounds__(KB) k_givens_proj(GState* st, int* run, const double2* dpart, int nblk,
+                                                    int jh) {
+  givens_proj_block(st, run, dpart, nblk, jh);
 }
 
-void krylov_givens_proj(GState* st, int* run, const double2* dpart, int nbatch, hipStream_t s, int jh) {
-  hipLaunchKernelGGL(k_givens_proj, dim3(nbatch), dim3(KB), 0, s, st, run, dpart, jh);
+void krylov_givens_proj(GState* st, int* run, const double2* dpart, int nblk, int nbatch, hipStream_t s, int jh) {
+  hipLaunchKernelGGL(k_givens_proj, dim3(nbatch), dim3(KB), 0, s, st, run, dpart, nblk, jh);
 }
 
 template <class T>
@@ -352,7 +346,7 @@ PSFD_D void solve_small_block(GState* st, const int* mask) {
       yl[i] = cdiv(t, R[i][i]);
     }
   }
-  if (threadIdx.x == 1) {
+  if (threadIdx.x == 64) {  // another wavefront, so that the two recurrences run side by side
     // r = V_{k+1} (beta e_1 - Hbar y) = V_{k+1} Q^H (g_k e_k): undo the rotations
     // G_i = [[cs, sn], [-conj(sn), cs]], last first, on g_k e_k
     for (int i = 0; i < k; ++i) cl[i] = make_double2(0, 0);
@@ -387,16 +381,16 @@ void krylov_solve_small(GState* st, const int* mask, int nbatch, hipStream_t s) 
 // the last column's Givens step from its projections, then the back
 // substitution, in one launch (the block's barrier orders the state it writes
 // before the reads of the second part)
-__global__ void __launch_bounds__(KB) k_givens_proj_solve(GState* st, int* run, const double2* dpart, int jh,
-                                                          const int* mask) {
-  givens_proj_block(st, run, dpart, jh);
+__global__ void __launch_bounds__(KB) k_givens_proj_solve(GState* st, int* run, const double2* dpart, int nblk,
+                                                          int jh, const int* mask) {
+  givens_proj_block(st, run, dpart, nblk, jh);
   __syncthreads();
   solve_small_block(st, mask);
 }
 
-void krylov_givens_proj_solve(GState* st, int* run, const double2* dpart, const int* mask, int nbatch, hipStream_t s,
-                              int jh) {
-  hipLaunchKernelGGL(k_givens_proj_solve, dim3(nbatch), dim3(KB), 0, s, st, run, dpart, jh, mask);
+void krylov_givens_proj_solve(GState* st, int* run, const double2* dpart, int nblk, const int* mask, int nbatch,
+                              hipStream_t s, int jh) {
+  hipLaunchKernelGGL(k_givens_proj_solve, dim3(nbatch), dim3(KB), 0, s, st, run, dpart, nblk, jh, mask);
 }
 
 template <class T, class TX>

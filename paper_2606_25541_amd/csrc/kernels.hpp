@@ -20,12 +20,12 @@ struct GivensTask {
   int by_pend;  // 1: only the instances with a pending update (GState::pend) take the task
                 // and the scale; the others' input was scaled on load
 };
-// The Gram-Schmidt update of column j - 1, left to the forward square-plane
-// kernel of step j (LD_UPD_VX, lock-step solves): every plane block sums the
-// projection partials of the step before (dpart, DotBlocks<float2> per value,
-// PSTR values per instance), forms slot_j -= sum_{i<j} h_i s_i slot_i over its
-// plane, stores it, and leaves the plane's ||slot_j||^2 in part[b * planes + plane];
-// the block of plane 0 stores h and ||w||^2 before the update for the Givens step.
+// The Gram-Schmidt update of column j - 1, left to the forward quarter-plane
+// kernel of step j (LD_UPD_VX, lock-step solves): every block sums the projection
+// partials of the step before (dpart, nblk per value, PSTR values per instance),
+// forms slot_j -= sum_{i<j} h_i s_i slot_i over its quarter, stores it, and leaves
+// its ||slot_j||^2 in part[b * 12 nz + 4 plane + quarter]; block 0 stores h and
+// ||w||^2 before the update for the Givens step.
 // The vector enters the transform unscaled: the next kernel applies its scale.
 // LD_UPD_VX: j >= 1, every instance at step j. LD_UPD_SLOT: per instance, j = 0
 // (the first step of a cycle: no update, slot 0 scaled on load by S.inv_norm, as
@@ -39,12 +39,13 @@ struct UpdateTask {
   const double2* dpart;
   double2* part;
   int j;
+  int nblk;             // partials per value in dpart
 };
 // The Gram-Schmidt projections of the new Arnoldi vector, left to the kernel
-// that writes it (ST_DOTS, inverse square planes): each plane block also forms
-// the partial dot products <slot_i, w> (i = 0..j) and ||w||^2 over its plane
-// and stores them where the projection pass would (PSTR values per instance,
-// DotBlocks<float2> partials each: the plane's own, zeros in the others).
+// that writes it (ST_DOTS, inverse quarter planes or square planes): each block
+// also forms the partial dot products <slot_i, w> (i = 0..j) and ||w||^2 over its
+// values and stores them where the projection pass would (PSTR values per
+// instance, nblk partials each: the block's own, zeros where no block owns one).
 struct DotTask {
   const void* V;        // basis of instance 0; slot i of instance b at V + b bsv + i ldv
   long long ldv, bsv;
@@ -52,6 +53,7 @@ struct DotTask {
                         // column is pending)
   double2* part;
   int jh;               // >= 0: every running instance stands at step jh
+  int nblk;             // partials per value in part
 };
 enum StoreOp { ST_PLAIN = 0, ST_AXPBY = 1, ST_DOTS = 2 };
 
@@ -124,9 +126,6 @@ bool tile_is_plane(const TileArgs& a, size_t esz);
 // whether launch_tile can store with ST_DOTS for these arguments (FP32 64 x 64 and
 // 128 x 128 planes, at most DotBlocks<float2> planes per instance)
 bool tile_takes_dots(const TileArgs& a, size_t esz);
-// whether launch_tile can load with LD_UPD_VX / LD_UPD_SLOT for these arguments (FP32 64 x 64 and
-// 128 x 128 planes)
-bool tile_takes_update(const TileArgs& a, size_t esz);
 template <class T>
 void launch_pencil(const PencilArgs& a, int nbatch, int nthr, size_t lds, hipStream_t s);
 // Quarter-plane transverse kernels of the operator apply (planes of 16 .. 256 on
@@ -138,6 +137,9 @@ void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s);
 // Columns of the quarter-layout pencil blocks of a shape; 0: the shape takes
 // the natural layout (planes too small or beyond LDS, nz < 8).
 int qplane_bx(int nx, int ny, int nz, size_t esz);
+// whether launch_qplane takes LD_UPD_VX, LD_UPD_SLOT and ST_DOTS for this shape
+// (FP32, planes of 4096 and more values, 8 <= nz <= 64)
+bool qplane_gs(int nx, int ny, int nz, size_t esz);
 // Threads of a compile-time pencil block of bx columns (a multiple of its 3 bx
 // sequences) and padded length 2^lpz: 8 values per thread in the FFT passes,
 // at least four readout partial sums per sequence.

@@ -16,7 +16,9 @@ constexpr int LIN_BLOCKS = 2048;  // blocks per instance of the solution update 
 // blocks per instance of the projection pass: 256 of 1024 threads (FP32 vectors)
 // or 512 of 512 threads (FP64)
 template <class T> struct DotBlocks { static constexpr int value = sizeof(T) == 8 ? 256 : 512; };
-constexpr int DOT_BLOCKS_MAX = 512;
+// partials per value in memory: the projection pass's, or one per quarter-plane
+// block of an inverse transverse kernel (12 nz, nz <= 64)
+constexpr int DOT_BLOCKS_MAX = 768;
 constexpr int PSTR = MAXM + 2;    // partial stride: up to MAXM + 1 dots and ||w||^2
 // threads of a block that take part in the Givens task and its norm sum; a
 // kernel that runs them needs at least this many threads per block
@@ -72,6 +74,44 @@ struct GState {
   double sc[MAXM + 1];        // slot scales: v_i = sc[i] slot_i (slots keep the unnormalised vectors)
 };
 
+// Sum over the 64 lanes of a wavefront, in every lane: within rows of 16 lanes by
+// DPP (a few cycles a step), across the rows by two shuffles. A chain of six
+// shuffles through LDS costs several times that, and the Arnoldi kernels end on it.
+template <int CTRL> PSFD_D float lane_move(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL> PSFD_D double lane_move(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true));
+}
+template <class R> PSFD_D R lane_sum(R v) {
+  v += lane_move<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += lane_move<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += lane_move<0x141>(v);  // row_half_mirror: the other quad of 8
+  v += lane_move<0x140>(v);  // row_mirror: the other half of the row
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  return v;
+}
+
+// Sum of the n projection partials of one value (n a multiple of 64) over a
+// wavefront in a fixed order: lane l takes partials l, l + 64, ..., then the
+// wavefront sum; 6 loads per lane are issued together. Every lane gets the sum.
+PSFD_D double2 dots_total(const double2* p, int n) {
+  constexpr int U = 6;
+  const int lane = threadIdx.x & 63;
+  double2 t = make_double2(0, 0);
+  for (int k0 = 0; k0 < n; k0 += 64 * U) {
+    double2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = p[min(k0 + 64 * u, n - 64) + lane];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k0 + 64 * u < n) t = cadd(t, v[u]);
+  }
+  return make_double2(lane_sum(t.x), lane_sum(t.y));
+}
+
 // The Arnoldi process runs on B for systems A = I - B (B = K V or M V): the apply
 // writes B v_j into slot j+1, Gram-Schmidt orthogonalises it, and the Givens step
 // forms column j of A's Hessenberg as e_j - h (same Krylov space, no cancellation
@@ -100,11 +140,10 @@ void krylov_update(T* V, long long ldv, long long bsv, long long n, GState* st, 
 // (RED_BLOCKS per instance in part): one block per instance
 void krylov_givens(GState* st, int* run, const double2* part, int nbatch, hipStream_t s);
 // The last column of a cycle without its update pass: h and ||w||^2 from the
-// projection partials (DotBlocks<float2> per value in dpart, as the update pass
-// sums them), ||w - V h||^2 = ||w||^2 - sum |h_i|^2 (orthonormal basis), then the
+// projection partials (nblk per value in dpart, summed by dots_total), ||w - V h||^2 = ||w||^2 - sum |h_i|^2 (orthonormal basis), then the
 // Givens step. Slot j + 1 keeps w; the residual coefficients of the restart fold
 // the update in (krylov_solve_small). One block per instance; FP32 bases.
-void krylov_givens_proj(GState* st, int* run, const double2* dpart, int nbatch, hipStream_t s, int jh);
+void krylov_givens_proj(GState* st, int* run, const double2* dpart, int nblk, int nbatch, hipStream_t s, int jh);
 // y = H^{-1} g over the k = j + 1 completed columns, and the coefficients of the
 // cycle's GMRES residual in the basis, cres = Q^H (g_k e_k) (Q: the Givens
 // rotations); both are stored times the slot scales sc[i], as coefficients of
@@ -112,7 +151,8 @@ void krylov_givens_proj(GState* st, int* run, const double2* dpart, int nbatch, 
 // cres_i -= cres_k h_i sc_i for i < k, so that cres applies to the slots as they are
 void krylov_solve_small(GState* st, const int* mask, int nbatch, hipStream_t s);
 // krylov_givens_proj (column jh) followed by krylov_solve_small (mask) in one launch
-void krylov_givens_proj_solve(GState* st, int* run, const double2* dpart, const int* mask, int nbatch, hipStream_t s,
+void krylov_givens_proj_solve(GState* st, int* run, const double2* dpart, int nblk, const int* mask, int nbatch,
+                              hipStream_t s,
                               int jh);
 // x += sum_{i<k} y_i v_i for the instances with mask[b]; for those with rec[b]
 // also the restart residual from the basis, r = sum_{i<=k} cres_i slot_i, into

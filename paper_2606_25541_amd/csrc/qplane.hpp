@@ -27,17 +27,20 @@
 #include <cstdlib>
 
 #include "kernels.hpp"
+#include "krylov.hpp"
 #include "fft_lds.hpp"
+#include "regfft.hpp"
 
 namespace psfd {
 
 // Threads and values per thread of a block. FP32: 16 values on the planes of
 // 4096 and more values per quarter (rows of 128 by radix 16 and 8, of 256 by
-// 16 and 16), FP64 and the smaller planes 8; at least one thread per column and
-// one wavefront. No pass takes a radix above the values of a thread.
+// 16 and 16), 4 at 1024 (256 threads shorten the chain that bounds them:
+// 64 x 64 x 32 apply 18.9 -> 18.0 us against 8), FP64 and the other planes 8; at
+// least one thread per column and one wavefront. No pass takes a radix above the values of a thread.
 template <class T, int LNX, int LNY> struct QpShape {
   static constexpr int NX = 1 << LNX, NY = 1 << LNY, ROWS = NY / 4, ELEM = ROWS * NX;
-  static constexpr int KW = sizeof(T) == 8 && ELEM >= 4096 ? 16 : 8;
+  static constexpr int KW = sizeof(T) == 8 && ELEM >= 4096 ? 16 : sizeof(T) == 8 && ELEM == 1024 ? 4 : 8;
   static constexpr int N0 = ELEM / KW > NX ? ELEM / KW : NX;
   static constexpr int NT = N0 > 64 ? N0 : 64, KT = ELEM / NT;
   static constexpr int LKT = KT == 16 ? 4 : KT == 8 ? 3 : KT == 4 ? 2 : 1;
@@ -49,13 +52,163 @@ template <class T, int LNX, int LNY> struct QpShape {
 
 template <int NX> PSFD_D int qp_index(int kyq, int kx, int q) { return kyq * (4 * NX) + (kx >> 2) * 16 + 4 * q + (kx & 3); }
 
+// ---- Gram-Schmidt work of an Arnoldi step inside the transverse kernels -------
+// The forward kernel of a step also does the update of the column before, the
+// inverse one the projections of the vector it writes: a block owns the same
+// values of every basis slot, element k of a thread at lane + k 4 NT values from
+// the plane's start in both directions, so a slot is read once per kernel and
+// the new vector not again. Bound by the slot reads on large planes and by the
+// block's chain (partials - sum - slots - transform) and the launch itself on
+// 64 x 64 ones; four blocks per plane overlap those chains. Mean over the columns
+// of GMRES(8), against one block per plane carrying the same work: 128 x 128 x 64
+// forward 36.4 -> 31.3 us, inverse 31.5 -> 28.0; 64 x 64 x 32 10.6 -> 9.4 and 9.9 ->
+// 8.0. Whole Arnoldi step: 128 x 128 x 64 112.7 -> 103.1 us, 128 x 128 x 16 72 -> 54,
+// 64 x 64 x 32 36.5 -> 31.7; shapes that ran separate projection and update passes:
+// 64 x 128 x 32 72.6 -> 40.9, 256 x 64 x 32 101 -> 64, 256 x 256 x 64 508 -> 452.
+//
+// The slots are read in groups of G whose loads are issued together (slots past
+// the last are empty buffers, which load nothing). Two of 4 values per thread,
+// else one: more in flight costs registers, and with them resident blocks, which
+// hide the chains better (64 x 64 x 32, groups of 8 / 4 / 2 / 1: 33.9 / 32.7 / 31.7 /
+// 31.6 us a step, eight instances 119.6 / 114.5 / 110.6 / 111.8).
+template <class S> constexpr int qp_group() { return S::KT == 4 ? 2 : 1; }
+
+template <class S, class T, int KT, int G>
+PSFD_D void qp_slots(const T* V, long long ldv, int i0, int cnt, unsigned lane, T (&p)[G][KT]) {
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const LaneBuf s(V + (long long)min(i0 + g, cnt - 1) * ldv, i0 + g < cnt ? S::NX * S::NY * (int)sizeof(T) : 0);
+#pragma unroll
+    for (int k = 0; k < KT; ++k) s.load(p[g][k], lane, k * 4 * S::NT * (int)sizeof(T));
+  }
+}
+
+// The Gram-Schmidt update of column cnt - 1 on this block's values wv of slot
+// cnt, in place: w - sum_{i<cnt} h_i s_i slot_i, stored back to the slot; this
+// block's ||slot||^2 goes to part[pidx]. h_i = s_i <slot_i, w> from the projection
+// partials, summed by every block in one fixed order (dots_total), so all get the
+// same coefficients bit for bit; block 0 stores h and ||w||^2 before the update
+// for the Givens step.
+template <class S, class T, int KT>
+PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& slot, unsigned lane, int b, int pidx,
+                      long long poff) {
+  constexpr int NT = S::NT, NW = NT / 64, G = qp_group<S>();
+  typedef typename real_of<T>::type R;
+  __shared__ T hc[MAXM];
+  __shared__ double nred[NW];
+  const UpdateTask& u = a.up;
+  const int tid = threadIdx.x, wave = tid >> 6;
+  GState& St = u.st[b];
+  const T* sb = reinterpret_cast<const T*>(u.V) + (long long)b * u.bsv + poff;
+  const double2* pb = u.dpart + (long long)b * PSTR * u.nblk;
+  T p[G][KT];
+  qp_slots<S>(sb, u.ldv, 0, cnt, lane, p);
+  for (int i = wave; i <= cnt; i += NW) {
+    const double sc = St.sc[i];
+    const double2 t = dots_total(pb + (long long)i * u.nblk, u.nblk);
+    if ((tid & 63) == 0) {
+      if (i < cnt) {
+        hc[i] = from_d<T>(cscale(t, sc * sc));
+        if (pidx == 0) St.h[i] = cscale(t, sc);
+      } else if (pidx == 0) {
+        St.wn2_in = t.x;  // value cnt is ||w||^2
+      }
+    }
+  }
+  __syncthreads();
+  for (int i0 = 0; i0 < cnt; i0 += G) {
+    if (i0 > 0) qp_slots<S>(sb, u.ldv, i0, cnt, lane, p);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (i0 + g < cnt) {
+        const T h = hc[i0 + g];
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {
+          wv[k].x -= h.x * p[g][k].x - h.y * p[g][k].y;
+          wv[k].y -= h.x * p[g][k].y + h.y * p[g][k].x;
+        }
+      }
+    }
+  }
+  R nn = 0;
+#pragma unroll
+  for (int k = 0; k < KT; ++k) {
+    slot.store(wv[k], lane, k * 4 * NT * (int)sizeof(T));
+    nn += wv[k].x * wv[k].x + wv[k].y * wv[k].y;
+  }
+  nn = lane_sum(nn);
+  if ((tid & 63) == 0) nred[wave] = (double)nn;
+  __syncthreads();
+  if (tid == 0) {
+    double t = nred[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) t += nred[w];
+    u.part[(long long)b * (12 * a.nz) + pidx] = make_double2(t, 0.0);
+  }
+}
+
+// Gram-Schmidt projections of this block's values wv of the new Arnoldi vector:
+// partial <slot_i, w> for i < cnt and ||w||^2, summed in the vector precision
+// within a wavefront and in FP64 across the wavefronts in a fixed order, stored
+// as partial pidx of nblk (indices no block owns get zeros). p holds the first
+// group of slots (qp_slots before the transform).
+template <class S, class T, int KT, int G>
+PSFD_D void qp_dots(const TileArgs& a, int cnt, const T (&wv)[KT], T (&p)[G][KT], const T* sb, unsigned lane, int b,
+                    int pidx) {
+  constexpr int NW = S::NT / 64;
+  static_assert(S::lds() >= (size_t)PSTR * NW * sizeof(double2), "partials fit the block's LDS");
+  extern __shared__ double2 smem_d[];
+  double2* red = smem_d;  // [PSTR][NW]; the plane's LDS is free after the barrier
+  const DotTask& d = a.dt;
+  const int tid = threadIdx.x, wave = tid >> 6;
+  __syncthreads();
+  for (int i0 = 0; i0 < cnt; i0 += G) {
+    if (i0 > 0) qp_slots<S>(sb, d.ldv, i0, cnt, lane, p);
+    // all G sums side by side (zeros for the slots past the last)
+    T acc[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      acc[g] = cmake<T>(0, 0);
+#pragma unroll
+      for (int k = 0; k < KT; ++k) {
+        acc[g].x += p[g][k].x * wv[k].x + p[g][k].y * wv[k].y;
+        acc[g].y += p[g][k].x * wv[k].y - p[g][k].y * wv[k].x;
+      }
+      acc[g] = cmake<T>(lane_sum(acc[g].x), lane_sum(acc[g].y));
+    }
+    if ((tid & 63) == 0) {
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        if (i0 + g < cnt) red[(i0 + g) * NW + wave] = to_d(acc[g]);
+    }
+  }
+  typename real_of<T>::type nn = 0;
+#pragma unroll
+  for (int k = 0; k < KT; ++k) nn += wv[k].x * wv[k].x + wv[k].y * wv[k].y;
+  nn = lane_sum(nn);
+  if ((tid & 63) == 0) red[cnt * NW + wave] = make_double2((double)nn, 0.0);
+  __syncthreads();
+  if (tid <= cnt) {
+    double2 t = red[tid * NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) t = cadd(t, red[tid * NW + w]);
+    double2* pp = d.part + ((long long)b * PSTR + tid) * d.nblk;
+    pp[pidx] = t;
+    for (int i = pidx + 12 * a.nz; i < d.nblk; i += 12 * a.nz) pp[i] = make_double2(0, 0);
+  }
+  // the update of this column is now pending (read by the next step's kernels)
+  if (pidx == 0 && tid == 0) d.st[b].pend = 1;
+}
+
 template <class T, bool INV, int LD, int ST, int LNX, int LNY>
 __global__ void __launch_bounds__((QpShape<T, LNX, LNY>::NT)) k_qplane(TileArgs a) {
   typedef QpShape<T, LNX, LNY> S;
   constexpr int NX = S::NX, NY = S::NY, QR = S::ROWS, P = NX + 1, NT = S::NT, KT = S::KT, TS = NT / NX;
   constexpr int PN = NX * NY;
   static_assert(!INV || LD == LD_PLAIN, "inverse: plain load");
-  static_assert(INV || (LD == LD_VX && ST == ST_PLAIN), "forward: contrast multiply, plain store");
+  constexpr bool UPD = LD == LD_UPD_VX || LD == LD_UPD_SLOT;  // Gram-Schmidt update on load
+  constexpr bool DOTS = ST == ST_DOTS;
+  static_assert(INV || ((LD == LD_VX || UPD) && ST == ST_PLAIN), "forward: contrast multiply, plain store");
   extern __shared__ double2 smem_d[];
   T* lds = reinterpret_cast<T*>(smem_d);
   T* twx = lds + QR * P;  // W_nx^k, k < nx
@@ -91,6 +244,24 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY>::NT)) k_qplane(TileArgs 
   // the twiddle loads ahead of the data loads: their LDS writes wait for them alone
   __builtin_amdgcn_sched_barrier(0);
   const T* in = vref<T>(a.in, b) + poff;
+  // the update of column cnt - 1 on slot cnt; per instance (up.j < 0) only with a
+  // pending update, and at up.j = 0 not at all: then the plain scaled load of the
+  // slot (by S.inv_norm, as LD_VX with in_scale)
+  int cnt = 0;
+  bool upd = LD == LD_UPD_VX;
+  if constexpr (UPD) cnt = a.up.j;
+  if constexpr (LD == LD_UPD_SLOT) {
+    if (a.up.j >= 0) {
+      upd = cnt > 0;
+    } else {
+      const GState& St = a.up.st[b];
+      const int pend = St.pend, js = St.j;
+      upd = pend != 0;
+      cnt = __builtin_amdgcn_readfirstlane(js + 1);
+      in = reinterpret_cast<const T*>(a.up.V) + (long long)b * a.up.bsv + (long long)(upd ? js + 1 : js) * a.up.ldv +
+           poff;
+    }
+  }
   const T* vol = INV ? nullptr : vref<T>(a.vol, b) + (long long)z * PN;
   const T* aux = ST == ST_AXPBY ? vref<T>(a.aux, b) + poff : nullptr;
   // the column transform's last pass (radix RL, stride PL = ny / 4 / RL)
@@ -100,6 +271,19 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY>::NT)) k_qplane(TileArgs 
   constexpr int RL = S::RL, PL = QR / RL, NBL = KT / RL;
   static_assert(PL == TS * NBL && NBL * RL == KT, "quarter-plane last column pass");
   T va[KT], vb[INV ? 1 : KT], xa[ST == ST_AXPBY ? KT : 1];
+  const unsigned lane = ((4 * (tid >> LNX) + q) * NX + (tid & (NX - 1))) * (unsigned)sizeof(T);
+  if constexpr (UPD) {
+    const LaneBuf slot(in, PN * (unsigned)sizeof(T));
+#pragma unroll
+    for (int k = 0; k < KT; ++k) slot.load(va[k], lane, k * 4 * NT * (int)sizeof(T));
+    const LaneBuf vbuf(vol, PN * (unsigned)sizeof(T));
+    constexpr bool VB0 = KT < 16;  // ahead of the slots where the registers allow it
+#pragma unroll
+    for (int k = 0; k < KT && VB0; ++k) vbuf.load(vb[k], lane, k * 4 * NT * (int)sizeof(T));
+    if (LD == LD_UPD_VX || upd) qp_update<S>(a, cnt, va, slot, lane, b, 4 * plane + q, poff);
+#pragma unroll
+    for (int k = 0; k < KT && !VB0; ++k) vbuf.load(vb[k], lane, k * 4 * NT * (int)sizeof(T));
+  } else
 #pragma unroll
   for (int k = 0; k < KT; ++k) {
     const int i = tid + k * NT, r = i >> LNX, x = i & (NX - 1);
@@ -119,9 +303,21 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY>::NT)) k_qplane(TileArgs 
         xa[i * RL + j] = aux[(4 * r + q) * NX + x];
       }
   }
+  // the first group of basis slots, on its way during the transform
+  constexpr int G = qp_group<S>();
+  T p[DOTS ? G : 1][DOTS ? KT : 1];
+  const T* sb = nullptr;
+  if constexpr (DOTS) {
+    sb = reinterpret_cast<const T*>(a.dt.V) + (long long)b * a.dt.bsv + poff;
+    cnt = a.dt.jh + 1;
+    if (a.dt.jh < 0) cnt = __builtin_amdgcn_readfirstlane(a.dt.st[b].j) + 1;
+    qp_slots<S>(sb, a.dt.ldv, 0, cnt, lane, p);
+  }
   const double* tab = a.tab + (long long)b * a.tab_stride;
   R ks = (R)1;
-  if constexpr (!INV) ks = (R)tab[TS_K0SQ] * (a.in_scale ? (R)a.in_scale[(long long)b * a.scale_stride] : (R)1);
+  // LD_UPD_*: an updated vector enters unscaled (the pencil kernel scales it)
+  if constexpr (UPD) ks = (R)tab[TS_K0SQ] * (LD == LD_UPD_SLOT && !upd ? (R)a.up.st[b].inv_norm : (R)1);
+  else if constexpr (!INV) ks = (R)tab[TS_K0SQ] * (a.in_scale ? (R)a.in_scale[(long long)b * a.scale_stride] : (R)1);
   if (tid < NX) twx[tid] = tw0;
   if (tid < QR) twr[tid] = tw1;
   if constexpr (NX != NY)
@@ -160,8 +356,10 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY>::NT)) k_qplane(TileArgs 
           v.y = al * xv.y + ga * v.y;
         }
         out[(4 * r + q) * NX + x] = v;
+        if constexpr (DOTS) va[i + NBL * j] = v;  // row 4 r + q: element k = i + NBL j of the thread
       }
     }
+  if constexpr (DOTS) qp_dots<S>(a, cnt, va, p, sb, lane, b, 4 * plane + q);
 }
 
 // Whether a plane takes the quarter kernels: both sides 16 .. 256 and 1024 or
@@ -177,6 +375,15 @@ constexpr bool qplane_fits(int lnx, int lny, size_t esz) {
   return lnx >= 4 && lnx <= 8 && lny >= 4 && lny <= 8 && lnx + lny >= 10 && lnx + lny - 2 <= (esz == 8 ? 14 : 13);
 }
 
+// Whether the quarter kernels of a plane also carry the Gram-Schmidt work of an
+// Arnoldi step: FP32 (mixed precision's inner solves), 4096 and more values per
+// plane. Every block of the update sums all 12 nz partials of each projection, so
+// on smaller planes that sum would outweigh the block's own values; they keep
+// the separate passes.
+constexpr bool qplane_gs_fits(int lnx, int lny, size_t esz) {
+  return esz == 8 && qplane_fits(lnx, lny, esz) && lnx + lny >= 12;
+}
+
 template <class T, bool INV, int LD, int ST>
 void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s) {
   auto go = [&](auto kern, int nt, size_t l) {
@@ -188,7 +395,8 @@ void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s) {
   if (!a.gv.st && nplanes == 3 * a.nz) {
     auto shape = [&](auto lx, auto ly) {
       constexpr int LX = decltype(lx)::value, LY = decltype(ly)::value;
-      if constexpr (qplane_fits(LX, LY, sizeof(T))) {
+      constexpr bool GS = ST == ST_DOTS || LD == LD_UPD_VX || LD == LD_UPD_SLOT;
+      if constexpr (GS ? qplane_gs_fits(LX, LY, sizeof(T)) : qplane_fits(LX, LY, sizeof(T))) {
         if (a.nx != 1 << LX || a.ny != 1 << LY) return;
         typedef QpShape<T, LX, LY> S;
         go(k_qplane<T, INV, LD, ST, LX, LY>, S::NT, S::lds());

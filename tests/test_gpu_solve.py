@@ -152,6 +152,50 @@ def test_update_in_forward_plane_kernel_matches_separate_pass(n, monkeypatch):
     assert np.max(np.abs(o1.cpu().numpy() - o2.cpu().numpy())) < 1e-9
 
 
+@pytest.mark.parametrize("shape", [(64, 64, 8), (128, 128, 16), (256, 16, 32), (16, 256, 64), (32, 128, 32),
+                                   (64, 128, 64), (256, 64, 32), (256, 256, 8)])
+def test_gram_schmidt_in_quarter_planes_matches_separate_passes(shape, monkeypatch):
+    """Mixed solves on planes of 4096 and more values: the Gram-Schmidt work in the
+    quarter-plane kernels (projections only below 32 z planes, where the partials
+    are padded for the separate update pass; with the update from 32 on) against
+    the separate passes (PSFD_FUSE_DOTS=0), for every split of a block (4, 8 and 16
+    values per thread, 1024 threads). Both stop at the same tolerance, so the
+    fields agree to the conditioning times it, within one restart cycle of the
+    same step count; repeated solves and a served slot are bitwise the same."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    nx, ny, nz = shape
+    layers, es = clips.mo_si_stack(40)
+    p = clips.Problem(nx=nx, ny=ny, nz=nz, lx_nm=2.0 * nx, ly_nm=2.0 * ny, t_nm=60.0, theta_deg=6.0,
+                      phi_deg=15.0, pol=1, layers=layers, eps_sub=es)
+    d = torch.from_numpy(clips.contact_holes(nx, ny, nz, 2.0 * nx, 2.0 * ny, 6, seed=78)).to(dev)
+    say("solve %dx%dx%d mixed, Gram-Schmidt in quarter planes" % shape)
+    plan = api.Plan(p, rtol=1e-9, precision="mixed", restart=8)
+    e1, o1, i1 = plan.psfd_solve(d)
+    e1b, o1b, i1b = plan.psfd_solve(d)
+    srv = api.Server(hbm_budget=8 << 30, max_slots=2, rtol=1e-9, precision="mixed", restart=8)
+    es_, os_ = torch.empty_like(e1), torch.empty_like(o1)
+    t = srv.submit(p, d, es_, os_)
+    deadline = time.perf_counter() + 60
+    done = False
+    while not done and time.perf_counter() < deadline:
+        done, info, _ = srv.poll(t)
+        time.sleep(0.002)
+    srv.close()
+    assert done, "served request not finished within 60 s"
+    monkeypatch.setenv("PSFD_FUSE_DOTS", "0")
+    e2, o2, i2 = plan.psfd_solve(d)
+    say("  fused", i1, "served", info, "separate", i2)
+    assert i1["status"] == 0 and i2["status"] == 0 and info["status"] == 0
+    assert torch.equal(e1, e1b) and i1 == i1b
+    if nz >= 32:
+        assert torch.equal(e1, es_) and info["iters"] == i1["iters"]
+    else:
+        assert rel(e1.cpu().numpy(), es_.cpu().numpy()) < 1e-7
+    assert abs(i1["iters"] - i2["iters"]) <= 8
+    assert rel(e1.cpu().numpy(), e2.cpu().numpy()) < 1e-7
+
+
 def test_fp64_solve_quarter_planes_match_strips(monkeypatch):
     """128 x 128 x 32, FP64, lock-step: the Arnoldi steps and b - A x on quarter
     planes (four blocks per plane, the radix-4 y combine in the pencil) against
