@@ -641,8 +641,10 @@ __global__ void __launch_bounds__(LPZ ? pencil_threads_ct(LPZ ? LPZ : 4, BXC) : 
   if (a.active && !a.active[b]) return;
   const int bx = LPZ ? BXC : a.bx, pz = LPZ ? (1 << LPZ) : a.pz, nz = pz / 2, nx = a.nx, ny = a.ny;
   static_assert(!YQ || LPZ > 0, "quarter layout: compile-time pencils");
-  const int ky = blockIdx.x / a.nblk_x;  // YQ: the quarter-spectrum row ky'
-  const int kx0 = (blockIdx.x - ky * a.nblk_x) * (YQ ? BXC / 4 : bx);
+  int bid = blockIdx.x;
+  if constexpr (YQ && BXC == 8) bid = (bid & ~15) | ((bid & 7) << 1) | ((bid >> 3) & 1);
+  const int ky = bid / a.nblk_x;  // YQ: the quarter-spectrum row ky'
+  const int kx0 = (bid - ky * a.nblk_x) * (YQ ? BXC / 4 : bx);
   const int tid = threadIdx.x, nthr = LPZ ? pencil_threads_ct(LPZ, BXC) : (int)blockDim.x;
   const int LS = 3 * bx;
   const int lbx = LPZ ? (BXC == 16 ? 4 : BXC == 8 ? 3 : 2) : ilog2i(bx);
@@ -658,7 +660,7 @@ __global__ void __launch_bounds__(LPZ ? pencil_threads_ct(LPZ ? LPZ : 4, BXC) : 
   constexpr bool CT = LPZ > 0;
   constexpr int ZSTEP = CT ? pencil_threads_ct(LPZ, BXC) / (3 * BXC) : 1;
   constexpr int VT = CT ? (1 << LPZ) / 2 / ZSTEP : 4;  // values per thread (data half)
-  static_assert(!CT || ((BXC == 16 || (BXC == 8 && LPZ == 8)) && pencil_threads_ct(LPZ, BXC) == ZSTEP * 3 * BXC &&
+  static_assert(!CT || ((BXC == 16 || BXC == 8) && pencil_threads_ct(LPZ, BXC) == ZSTEP * 3 * BXC &&
                         VT * ZSTEP * 2 == (1 << LPZ) && (VT == 4 || VT == 2)),
                 "pencil thread split");
   const int ck = tid & (bx - 1);
@@ -969,6 +971,7 @@ void launch_pencil(const PencilArgs& a, int nbatch, int nthr, size_t lds, hipStr
     if (is(6, 16)) return go(k_pencil<T, 6, 16, true>);
     if (is(7, 16)) return go(k_pencil<T, 7, 16, true>);
     if (is(8, 8)) return go(k_pencil<T, 8, 8, true>);
+    if (is(7, 8)) return go(k_pencil<T, 7, 8, true>);
     std::fprintf(stderr, "psfd: internal error: quarter-plane pencil on an unsupported shape\n");
     std::abort();
   }
