@@ -7,12 +7,13 @@
 //
 // A step runs on the device alone: the step kernel sums the partials, forms the
 // norm and scale the update takes, and writes them to mapped host memory; the
-// three launches of a second pass test its flag and return at once where it is not
+// launches of a second pass test its flag and return at once where it is not
 // needed. The host issues the next step's apply before it waits for a step's
 // scalars, so that the device never waits for the host's rotations; that apply is
 // dropped where the step ends the cycle. On a 32 x 32 x 16 isolated FP64 solve a step
 // took about 165 us of which its kernels were 45 (copies down and up, two waits and
-// their wake-ups); it takes about 55 now, 2.6 -> 0.91 ms the solve.
+// their wake-ups); with the three launches of k_gm_pass it takes about 40,
+// 2.6 -> 0.79 ms the solve.
 #include "gmres_host.hpp"
 
 #include <algorithm>
@@ -27,6 +28,11 @@ namespace {
 
 constexpr int KB = 256;      // threads per block
 constexpr double ETA_MIXED = 1e-4;
+// Vectors up to this length (4 values per thread of GM_BLOCKS blocks) take a
+// Gram-Schmidt pass in one launch (k_gm_pass); beyond, 256 blocks are too few
+// for the memory and the separate kernels' blocks are as many as the vector needs
+// (a step at 98304 values 67.2 -> 63.6 us, at 196608 98.6 -> 97.4, at 786432 207 -> 208).
+constexpr long long GM_SHORT = 4LL * GM_BLOCKS * KB;
 
 #define GMCHK(call)                                    \
   do {                                                 \
@@ -68,11 +74,7 @@ __global__ void __launch_bounds__(KB) k_gm_dots(const T* __restrict__ V, long lo
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      acc[q].x += __shfl_xor(acc[q].x, off, 64);
-      acc[q].y += __shfl_xor(acc[q].y, off, 64);
-    }
+    acc[q] = make_double2(lane_sum(acc[q].x), lane_sum(acc[q].y));
     if ((tid & 63) == 0) red[q][tid >> 6] = acc[q];
   }
   __syncthreads();
@@ -84,30 +86,41 @@ __global__ void __launch_bounds__(KB) k_gm_dots(const T* __restrict__ V, long lo
   }
 }
 
-// One block: the nv sums of the partials (one wavefront each, in a fixed order):
-// the projections h of a pass, then ||w||^2 before it; hn, inv and (first pass)
-// cancel as in GmScalars. What the host reads also goes to mapped host memory.
-__global__ void __launch_bounds__(1024) k_gm_step(const double2* __restrict__ part, int nv, double cancel,
-                                                  GmScalars* dev, GmScalars* host, bool second) {
-  __shared__ double2 h[GM_MAX + 2];
-  if (second && !dev->cancel) return;
+// The nv sums of the partials into h (LDS), one wavefront each in a fixed order;
+// every thread of the block of NT calls it, a barrier follows.
+template <int NT> PSFD_D void gm_sums(const double2* __restrict__ part, int nv, double2* h) {
   const int lane = threadIdx.x & 63;
-  for (int i = threadIdx.x >> 6; i < nv; i += 16) {
+#pragma unroll 2
+  for (int i = threadIdx.x >> 6; i < nv; i += NT / 64) {
     double2 p[GM_BLOCKS / 64];
 #pragma unroll
     for (int k = 0; k < GM_BLOCKS / 64; ++k) p[k] = part[(long long)i * GM_BLOCKS + lane + 64 * k];
     double2 t = p[0];
 #pragma unroll
     for (int k = 1; k < GM_BLOCKS / 64; ++k) t = cadd(t, p[k]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      t.x += __shfl_xor(t.x, off, 64);
-      t.y += __shfl_xor(t.y, off, 64);
-    }
+    t = make_double2(lane_sum(t.x), lane_sum(t.y));
     if (lane == 0) h[i] = t;
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nv; i += 1024) {
+}
+
+// ||w||^2 before a pass is h[nv - 1], the projections are the others: the norm
+// after it by Pythagoras
+PSFD_D double gm_norm(const double2* h, int nv) {
+  const double w2 = h[nv - 1].x;
+  double p2 = 0.0;
+  for (int i = 0; i < nv - 1; ++i) p2 += h[i].x * h[i].x + h[i].y * h[i].y;
+  const double d2 = w2 - p2;
+  return d2 == d2 ? sqrt(fmax(d2, 0.0)) : d2;  // (fmax would drop a NaN)
+}
+PSFD_D double gm_inv(double hn) { return hn > 0.0 ? 1.0 / hn : 1.0; }
+PSFD_D bool gm_cancel(double hn, double w2, double cancel) { return !(hn >= cancel * sqrt(fmax(w2, 0.0))); }
+
+// What a pass leaves in GmScalars; what the host reads also goes to mapped host
+// memory. NT threads of one block.
+template <int NT>
+PSFD_D void gm_publish(const double2* h, int nv, double hn, double cancel, GmScalars* dev, GmScalars* host,
+                       bool second) {
+  for (int i = threadIdx.x; i < nv; i += NT) {
     if (second) {
       dev->h2[i] = h[i];
       host->h[i] = cadd(dev->h[i], h[i]);
@@ -116,17 +129,95 @@ __global__ void __launch_bounds__(1024) k_gm_step(const double2* __restrict__ pa
     }
   }
   if (threadIdx.x == 0) {
-    const double w2 = h[nv - 1].x;
-    double p2 = 0.0;
-    for (int i = 0; i < nv - 1; ++i) p2 += h[i].x * h[i].x + h[i].y * h[i].y;
-    const double d2 = w2 - p2;
-    const double hn = d2 == d2 ? sqrt(fmax(d2, 0.0)) : d2;  // (fmax would drop a NaN)
     dev->hn = host->hn = hn;
-    dev->inv = hn > 0.0 ? 1.0 / hn : 1.0;
+    dev->inv = gm_inv(hn);
     if (!second) {
+      const double w2 = h[nv - 1].x;
       dev->w2 = host->w2 = w2;
-      dev->cancel = !(hn >= cancel * sqrt(fmax(w2, 0.0)));
+      dev->cancel = gm_cancel(hn, w2, cancel);
     }
+  }
+}
+
+// One block: the sums of the partials, then hn, inv and (first pass) cancel as in
+// GmScalars.
+__global__ void __launch_bounds__(1024) k_gm_step(const double2* __restrict__ part, int nv, double cancel,
+                                                  GmScalars* dev, GmScalars* host, bool second) {
+  __shared__ double2 h[GM_MAX + 2];
+  if (second && !dev->cancel) return;
+  gm_sums<1024>(part, nv, h);
+  __syncthreads();
+  const double hn = threadIdx.x == 0 ? gm_norm(h, nv) : 0.0;
+  gm_publish<1024>(h, nv, hn, cancel, dev, host, second);
+}
+
+// A Gram-Schmidt pass of a short vector in one launch of GM_BLOCKS blocks: every
+// block sums the projection partials itself (part; nv vectors and ||w||^2), updates
+// its elements of w, and in the first pass, where a second one follows, forms that
+// one's partials (part2) from the elements it has just written. With k_gm_dots in
+// front a step then takes three launches beside the apply where dots, step and
+// update of both passes take six, each 3 to 6 us of latency on the timeline
+// whatever its work: a 32 x 32 x 16 FP64 isolated solve 914 -> 787 us,
+// 64 x 64 x 16 mixed 71 -> 68 us a step. Element
+// and partial order are those of the separate kernels.
+template <class T, bool SECOND>
+__global__ void __launch_bounds__(KB) k_gm_pass(T* __restrict__ w, const T* __restrict__ V, long long stride, int nv,
+                                                long long n, const double2* __restrict__ part,
+                                                double2* __restrict__ part2, double cancel, GmScalars* dev,
+                                                GmScalars* host) {
+  __shared__ double2 h[GM_MAX + 2], red[4][KB / 64];
+  __shared__ double hns;
+  if (SECOND && !dev->cancel) return;
+  const int tid = threadIdx.x;
+  const long long e0 = (long long)blockIdx.x * KB + tid, step = (long long)GM_BLOCKS * KB;
+  gm_sums<KB>(part, nv + 1, h);
+  __syncthreads();
+  if (tid == 0) hns = gm_norm(h, nv + 1);
+  __syncthreads();
+  const double hn = hns;
+  const bool more = !SECOND && gm_cancel(hn, h[nv].x, cancel);
+  const double inv = more ? 1.0 : gm_inv(hn);
+  if (blockIdx.x == 0) gm_publish<KB>(h, nv + 1, hn, cancel, dev, host, SECOND);
+  for (long long e = e0; e < n; e += step) {
+    double2 acc = to_d(w[e]);
+#pragma unroll 4
+    for (int i = 0; i < nv; ++i) {
+      const double2 c = h[i], v = to_d(V[i * stride + e]);
+      acc.x -= c.x * v.x - c.y * v.y;
+      acc.y -= c.x * v.y + c.y * v.x;
+    }
+    w[e] = from_d<T>(cscale(acc, inv));
+  }
+  if (!more) return;
+  for (int i0 = 0; i0 <= nv; i0 += 4) {
+    const T* v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = i0 + q < nv ? V + (i0 + q) * stride : w;
+    double2 acc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = make_double2(0.0, 0.0);
+    for (long long e = e0; e < n; e += step) {
+      const double2 c = to_d(w[e]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double2 a = to_d(v[q][e]);
+        acc[q].x += a.x * c.x + a.y * c.y;
+        acc[q].y += a.x * c.y - a.y * c.x;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc[q] = make_double2(lane_sum(acc[q].x), lane_sum(acc[q].y));
+      if ((tid & 63) == 0) red[q][tid >> 6] = acc[q];
+    }
+    __syncthreads();
+    if (tid < 4 && i0 + tid <= nv) {
+      double2 t = red[tid][0];
+#pragma unroll
+      for (int k = 1; k < KB / 64; ++k) t = cadd(t, red[tid][k]);
+      part2[(long long)(i0 + tid) * GM_BLOCKS + blockIdx.x] = t;
+    }
+    __syncthreads();
   }
 }
 
@@ -219,9 +310,13 @@ Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, cons
   const volatile GmScalars* hs = ws.host;
   // the sums V_i^H w, i < nv (the last: w itself), what the step kernel makes of
   // them, and the scalars' event
-  auto dots = [&](int nv, const T* w, bool second) {
+  double2* part2 = ws.part + GM_BLOCKS * (GM_MAX + 2);
+  auto proj = [&](int nv, const T* w, bool second) {
     hipLaunchKernelGGL(k_gm_dots<T>, dim3(GM_BLOCKS, (nv + 3) / 4), dim3(KB), 0, s, (const T*)V, n, nv, w, n, ws.part,
                        (const GmScalars*)ws.dev, second);
+  };
+  auto dots = [&](int nv, const T* w, bool second) {
+    proj(nv, w, second);
     hipLaunchKernelGGL(k_gm_step, dim3(1), dim3(1024), 0, s, ws.part, nv, o.cancel, ws.dev, ws.dhost, second);
   };
   // ev marks the scalars of the launches so far
@@ -290,13 +385,22 @@ Status gmres_t(long long n, const ApplyFn& A, const double2* B, double2* X, cons
       // cancellation (norm ratio below cancel) takes a second pass
       T* wj = V + (j + 1) * n;
       if (!ahead && !(st = A(V + j * n, wj, dt, s)).ok()) return st;
-      dots(j + 2, wj, false);
-      hipLaunchKernelGGL((k_gm_update<T, false>), dim3(g1), dim3(KB), 0, s, wj, (const T*)V, n,
-                         (const GmScalars*)ws.dev, j + 1, n);
-      dots(j + 2, wj, true);
-      if (!(st = mark()).ok()) return st;
-      hipLaunchKernelGGL((k_gm_update<T, true>), dim3(g1), dim3(KB), 0, s, wj, (const T*)V, n,
-                         (const GmScalars*)ws.dev, j + 1, n);
+      if (n <= GM_SHORT) {
+        proj(j + 2, wj, false);
+        hipLaunchKernelGGL((k_gm_pass<T, false>), dim3(GM_BLOCKS), dim3(KB), 0, s, wj, (const T*)V, n, j + 1, n,
+                           (const double2*)ws.part, part2, o.cancel, ws.dev, ws.dhost);
+        hipLaunchKernelGGL((k_gm_pass<T, true>), dim3(GM_BLOCKS), dim3(KB), 0, s, wj, (const T*)V, n, j + 1, n,
+                           (const double2*)part2, ws.part, o.cancel, ws.dev, ws.dhost);
+        if (!(st = mark()).ok()) return st;
+      } else {
+        dots(j + 2, wj, false);
+        hipLaunchKernelGGL((k_gm_update<T, false>), dim3(g1), dim3(KB), 0, s, wj, (const T*)V, n,
+                           (const GmScalars*)ws.dev, j + 1, n);
+        dots(j + 2, wj, true);
+        if (!(st = mark()).ok()) return st;
+        hipLaunchKernelGGL((k_gm_update<T, true>), dim3(g1), dim3(KB), 0, s, wj, (const T*)V, n,
+                           (const GmScalars*)ws.dev, j + 1, n);
+      }
       ahead = j + 1 < m && inf.iters + 1 < o.max_iters;
       if (ahead && !(st = A(wj, wj + n, dt, s)).ok()) return st;
       if (!(st = wait()).ok()) return st;
@@ -354,7 +458,7 @@ GmresWs::~GmresWs() {
 }
 
 static Status ws_ready(GmresWs& w) {
-  if (!w.part) GMCHK(hipMalloc((void**)&w.part, sizeof(double2) * GM_BLOCKS * (GM_MAX + 2)));
+  if (!w.part) GMCHK(hipMalloc((void**)&w.part, 2 * sizeof(double2) * GM_BLOCKS * (GM_MAX + 2)));
   if (!w.dev) GMCHK(hipMalloc((void**)&w.dev, sizeof(GmScalars)));
   if (!w.host) {
     GMCHK(hipHostMalloc((void**)&w.host, sizeof(GmScalars), hipHostMallocCoherent | hipHostMallocMapped));

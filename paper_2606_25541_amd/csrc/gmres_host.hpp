@@ -21,7 +21,7 @@ struct HostGmres {
 };
 
 // Small buffers of a solver, kept by the plan that calls it (solves on one plan
-// do not overlap): reduction partials, the scalars of the current step on the
+// do not overlap): reduction partials of two passes, the scalars of the current step on the
 // device, and their copy in mapped host memory, which the step kernel writes
 // itself.
 constexpr int GM_MAX = 64;      // largest restart length

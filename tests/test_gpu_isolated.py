@@ -313,3 +313,56 @@ def test_iso_line_lengths_match_the_padded_convolution(shape):
         err = np.abs(y.cpu().numpy() - ref).max() / np.abs(ref).max()
         say("  ", dt, "err %.2e" % err)
         assert err <= bar
+
+
+@pytest.mark.parametrize("second_pass", ["on_cancellation", "always"])
+@pytest.mark.parametrize("shape", [(4, 4, 2), (16, 16, 8), (32, 32, 16), (64, 64, 16), (64, 64, 32)],
+                         ids=lambda s: "%dx%dx%d" % s)
+def test_iso_solve_steps_match_a_plain_gmres(shape, second_pass, monkeypatch):
+    """The Gram-Schmidt launches of short vectors (up to 262144 values: fewer values
+    than threads, one and three per thread) and of long ones, against modified
+    Gram-Schmidt GMRES in complex128 torch on the same operator: the residual
+    formed outside the solver is within the tolerance (1 + 1e-6: the FP64 rounding
+    of b - A x), and the steps agree within one (the residual estimates of the two
+    orthogonalisations differ by rounding, which matters only at the threshold)."""
+    if second_pass == "always":
+        monkeypatch.setenv("PSFD_ISO_CANCEL", "2.0")
+    nx, ny, nz = shape
+    dev = device()
+    plan = iso_plan((nz, ny, nx), (2.0, 2.0, 2.0), 1.0 + 0.0j)
+    g = torch.Generator(device=dev).manual_seed(31)
+    n = (3, nz, ny, nx)
+    cplx = lambda s: torch.complex(*(torch.randn(s, dtype=torch.float64, device=dev, generator=g) for _ in range(2)))
+    d = 0.2 * cplx(n[1:])
+    b = cplx(n)
+    rtol, m = 1e-9, 12
+    say("isolated solve steps", shape, second_pass)
+    x, info = plan.psfd_iso_solve(d, b, rtol=rtol, restart=m)
+    assert info["status"] == 0
+    bn = torch.linalg.vector_norm(b)
+    assert torch.linalg.vector_norm(b - plan.psfd_iso_apply(d, x)) <= rtol * (1 + 1e-6) * bn
+    xr, steps = torch.zeros_like(b), 0
+    while True:
+        assert steps < 600
+        r = b - plan.psfd_iso_apply(d, xr)
+        beta = torch.linalg.vector_norm(r)
+        if beta <= rtol * bn:
+            break
+        V, H = [r / beta], torch.zeros((m + 1, m), dtype=torch.complex128)
+        for j in range(m):
+            w = plan.psfd_iso_apply(d, V[j])
+            for i in range(j + 1):
+                H[i, j] = torch.sum(torch.conj(V[i]) * w).cpu()
+                w = w - H[i, j].item() * V[i]
+            H[j + 1, j] = torch.linalg.vector_norm(w).cpu()
+            V.append(w / H[j + 1, j].item())
+            steps += 1
+            e = torch.zeros(j + 2, dtype=torch.complex128)
+            e[0] = beta.cpu()
+            y = torch.linalg.lstsq(H[:j + 2, :j + 1], e[:, None]).solution
+            if torch.linalg.vector_norm(e[:, None] - H[:j + 2, :j + 1] @ y) <= rtol * bn.cpu():
+                break
+        for i in range(j + 1):
+            xr = xr + y[i, 0].item() * V[i]
+    say("  steps", info["iters"], "plain", steps)
+    assert abs(info["iters"] - steps) <= 1
