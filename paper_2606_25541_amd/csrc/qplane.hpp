@@ -33,14 +33,18 @@
 
 namespace psfd {
 
-// Threads and values per thread of a block. FP32: 16 values on the planes of
-// 4096 and more values per quarter (rows of 128 by radix 16 and 8, of 256 by
-// 16 and 16), 4 at 1024 (256 threads shorten the chain that bounds them:
-// 64 x 64 x 32 apply 18.9 -> 18.0 us against 8), FP64 and the other planes 8; at
-// least one thread per column and one wavefront. No pass takes a radix above the values of a thread.
-template <class T, int LNX, int LNY> struct QpShape {
+// Threads and values per thread of a block. FP32: 16 values on quarters of more
+// than 4096 values (256 x 256: 1024 threads), 4 at 1024 (256 threads shorten the
+// chain that bounds them: 64 x 64 x 32 apply 18.9 -> 18.0 us against 8), else 8. At
+// 4096 values 8 against 16: apply 256 x 64 x 16 28.2 -> 26.9 us, 128 x 128 x 8 22.7 ->
+// 21.3, 128 x 128 x 64 51.4 alike; with the Gram-Schmidt work a step at
+// 128 x 128 x 8 43.1 -> 41.3, at 32 planes 66.3 alike, at 64 103.7 -> 105.7: WIDE (16)
+// there, where the blocks are enough to fill the chip and the basis slots bound
+// the kernel. FP64: 8. At least one thread per column and one wavefront. No pass
+// takes a radix above the values of a thread.
+template <class T, int LNX, int LNY, bool WIDE> struct QpShape {
   static constexpr int NX = 1 << LNX, NY = 1 << LNY, ROWS = NY / 4, ELEM = ROWS * NX;
-  static constexpr int KW = sizeof(T) == 8 && ELEM >= 4096 ? 16 : sizeof(T) == 8 && ELEM == 1024 ? 4 : 8;
+  static constexpr int KW = sizeof(T) == 16 ? 8 : ELEM >= (WIDE ? 4096 : 8192) ? 16 : ELEM == 1024 ? 4 : 8;
   static constexpr int N0 = ELEM / KW > NX ? ELEM / KW : NX;
   static constexpr int NT = N0 > 64 ? N0 : 64, KT = ELEM / NT;
   static constexpr int LKT = KT == 16 ? 4 : KT == 8 ? 3 : KT == 4 ? 2 : 1;
@@ -200,9 +204,9 @@ PSFD_D void qp_dots(const TileArgs& a, int cnt, const T (&wv)[KT], T (&p)[G][KT]
   if (pidx == 0 && tid == 0) d.st[b].pend = 1;
 }
 
-template <class T, bool INV, int LD, int ST, int LNX, int LNY>
-__global__ void __launch_bounds__((QpShape<T, LNX, LNY>::NT)) k_qplane(TileArgs a) {
-  typedef QpShape<T, LNX, LNY> S;
+template <class T, bool INV, int LD, int ST, int LNX, int LNY, bool WIDE>
+__global__ void __launch_bounds__((QpShape<T, LNX, LNY, WIDE>::NT)) k_qplane(TileArgs a) {
+  typedef QpShape<T, LNX, LNY, WIDE> S;
   constexpr int NX = S::NX, NY = S::NY, QR = S::ROWS, P = NX + 1, NT = S::NT, KT = S::KT, TS = NT / NX;
   constexpr int PN = NX * NY;
   static_assert(!INV || LD == LD_PLAIN, "inverse: plain load");
@@ -398,8 +402,16 @@ void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s) {
       constexpr bool GS = ST == ST_DOTS || LD == LD_UPD_VX || LD == LD_UPD_SLOT;
       if constexpr (GS ? qplane_gs_fits(LX, LY, sizeof(T)) : qplane_fits(LX, LY, sizeof(T))) {
         if (a.nx != 1 << LX || a.ny != 1 << LY) return;
-        typedef QpShape<T, LX, LY> S;
-        go(k_qplane<T, INV, LD, ST, LX, LY>, S::NT, S::lds());
+        // the 16-value split by the shape alone, so that a solve takes the same
+        // arithmetic by itself, in a batch and in a server's slot
+        constexpr bool W = GS && LX + LY == 14;
+        auto split = [&](auto wide) {
+          constexpr bool WIDE = decltype(wide)::value;
+          typedef QpShape<T, LX, LY, WIDE> S;
+          go(k_qplane<T, INV, LD, ST, LX, LY, WIDE>, S::NT, S::lds());
+        };
+        if (W && a.nz > 32) split(std::bool_constant<W>());
+        else split(std::false_type());
         done = true;
       }
     };
