@@ -8,9 +8,9 @@
 //   y = IFFT_xy C FFT_xy x - V x,   D y = IFFT_xy D_z (C FFT_xy x - FFT_xy V x).
 // (The run-time kernels take four and seven: V x as a pass of its own, and the
 // damping as another forward transform, pencil and inverse.) Whole apply, before
-// and after: 32 x 32 x 256 FP32 damped 97 -> 33.6 us, 64 x 64 x 128 FP64 undamped
-// 70.8 -> 46.1, 16 x 32 x 128 FP32 undamped 39.0 -> 17.6. The FP64 case moves 160 MB
-// (3.5 TB/s); the small ones are bound by the serial chain of a column's transforms
+// and after: 32 x 32 x 256 FP32 damped 97 -> 32.0 us, 64 x 64 x 128 FP64 undamped
+// 70.7 -> 43.8, 16 x 32 x 128 FP32 undamped 39.0 -> 17. The FP64 case moves 160 MB
+// (3.7 TB/s); the small ones are bound by the serial chain of a column's transforms
 // and by launches.
 #include "diff.hpp"
 #include "fft_lds.hpp"
@@ -106,15 +106,17 @@ __global__ void __launch_bounds__((DpShape<LNX, LNY>::NT)) k_diff_plane(DiffPlan
 // z columns. A sequence (component, column) of N planes lives in TH = N / R1
 // threads, thread t holding planes t + TH j (j < R1). Its DFT is one register DFT
 // over j, an exchange through LDS, and the TH-point transform over t of every
-// residue k1: a second register DFT (N <= 256), or two with another exchange (512,
-// 1024). The inverse goes back the same way, in place, to the same planes.
+// residue k1: a second register DFT where TH <= R1, else two with another exchange.
+// The inverse goes back the same way, in place, to the same planes.
 // -------------------------------------------------------------------------
-template <class T, int N, int LB> struct ZF {
-  static constexpr bool L3 = N > 256;
-  static constexpr int R1 = N == 64 ? 8 : 16, TH = N / R1, E = R1;
-  static constexpr int K = R1 / TH;           // N <= 256: residues per thread
-  static constexpr int SK = N == 1024 ? 8 : 4;  // L3: TH = SK * 8, t = t0 + SK t1
-  static constexpr int NC = 16 * 8 / (L3 ? TH : 128);  // L3: last butterflies (radix SK) per thread
+template <class T, int N, int LB, int R1> struct ZF {
+  static constexpr int TH = N / R1, E = R1;
+  static constexpr bool L3 = TH > R1;
+  static constexpr int K = L3 ? 1 : R1 / TH;       // two passes: residues per thread
+  static constexpr int SK = L3 ? TH / 8 : 1;       // L3: TH = SK * 8, t = t0 + SK t1
+  static constexpr int NM = R1 * SK / TH;          // L3: middle butterflies (radix 8) per thread
+  static constexpr int NC = L3 ? R1 * 8 / TH : 1;  // L3: last butterflies (radix SK) per thread
+  static_assert(!L3 || (SK <= 8 && NM >= 1 && NC >= 1 && NM * 8 == R1 && NC * SK == R1), "z column passes");
   // LDS position of (k1, t): rows of TH with a pad per row (L3: per SK), so that the
   // lanes of a pass (LB columns by consecutive t, or by consecutive k1 or t1) meet
   // distinct banks
@@ -125,7 +127,7 @@ template <class T, int N, int LB> struct ZF {
   PSFD_D static int freq(int t, int e) {
     if constexpr (L3) {
       const int b = t + TH * (e / SK);
-      return (b >> 3) + 16 * ((b & 7) + 8 * (e % SK));
+      return (b >> 3) + R1 * ((b & 7) + 8 * (e % SK));
     } else {
       return t + TH * (e / TH) + R1 * (e % TH);
     }
@@ -160,7 +162,7 @@ template <class T, int N, int LB> struct ZF {
     } else {
       if (act) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < NM; ++i) {
           const int b = t + TH * i, k1 = b / SK, t0 = b % SK;
           T v[8];
 #pragma unroll
@@ -168,7 +170,7 @@ template <class T, int N, int LB> struct ZF {
           dft_r<T, 8, false>(v);
 #pragma unroll
           for (int s = 0; s < 8; ++s) {
-            if (s > 0) v[s] = cmul(v[s], tw[16 * t0 * s]);
+            if (s > 0) v[s] = cmul(v[s], tw[R1 * t0 * s]);
             buf[at(k1, t0 + SK * s)] = v[s];
           }
         }
@@ -215,13 +217,13 @@ template <class T, int N, int LB> struct ZF {
       __syncthreads();
       if (act) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < NM; ++i) {
           const int b = t + TH * i, k1 = b / SK, t0 = b % SK;
           T v[8];
 #pragma unroll
           for (int s = 0; s < 8; ++s) {
             v[s] = buf[at(k1, t0 + SK * s)];
-            if (s > 0) v[s] = cmulc(v[s], tw[16 * t0 * s]);
+            if (s > 0) v[s] = cmulc(v[s], tw[R1 * t0 * s]);
           }
           dft_r<T, 8, true>(v);
 #pragma unroll
@@ -259,17 +261,17 @@ template <class T> PSFD_D T times_i(T a, typename real_of<T>::type k) {  // i k 
 // thread form a serial chain.
 // The values of planes (component c, t + TH j) are read from memory again where
 // they are needed next instead of held (FP64: they do not fit).
-template <class T, int N, int LB> struct ZcolShape {
-  typedef ZF<T, N, LB> F;
+template <class T, int N, int LB, int R1> struct ZcolShape {
+  typedef ZF<T, N, LB, R1> F;
   static constexpr int GT = LB * F::TH, NT = 3 * GT;
   static constexpr int LDS = (3 * F::ELEMS + 2 * N) * (int)sizeof(T);  // buffers, twiddles, 1 / s(z)
   static_assert(GT % 64 == 0 && NT <= 1024 && LDS <= 160 * 1024, "z column split");
 };
 
-template <class T, int N, int LB, bool DAMP>
-__global__ void __launch_bounds__((ZcolShape<T, N, LB>::NT)) k_diff_zcol(DiffZcolArgs a) {
-  typedef ZcolShape<T, N, LB> S;
-  typedef ZF<T, N, LB> F;
+template <class T, int N, int LB, int R1, bool DAMP>
+__global__ void __launch_bounds__((ZcolShape<T, N, LB, R1>::NT)) k_diff_zcol(DiffZcolArgs a) {
+  typedef ZcolShape<T, N, LB, R1> S;
+  typedef ZF<T, N, LB, R1> F;
   typedef typename real_of<T>::type R;
   constexpr int E = F::E, TH = F::TH;
   extern __shared__ double2 smem_d[];
@@ -390,6 +392,12 @@ __global__ void __launch_bounds__((ZcolShape<T, N, LB>::NT)) k_diff_zcol(DiffZco
 template <class T> static constexpr int zcol_lb(int n) {
   return n <= 128 ? 8 : n == 1024 && sizeof(T) == 16 ? 2 : 4;
 }
+// 16 planes per thread instead of 8 (32 x 32 x 512 FP64 damped 62.2 -> 55.4 us with 8,
+// 64 x 64 x 512 FP64 damped 229 -> 205, FP32 148 -> 127, 64 x 64 x 128 FP64 47.1 -> 45.1,
+// 32 x 32 x 256 FP32 damped 34.4 -> 32.9): only FP64 with damping at 256 planes in more
+// than 512 blocks, whose two exchanges and 97 registers then bound it
+// (64 x 64 x 256 105 us with 16, 111 with 8; 32 x 64, 512 blocks, 55.8 and 53.0).
+template <class T> static constexpr bool zcol_wide(int n) { return sizeof(T) == 16 && n == 256; }
 template <class T> static constexpr bool dplane_fits(int lx, int ly) {
   return lx >= 4 && lx <= 7 && ly >= 4 && ly <= 7 && lx + ly <= (sizeof(T) == 8 ? 13 : 12);
 }
@@ -437,10 +445,23 @@ template <class T>
 bool launch_diff_zcol(const DiffZcolArgs& a, int pe, bool damp, hipStream_t s) {
   auto go = [&](auto n) {
     constexpr int N = decltype(n)::value, LB = zcol_lb<T>(N);
-    typedef ZcolShape<T, N, LB> S;
     const int nblk = a.ny * (a.nx / LB);
-    if (damp) run(k_diff_zcol<T, N, LB, true>, nblk, S::NT, S::LDS, s, a);
-    else run(k_diff_zcol<T, N, LB, false>, nblk, S::NT, S::LDS, s, a);
+    auto one = [&](auto r) {
+      constexpr int R1 = decltype(r)::value;
+      typedef ZcolShape<T, N, LB, R1> S;
+      if (damp) run(k_diff_zcol<T, N, LB, R1, true>, nblk, S::NT, S::LDS, s, a);
+      else run(k_diff_zcol<T, N, LB, R1, false>, nblk, S::NT, S::LDS, s, a);
+    };
+    // 8 planes per thread, which gives a column twice the wavefronts of 16 and each
+    // half the chain, for one more exchange (N = 1024 has no such split). One kind
+    // is faster with 16: see zcol_wide.
+    if constexpr (zcol_wide<T>(N)) {
+      if (damp && nblk > 512) {
+        one(std::integral_constant<int, 16>());
+        return true;
+      }
+    }
+    one(std::integral_constant<int, N == 1024 ? 16 : 8>());
     return true;
   };
   switch (pe) {

@@ -68,6 +68,7 @@ CT_CASES = [
     # nx, ny, nz (absorber), pe, pml
     (16, 16, 16, 64, 8),
     (64, 32, 16, 128, 24),
+    (64, 64, 32, 256, 32),
     (16, 32, 32, 256, 32),
     (32, 16, 64, 512, 60),
     (16, 16, 32, 1024, 100),
