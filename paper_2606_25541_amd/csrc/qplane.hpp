@@ -36,11 +36,11 @@ namespace psfd {
 // Threads and values per thread of a block. FP32: 16 values on quarters of more
 // than 4096 values (256 x 256: 1024 threads), 4 at 1024 (256 threads shorten the
 // chain that bounds them: 64 x 64 x 32 apply 18.9 -> 18.0 us against 8), else 8. At
-// 4096 values 8 against 16: apply 256 x 64 x 16 28.2 -> 26.9 us, 128 x 128 x 8 22.7 ->
-// 21.3, 128 x 128 x 64 51.4 alike; with the Gram-Schmidt work a step at
-// 128 x 128 x 8 43.1 -> 41.3, at 32 planes 66.3 alike, at 64 103.7 -> 105.7: WIDE (16)
-// there, where the blocks are enough to fill the chip and the basis slots bound
-// the kernel. FP64: 8. At least one thread per column and one wavefront. No pass
+// 4096 values 8 against 16: apply 256 x 64 x 16 28.2 -> 26.9 us, 128 x 128 x 16 25.1 ->
+// 23.8, 128 x 128 x 32 36.6 -> 36.3, 128 x 128 x 64 51.9 -> 52.2, 256 x 64 x 64 52.4 ->
+// 53.3; with the Gram-Schmidt work a step at 128 x 128 x 8 43.1 -> 41.3, at 32 planes
+// 66.3 alike, at 64 103.7 -> 105.7: WIDE (16) above 32 planes, where the blocks
+// are enough to fill the chip. FP64: 8. At least one thread per column and one wavefront. No pass
 // takes a radix above the values of a thread.
 template <class T, int LNX, int LNY, bool WIDE> struct QpShape {
   static constexpr int NX = 1 << LNX, NY = 1 << LNY, ROWS = NY / 4, ELEM = ROWS * NX;
@@ -404,7 +404,7 @@ void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s) {
         if (a.nx != 1 << LX || a.ny != 1 << LY) return;
         // the 16-value split by the shape alone, so that a solve takes the same
         // arithmetic by itself, in a batch and in a server's slot
-        constexpr bool W = GS && LX + LY == 14;
+        constexpr bool W = sizeof(T) == 8 && LX + LY == 14;
         auto split = [&](auto wide) {
           constexpr bool WIDE = decltype(wide)::value;
           typedef QpShape<T, LX, LY, WIDE> S;
