@@ -163,13 +163,13 @@ void apply_op(Group& g, const T* deps, VecRef in, VecRef out, T* ws, int kmode, 
               const GivensTask* gt = nullptr);
 // one of the three launches of apply_op: 0 transverse forward, 1 z-pencil, 2 transverse inverse.
 // qp: the quarter-plane kernels and layout (all three stages of one apply alike;
-// only where quarter_planes holds and with no gt)
+// only where quarter_planes holds; a gt of stage 0 then takes a launch of its own)
 template <class T>
 void apply_stage(Group& g, int stage, const T* deps, VecRef in, VecRef out, T* ws, int kmode, int transpose,
                  int refl, const int* active, hipStream_t s, const double* in_scale = nullptr,
                  long long scale_stride = 0, const GivensTask* gt = nullptr, bool qp = false);
-// whether the operator apply of this group's shape takes the quarter-plane
-// kernels (qplane_bx; PSFD_QUARTER_PLANES=0 turns them off)
+// whether the operator applies and Arnoldi steps of this group's shape take the
+// quarter-plane kernels (qplane_bx; PSFD_QUARTER_PLANES=0 turns them off)
 bool quarter_planes(const Group& g, size_t esz);
 
 struct SolveStats {

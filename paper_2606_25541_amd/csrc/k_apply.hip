@@ -642,6 +642,9 @@ __global__ void __launch_bounds__(LPZ ? pencil_threads_ct(LPZ ? LPZ : 4, BXC) : 
   const int bx = LPZ ? BXC : a.bx, pz = LPZ ? (1 << LPZ) : a.pz, nz = pz / 2, nx = a.nx, ny = a.ny;
   static_assert(!YQ || LPZ > 0, "quarter layout: compile-time pencils");
   int bid = blockIdx.x;
+  // 8 columns are half of a 128-byte line of the layout: the two blocks that share
+  // lines run on one XCD, one after the other (128 x 128 x 128: FP32 65 -> 50 us,
+  // FP64 140 -> 108; the launch has a multiple of 16 such blocks)
   if constexpr (YQ && BXC == 8) bid = (bid & ~15) | ((bid & 7) << 1) | ((bid >> 3) & 1);
   const int ky = bid / a.nblk_x;  // YQ: the quarter-spectrum row ky'
   const int kx0 = (bid - ky * a.nblk_x) * (YQ ? BXC / 4 : bx);

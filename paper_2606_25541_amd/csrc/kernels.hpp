@@ -130,7 +130,8 @@ template <class T>
 void launch_pencil(const PencilArgs& a, int nbatch, int nthr, size_t lds, hipStream_t s);
 // Quarter-plane transverse kernels of the operator apply (planes of 16 .. 256 on
 // both sides, of 1024 and more values, whose quarter fits LDS): forward (LD_VX, ST_PLAIN) into the
-// quarter-plane layout, inverse (LD_PLAIN, ST_PLAIN or ST_AXPBY) from it;
+// quarter-plane layout, inverse (LD_PLAIN, ST_PLAIN or ST_AXPBY) from it, and
+// where qplane_gs holds LD_UPD_VX, LD_UPD_SLOT and ST_DOTS;
 // nplanes = 3 nz, no GivensTask. The pencil between them runs with PencilArgs::yq.
 template <class T, bool INV, int LD, int ST>
 void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s);

@@ -1,4 +1,4 @@
-// Quarter-plane kernels (operator apply): the transverse transform of an
+// Quarter-plane kernels (operator apply and Arnoldi steps): the transverse transform of an
 // ny x nx plane split four ways over y. Block q of a plane takes the rows
 // y = 4 r + q (r < ny / 4), transforms them along x (nx points) and along r
 // (ny / 4 points), and stores the quarter spectrum times its twiddle,
@@ -372,8 +372,8 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY, WIDE>::NT)) k_qplane(Til
 // of LDS; a 256 x 256 FP64 quarter would need twice that). Whole apply, quarter
 // planes against one block (or row and column strips) per plane, with the
 // compile-time pencils: 32 x 32 x 32 FP64 20.5 -> 16.1 us, 256 x 64 x 16 FP32
-// 46.8 -> 25.7, 64 x 128 x 16 FP32 36.6 -> 19.2, 64 x 32 x 64 FP32 24.6 -> 18.1,
-// 128 x 32 x 64 FP32 30.4 -> 22.0, 64 x 64 x 32 FP32 20.7 -> 19.2, 128 x 128 x 64
+// 46.8 -> 24.0, 64 x 128 x 16 FP32 36.6 -> 19.2, 64 x 32 x 64 FP32 24.6 -> 18.1,
+// 128 x 32 x 64 FP32 30.4 -> 22.0, 64 x 64 x 32 FP32 20.7 -> 17.7, 128 x 128 x 64
 // FP64 137 -> 105, 256 x 256 x 64 FP32 243 -> 221.
 constexpr bool qplane_fits(int lnx, int lny, size_t esz) {
   return lnx >= 4 && lnx <= 8 && lny >= 4 && lny <= 8 && lnx + lny >= 10 && lnx + lny - 2 <= (esz == 8 ? 14 : 13);
