@@ -234,7 +234,7 @@ def sec_apply(ctx, args, out):
     # as well, (j + 3) 3N, and no separate projection pass runs
     # The forward stage of step j + 1 (pass 3) reads the slot, the contrast and writes the workspace,
     # 7N; where it also does the update of column j (FP32 128 x 128 planes, lock-step solves) it reads
-    # v_0..v_j too and writes the slot back, (j + 3) 3N + 7N
+    # v_0..v_j too and writes the slot back, (j + 2) 3N + 7N
     m = args.restart
     sq128 = prob.nx == prob.ny == 128
     fused = sq128 and 3 * prob.nz <= 256 and os.environ.get("PSFD_FUSE_DOTS", "1") != "0"
@@ -243,7 +243,7 @@ def sec_apply(ctx, args, out):
     gs = {}
     for pname, pas, nvec in (("projections", 0, lambda j: j + 2), ("update", 1, lambda j: j + 3),
                              ("stage 2 step", 2, lambda j: j + 3 if fused else 2),
-                             ("stage 0 step", 3, lambda j: (j + 3 if fused_upd else 0) + 7 / 3)):
+                             ("stage 0 step", 3, lambda j: (j + 2 if fused_upd else 0) + 7 / 3)):
         us, byt = [], []
         for j in range(m):
             ms = C.c_float()
@@ -266,7 +266,7 @@ def sec_apply(ctx, args, out):
     if fused_upd:
         g0 = gs["stage 0 step"]
         us0 = [st32[0]["us"]] + g0["us_per_column"][:m - 1]
-        by0 = [st32[0]["bytes"]] + [(j + 3) * 3 * N * 8 + 7 * N * 8 for j in range(m - 1)]
+        by0 = [st32[0]["bytes"]] + [(j + 2) * 3 * N * 8 + 7 * N * 8 for j in range(m - 1)]
         cand["stage 0 + update"] = (
             "k_qplane<float2,fwd,update+V*x> (Gram-Schmidt update of the previous column + transverse FFT "
             "forward; plain at step 0; mean over the steps of a cycle)", sum(us0) / m, sum(by0) / m)
@@ -337,13 +337,13 @@ def sec_isolated(ctx, args, out):
     reps = 20 if args.only == "isolated" else 100
     # algorithmic bytes per voxel in complex values (esz bytes each): x rows read x (3) and
     # delta_eps (1), write half the padded rows (6); y columns read 6, write 12; the z pencils read
-    # and write 12 and read the 6-entry table of the padded grid for kz = 0 .. nz (the table is even
-    # or odd in kz: 24 (nz + 1) / nz); inverse y columns read 12, write 6; inverse x rows read 6 and
-    # x (3), write y (3)
-    per_vox = {0: 10, 1: 18, 2: 24 + 24 * (nz + 1) / nz, 3: 18, 4: 12}
-    names = {0: "k_iso_lines<fwd, x rows * V>", 1: "k_iso_lines<fwd, y columns>",
-             2: "k_iso_zmul (z FFT, 3x3 table product, inverse z FFT)", 3: "k_iso_lines<inv, y columns>",
-             4: "k_iso_lines<inv, x rows, y = x - w>"}
+    # and write 12 and read the 6-entry table once, of which the octant kx = 0 .. nx, ky = 0 .. ny,
+    # kz = 0 .. nz is kept (the table is even or odd on each axis); inverse y columns read 12, write
+    # 6; inverse x rows read 6 and x (3), write y (3)
+    per_vox = {0: 10, 1: 18, 2: 24 + 6 * (nx + 1) * (ny + 1) * (nz + 1) / N, 3: 18, 4: 12}
+    names = {0: "k_iso_line<fwd, x rows * V>", 1: "k_iso_line<fwd, y columns>",
+             2: "z pass (z FFT, 3x3 table product, inverse z FFT)", 3: "k_iso_line<inv, y columns>",
+             4: "k_iso_line<inv, x rows, y = x - w>"}
     res = {"grid": [nx, ny, nz], "spacing_nm": list(spacing), "radius_nm": R, "oversampling_zyx": list(over),
            "precompute_ms": 1e3 * t_pre}
     for name, dt_, esz in (("fp32", torch.complex64, 8), ("fp64", torch.complex128, 16)):
