@@ -723,6 +723,17 @@ static int dot_partials(const Group& g, size_t esz) {
   return fuse_update(g, esz) ? 12 * g.sh.nz : esz == 8 ? DotBlocks<float2>::value : DotBlocks<double2>::value;
 }
 
+// Whether the quarter-plane kernels read the basis slots nontemporally: where the
+// basis of all instances of a lock-step group exceeds the 256 MB Infinity Cache, a
+// slot is gone before its next reader and caching it only drives out what the
+// next kernel reads. Step of GMRES(8) with and without: 4 x 128 x 128 x 64 (905 MB)
+// 373 against 421 us, 32 x 64 x 64 x 32 (905 MB) 421 against 463; but of bases that fit
+// 128 x 128 x 64 (226 MB) 109.8 against 102.7, 8 x 64 x 64 x 32 (226 MB) 121 against 111.
+// A server's group runs with any number of its slots idle and keeps the caches.
+static bool stream_basis(const Group& g, size_t esz, bool lock) {
+  return lock && (double)g.B * (g.m + 1) * g.sh.n3 * esz > 256.0 * (1 << 20);
+}
+
 // The inverse transverse stage of an Arnoldi step: the slot vout (j + 1) =
 // IFFT_xy of the workspace. Returns true when the kernel also stored the
 // projection partials of the new vector (fuse_dots), false when the separate
@@ -736,7 +747,8 @@ static bool arnoldi_inverse(Group& g, VecRef vout, int jh, hipStream_t s, bool q
       const XYCfg c = xy_config(g.sh, sizeof(T));
       TileArgs a = tile_base(g, twiddles<T>(g), c.full);
       a.in = vr(ws, n3); a.out = vout; a.active = g.run;
-      a.dt = DotTask{g.basis, n3, bsv, g.st, g.dpart2, jh, dot_partials(g, sizeof(T))};
+      a.dt = DotTask{g.basis, n3, bsv, g.st, g.dpart2, jh, dot_partials(g, sizeof(T)),
+                     stream_basis(g, sizeof(T), jh >= 0)};
       if (qp) launch_qplane<T, true, LD_PLAIN, ST_DOTS>(a, 3 * g.sh.nz, g.B, s);
       else launch_tile<T, true, LD_PLAIN, ST_DOTS>(a, 3 * g.sh.nz, g.B, c.full.nthr, c.full.lds, s);
       return true;
@@ -781,7 +793,8 @@ static Status bench_gs_t(Group& g, int pass, int j, const T* x, int reps, float*
       const XYCfg c = xy_config(g.sh, sizeof(T));
       fa = tile_base(g, twiddles<T>(g), c.full);
       fa.in = vout; fa.vol = vr(deps_of_mut<T>(g), g.sh.N); fa.out = vr(g.wsP, n3); fa.active = g.run;
-      fa.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, j + 1, DotBlocks<T>::value};
+      fa.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, j + 1, DotBlocks<T>::value,
+                         stream_basis(g, sizeof(T), true)};
     }
   }
   auto run_pass = [&]() {
@@ -861,7 +874,7 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
     // the projections, so that a slot computes exactly what a lone solve does
     TileArgs a = tile_base(g, twiddles<T>(g), xy_config(g.sh, sizeof(T)).full);
     a.in = vin; a.vol = vr(deps_of<T>(g), g.sh.N); a.out = vr((T*)g.wsP, n3); a.active = g.run;
-    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, -1, nblk};
+    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, -1, nblk, 0};
     if constexpr (std::is_same<T, float2>::value) launch_qplane<T, false, LD_UPD_SLOT, ST_PLAIN>(a, 3 * g.sh.nz, g.B, s);
     const GivensTask gp{g.st, g.run, g.part, nq, 1};
     apply_stage<T>(g, 1, deps_of<T>(g), vin, vout, (T*)g.wsP, 1, transpose, refl, g.run, s, nullptr, 0, &gp, qp);
@@ -875,7 +888,8 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
     // blocks and runs the Givens step of column jh - 1 in one extra block
     TileArgs a = tile_base(g, twiddles<T>(g), xy_config(g.sh, sizeof(T)).full);
     a.in = vin; a.vol = vr(deps_of<T>(g), g.sh.N); a.out = vr((T*)g.wsP, n3); a.active = g.run;
-    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, jh, nblk};
+    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, jh, nblk,
+                      stream_basis(g, sizeof(T), true)};
     // at step 0 the per-slot kernel loads slot 0 scaled (no update, as the
     // server's first step does), and no Givens step is pending
     if constexpr (std::is_same<T, float2>::value) {

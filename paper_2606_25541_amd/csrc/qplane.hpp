@@ -68,22 +68,28 @@ template <int NX> PSFD_D int qp_index(int kyq, int kx, int q) { return kyq * (4 
 // forward 36.4 -> 31.3 us, inverse 31.5 -> 28.0; 64 x 64 x 32 10.6 -> 9.4 and 9.9 ->
 // 8.0. Whole Arnoldi step: 128 x 128 x 64 112.7 -> 103.1 us, 128 x 128 x 16 72 -> 54,
 // 64 x 64 x 32 36.5 -> 31.7; shapes that ran separate projection and update passes:
-// 64 x 128 x 32 72.6 -> 40.9, 256 x 64 x 32 101 -> 64, 256 x 256 x 64 508 -> 452.
+// 64 x 128 x 32 72.6 -> 40.9, 256 x 64 x 32 101 -> 64, 256 x 256 x 64 509 -> 407.
 //
 // The slots are read in groups of G whose loads are issued together (slots past
 // the last are empty buffers, which load nothing). Two of 4 values per thread,
 // else one: more in flight costs registers, and with them resident blocks, which
 // hide the chains better (64 x 64 x 32, groups of 8 / 4 / 2 / 1: 33.9 / 32.7 / 31.7 /
 // 31.6 us a step, eight instances 119.6 / 114.5 / 110.6 / 111.8).
+// With nt the slots are read past the caches: see stream_basis.
 template <class S> constexpr int qp_group() { return S::KT == 4 ? 2 : 1; }
 
 template <class S, class T, int KT, int G>
-PSFD_D void qp_slots(const T* V, long long ldv, int i0, int cnt, unsigned lane, T (&p)[G][KT]) {
+PSFD_D void qp_slots(const T* V, long long ldv, bool nt, int i0, int cnt, unsigned lane, T (&p)[G][KT]) {
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     const LaneBuf s(V + (long long)min(i0 + g, cnt - 1) * ldv, i0 + g < cnt ? S::NX * S::NY * (int)sizeof(T) : 0);
+    if (nt) {
 #pragma unroll
-    for (int k = 0; k < KT; ++k) s.load(p[g][k], lane, k * 4 * S::NT * (int)sizeof(T));
+      for (int k = 0; k < KT; ++k) s.load_nt(p[g][k], lane, k * 4 * S::NT * (int)sizeof(T));
+    } else {
+#pragma unroll
+      for (int k = 0; k < KT; ++k) s.load(p[g][k], lane, k * 4 * S::NT * (int)sizeof(T));
+    }
   }
 }
 
@@ -106,7 +112,7 @@ PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& sl
   const T* sb = reinterpret_cast<const T*>(u.V) + (long long)b * u.bsv + poff;
   const double2* pb = u.dpart + (long long)b * PSTR * u.nblk;
   T p[G][KT];
-  qp_slots<S>(sb, u.ldv, 0, cnt, lane, p);
+  qp_slots<S>(sb, u.ldv, u.nt, 0, cnt, lane, p);
   for (int i = wave; i <= cnt; i += NW) {
     const double sc = St.sc[i];
     const double2 t = dots_total(pb + (long long)i * u.nblk, u.nblk);
@@ -121,7 +127,7 @@ PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& sl
   }
   __syncthreads();
   for (int i0 = 0; i0 < cnt; i0 += G) {
-    if (i0 > 0) qp_slots<S>(sb, u.ldv, i0, cnt, lane, p);
+    if (i0 > 0) qp_slots<S>(sb, u.ldv, u.nt, i0, cnt, lane, p);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       if (i0 + g < cnt) {
@@ -167,7 +173,7 @@ PSFD_D void qp_dots(const TileArgs& a, int cnt, const T (&wv)[KT], T (&p)[G][KT]
   const int tid = threadIdx.x, wave = tid >> 6;
   __syncthreads();
   for (int i0 = 0; i0 < cnt; i0 += G) {
-    if (i0 > 0) qp_slots<S>(sb, d.ldv, i0, cnt, lane, p);
+    if (i0 > 0) qp_slots<S>(sb, d.ldv, d.nt, i0, cnt, lane, p);
     // all G sums side by side (zeros for the slots past the last)
     T acc[G];
 #pragma unroll
@@ -315,7 +321,7 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY, WIDE>::NT)) k_qplane(Til
     sb = reinterpret_cast<const T*>(a.dt.V) + (long long)b * a.dt.bsv + poff;
     cnt = a.dt.jh + 1;
     if (a.dt.jh < 0) cnt = __builtin_amdgcn_readfirstlane(a.dt.st[b].j) + 1;
-    qp_slots<S>(sb, a.dt.ldv, 0, cnt, lane, p);
+    qp_slots<S>(sb, a.dt.ldv, a.dt.nt, 0, cnt, lane, p);
   }
   const double* tab = a.tab + (long long)b * a.tab_stride;
   R ks = (R)1;

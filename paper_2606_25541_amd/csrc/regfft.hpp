@@ -20,6 +20,11 @@ struct LaneBuf {
     const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, lane, uni, 0);
     x = make_float2(__uint_as_float(u[0]), __uint_as_float(u[1]));
   }
+  // nontemporal: the line is not kept for a later reader
+  PSFD_D void load_nt(float2& x, unsigned lane, unsigned uni) const {
+    const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, lane, uni, 2);
+    x = make_float2(__uint_as_float(u[0]), __uint_as_float(u[1]));
+  }
   PSFD_D void load(double2& x, unsigned lane, unsigned uni) const {
     const auto u = __builtin_amdgcn_raw_buffer_load_b128(r, lane, uni, 0);
     x.x = __hiloint2double((int)u[1], (int)u[0]);
