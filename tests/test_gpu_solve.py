@@ -196,6 +196,29 @@ def test_gram_schmidt_in_quarter_planes_matches_separate_passes(shape, monkeypat
     assert rel(e1.cpu().numpy(), e2.cpu().numpy()) < 1e-7
 
 
+def test_batch_beyond_the_infinity_cache_matches_alone():
+    """Ten 64 x 64 x 32 mixed instances in lock-step (basis 9 x 3.1 MB each, 283 MB in
+    all: the slots are read nontemporally) against a lone solve (28 MB: through the
+    caches): the loads differ, the arithmetic does not, so fields and step counts
+    are bitwise the same."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    layers, es = clips.mo_si_stack(40)
+    p = clips.Problem(nx=64, ny=64, nz=32, lx_nm=128.0, ly_nm=128.0, t_nm=60.0, theta_deg=6.0,
+                      phi_deg=15.0, pol=1, layers=layers, eps_sub=es)
+    ds = [torch.from_numpy(clips.contact_holes(64, 64, 32, 128.0, 128.0, 6, seed=200 + i)).to(dev) for i in range(10)]
+    opts = dict(rtol=1e-8, precision="mixed", restart=8)
+    say("solve 10 x 64x64x32 mixed, batch vs alone")
+    em, od, infos = api.psfd_solve_batch([p] * 10, ds, **opts)
+    plan = api.Plan(p, **opts)
+    for i in (0, 9):
+        e, o, info = plan.psfd_solve(ds[i])
+        say("  instance", i, infos[i]["iters"], info["iters"])
+        assert info["status"] == 0 and infos[i]["status"] == 0
+        assert infos[i]["iters"] == info["iters"]
+        assert torch.equal(em[i], e) and torch.equal(od[i], o)
+
+
 def test_fp64_solve_quarter_planes_match_strips(monkeypatch):
     """128 x 128 x 32, FP64, lock-step: the Arnoldi steps and b - A x on quarter
     planes (four blocks per plane, the radix-4 y combine in the pencil) against
