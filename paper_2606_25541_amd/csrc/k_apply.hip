@@ -663,7 +663,7 @@ __global__ void __launch_bounds__(LPZ ? pencil_threads_ct(LPZ ? LPZ : 4, BXC) : 
   constexpr bool CT = LPZ > 0;
   constexpr int ZSTEP = CT ? pencil_threads_ct(LPZ, BXC) / (3 * BXC) : 1;
   constexpr int VT = CT ? (1 << LPZ) / 2 / ZSTEP : 4;  // values per thread (data half)
-  static_assert(!CT || ((BXC == 16 || BXC == 8) && pencil_threads_ct(LPZ, BXC) == ZSTEP * 3 * BXC &&
+  static_assert(!CT || ((BXC == 16 || (BXC == 8 && LPZ == 8)) && pencil_threads_ct(LPZ, BXC) == ZSTEP * 3 * BXC &&
                         VT * ZSTEP * 2 == (1 << LPZ) && (VT == 4 || VT == 2)),
                 "pencil thread split");
   const int ck = tid & (bx - 1);
@@ -974,7 +974,6 @@ void launch_pencil(const PencilArgs& a, int nbatch, int nthr, size_t lds, hipStr
     if (is(6, 16)) return go(k_pencil<T, 6, 16, true>);
     if (is(7, 16)) return go(k_pencil<T, 7, 16, true>);
     if (is(8, 8)) return go(k_pencil<T, 8, 8, true>);
-    if (is(7, 8)) return go(k_pencil<T, 7, 8, true>);
     std::fprintf(stderr, "psfd: internal error: quarter-plane pencil on an unsupported shape\n");
     std::abort();
   }
