@@ -242,6 +242,22 @@ int psfd_bench_stage(psfd_plan* plan, int stage, const void* d_deps, const void*
 int psfd_bench_gram_schmidt(psfd_plan* plan, int pass, int j, const void* d_x, int dtype, int reps, float* ms,
                             void* stream);
 
+/* Diagnostics: which kernels a GMRES step (Saad & Schultz; Sec. 3) of a grid runs
+ * at the library's present environment switches. No device is needed. */
+typedef struct {
+  int32_t quarter_planes;    /* transverse transforms split four ways over y */
+  int32_t dots_in_inverse;   /* the inverse transverse kernel also forms the projections */
+  int32_t update_in_forward; /* the forward one also does the previous column's update (lock-step
+                                solves: at steps >= 1; the last column of a cycle takes none) */
+  int32_t partials;          /* partial sums per projection */
+  int32_t cached_instances;  /* quarter planes read the basis through the caches while at most this
+                                many instances of a lock-step group run, past them beyond */
+} psfd_step_kernels;
+/* nx, ny, nz powers of two as in psfd_problem; precision PSFD_FP64 or PSFD_MIXED
+ * (the FP32 inner steps); step >= 0 within a restart cycle of a lock-step solve,
+ * or -1 for a server's slots. Errors: INVALID_ARG, UNSUPPORTED_SIZE. */
+int psfd_step_info(int32_t nx, int32_t ny, int32_t nz, int precision, int step, psfd_step_kernels* out);
+
 /* ------------------------------------------------------------------------
  * Isolated-domain mode: a scatterer in free space (no periodicity, no
  * multilayer), with the dyadic Green's function truncated to a ball of radius R

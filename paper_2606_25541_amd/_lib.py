@@ -53,6 +53,11 @@ class psfd_info(C.Structure):
         return {k: getattr(self, k) for k, _ in self._fields_}
 
 
+class psfd_step_kernels(C.Structure):
+    _fields_ = [("quarter_planes", C.c_int32), ("dots_in_inverse", C.c_int32), ("update_in_forward", C.c_int32),
+                ("partials", C.c_int32), ("cached_instances", C.c_int32)]
+
+
 class psfd_iso_problem(C.Structure):
     _fields_ = [("nx", C.c_int32), ("ny", C.c_int32), ("nz", C.c_int32),
                 ("dx_nm", C.c_double), ("dy_nm", C.c_double), ("dz_nm", C.c_double),
@@ -94,6 +99,7 @@ EXPORTS = {
                                    C.POINTER(C.c_float), C.c_void_p]),
     "psfd_bench_gram_schmidt": (C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_int,
                                           C.POINTER(C.c_float), C.c_void_p]),
+    "psfd_step_info": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int, C.c_int, C.POINTER(psfd_step_kernels)]),
     "psfd_iso_plan_create": (C.c_int, [C.POINTER(psfd_iso_problem), C.POINTER(C.c_void_p)]),
     "psfd_iso_plan_destroy": (None, [C.c_void_p]),
     "psfd_iso_apply": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_void_p]),

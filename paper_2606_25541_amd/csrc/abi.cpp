@@ -215,6 +215,24 @@ int psfd_bench_gram_schmidt(psfd_plan* plan, int pass, int j, const void* d_x, i
   return PSFD_OK;
 }
 
+int psfd_step_info(int32_t nx, int32_t ny, int32_t nz, int precision, int step, psfd_step_kernels* out) {
+  if (!out || step < -1 || (precision != PSFD_FP64 && precision != PSFD_MIXED))
+    return fail(PSFD_ERR_INVALID_ARG, "bad arguments");
+  psfd_problem p{};
+  p.nx = nx; p.ny = ny; p.nz = nz;
+  p.lx_nm = p.ly_nm = p.t_nm = p.wavelength_nm = p.eps_bg = 1.0;
+  Problem pr;
+  Status st = validate_problem(&p, pr);
+  if (!st.ok()) return fail(st);
+  const StepKernels k = step_kernels(shape_of(p), precision == PSFD_FP64 ? 16 : 8, step);
+  out->quarter_planes = k.quarter;
+  out->dots_in_inverse = k.dots;
+  out->update_in_forward = k.update;
+  out->partials = k.partials;
+  out->cached_instances = k.cached;
+  return PSFD_OK;
+}
+
 static void fill_info(psfd_info* info, const SolveStats& s) {
   if (!info) return;
   info->iters = s.iters;

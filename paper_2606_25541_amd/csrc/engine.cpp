@@ -5,6 +5,7 @@
 #include <deque>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <complex>
 #include <cstdio>
@@ -405,25 +406,30 @@ template <class T> static const T* twiddles(const Group& g);
 template <> const float2* twiddles<float2>(const Group& g) { return g.dc->tw32; }
 template <> const double2* twiddles<double2>(const Group& g) { return g.dc->tw64; }
 
-static TileArgs tile_base(const Group& g, const void* tw, const TileShape& t) {
+static TileArgs tile_shape(const Shape& sh, const TileShape& t) {
   TileArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.nx = g.sh.nx; a.ny = g.sh.ny; a.nz = g.sh.nz;
-  a.log2nx = ilog2i(g.sh.nx); a.log2ny = ilog2i(g.sh.ny);
+  a.nx = sh.nx; a.ny = sh.ny; a.nz = sh.nz;
+  a.log2nx = ilog2i(sh.nx); a.log2ny = ilog2i(sh.ny);
   a.tx = t.tx; a.ty = t.ty; a.pitch = t.pitch;
-  a.tiles_x = g.sh.nx / t.tx; a.tiles_y = g.sh.ny / t.ty;
+  a.tiles_x = sh.nx / t.tx; a.tiles_y = sh.ny / t.ty;
   a.do_x = t.do_x; a.do_y = t.do_y;
+  return a;
+}
+
+static TileArgs tile_base(const Group& g, const void* tw, const TileShape& t) {
+  TileArgs a = tile_shape(g.sh, t);
   a.tab = g.tab; a.tab_stride = g.tab_stride;
   a.tw = tw;
   a.alpha = 0; a.gamma = 1;
   return a;
 }
 
-bool quarter_planes(const Group& g, size_t esz) {
-  const Shape& sh = g.sh;
+static bool quarter_planes(const Shape& sh, size_t esz) {
   if ((esz != 8 && esz != 16) || env_int("PSFD_QUARTER_PLANES", 1) == 0) return false;
   return qplane_bx(sh.nx, sh.ny, sh.nz, esz) != 0;
 }
+bool quarter_planes(const Group& g, size_t esz) { return quarter_planes(g.sh, esz); }
 
 // the quarter-layout pencil blocks of a shape that takes them
 static ZCfg zq_config(const Shape& sh, size_t esz) {
@@ -696,10 +702,9 @@ template <> double2* deps_of_mut<double2>(Group& g) { return g.deps64; }
 // task (at least GIVENS_THREADS threads, i.e. padded z lengths of 64 and more).
 // PSFD_FUSE_UPDATE=0 keeps the separate update pass; so does PSFD_FUSE_DOTS=0
 // (read per call).
-static bool fuse_update(const Group& g, size_t esz) {
-  const Shape& sh = g.sh;
+static bool fuse_update(const Shape& sh, size_t esz) {
   if (env_int("PSFD_FUSE_DOTS", 1) == 0 || env_int("PSFD_FUSE_UPDATE", 1) == 0) return false;
-  return quarter_planes(g, esz) && qplane_gs(sh.nx, sh.ny, sh.nz, esz) && zq_config(sh, esz).nthr >= GIVENS_THREADS;
+  return quarter_planes(sh, esz) && qplane_gs(sh.nx, sh.ny, sh.nz, esz) && zq_config(sh, esz).nthr >= GIVENS_THREADS;
 }
 
 // Whether the inverse transverse kernel of an Arnoldi step also forms the
@@ -708,30 +713,49 @@ static bool fuse_update(const Group& g, size_t esz) {
 // the separate update pass, and without quarter planes (fewer than 8 z planes)
 // the FP32 64 x 64 and 128 x 128 square planes. PSFD_FUSE_DOTS=0 keeps the
 // separate projection pass (read per call).
-static bool fuse_dots(const Group& g, size_t esz) {
-  const Shape& sh = g.sh;
+static bool fuse_dots(const Shape& sh, size_t esz) {
   if (env_int("PSFD_FUSE_DOTS", 1) == 0) return false;
-  if (quarter_planes(g, esz))
-    return qplane_gs(sh.nx, sh.ny, sh.nz, esz) && (12 * sh.nz <= DotBlocks<float2>::value || fuse_update(g, esz));
+  if (quarter_planes(sh, esz))
+    return qplane_gs(sh.nx, sh.ny, sh.nz, esz) && (12 * sh.nz <= DotBlocks<float2>::value || fuse_update(sh, esz));
   const XYCfg c = xy_config(sh, esz);
-  return c.fused && tile_takes_dots(tile_base(g, nullptr, c.full), esz);
+  return c.fused && tile_takes_dots(tile_shape(sh, c.full), esz);
 }
 
 // projection partials per value of an Arnoldi step: one per quarter-plane block
 // where the fused update sums them, else those of the projection pass
-static int dot_partials(const Group& g, size_t esz) {
-  return fuse_update(g, esz) ? 12 * g.sh.nz : esz == 8 ? DotBlocks<float2>::value : DotBlocks<double2>::value;
+static int dot_partials(const Shape& sh, size_t esz) {
+  return fuse_update(sh, esz) ? 12 * sh.nz : esz == 8 ? DotBlocks<float2>::value : DotBlocks<double2>::value;
 }
 
-// Whether the quarter-plane kernels read the basis slots nontemporally: where the
-// basis of all instances of a lock-step group exceeds the 256 MB Infinity Cache, a
-// slot is gone before its next reader and caching it only drives out what the
-// next kernel reads. Step of GMRES(8) with and without: 4 x 128 x 128 x 64 (905 MB)
-// 373 against 421 us, 32 x 64 x 64 x 32 (905 MB) 421 against 463; but of bases that fit
-// 128 x 128 x 64 (226 MB) 109.8 against 102.7, 8 x 64 x 64 x 32 (226 MB) 121 against 111.
-// A server's group runs with any number of its slots idle and keeps the caches.
-static bool stream_basis(const Group& g, size_t esz, bool lock) {
-  return lock && (double)g.B * (g.m + 1) * g.sh.n3 * esz > 256.0 * (1 << 20);
+// The largest number of running instances whose basis slots the quarter-plane
+// kernels of lock-step step jh read through the caches. The step works on slots
+// 0 .. jh + 1 and a workspace of their size per instance; where those of all
+// running instances exceed the 256 MB Infinity Cache, a slot is gone before its
+// next reader and caching it only drives out what the next kernel reads. us a
+// step, always through the caches / past them by the whole basis / by this rule:
+// 10 x 64 x 64 x 32 GMRES(8) (283 MB) 152.9 / 162.4 / 154.6, 128 x 128 x 32 GMRES(30)
+// (390 MB) 120.0 / 125.1 / 120.1, 128 x 128 x 64 GMRES(16) (428 MB) 137.0 / 136.0 / 134.2,
+// GMRES(30) (780 MB) 207.8 / 195.6 / 195.1, 8 x 64 x 64 x 32 GMRES(30) (780 MB) 225.5 /
+// 225.1 / 218.8, 4 x 128 x 128 x 64 GMRES(8) (905 MB) 442 / 396 / 398, 32 x 64 x 64 x 32
+// GMRES(8) (905 MB) 512 / 475 / 473. The kernels count the instances themselves
+// (their flags), since a batch's instances converge at different steps.
+// A server's slots stand at different steps; its groups keep the caches.
+static int cached_instances(const Shape& sh, size_t esz, int jh) {
+  if (jh < 0) return INT_MAX;
+  return (int)(256.0 * (1 << 20) / ((double)(jh + 3) * sh.n3 * esz));
+}
+
+// how the kernels of a launch of B instances decide (UpdateTask::nt)
+static int slots_nt(int B, int cached) { return B <= cached ? 0 : cached < 1 ? 1 : 2; }
+
+StepKernels step_kernels(const Shape& sh, size_t esz, int jh) {
+  StepKernels k;
+  k.quarter = quarter_planes(sh, esz);
+  k.dots = esz == 8 && fuse_dots(sh, esz);
+  k.update = esz == 8 && fuse_update(sh, esz);
+  k.partials = dot_partials(sh, esz);
+  k.cached = k.quarter && k.dots ? cached_instances(sh, esz, jh) : INT_MAX;
+  return k;
 }
 
 // The inverse transverse stage of an Arnoldi step: the slot vout (j + 1) =
@@ -742,13 +766,13 @@ template <class T>
 static bool arnoldi_inverse(Group& g, VecRef vout, int jh, hipStream_t s, bool qp) {
   T* ws = (T*)g.wsP;
   if constexpr (std::is_same<T, float2>::value) {
-    if (fuse_dots(g, sizeof(T))) {
+    if (fuse_dots(g.sh, sizeof(T))) {
       const long long n3 = g.sh.n3, bsv = (long long)(g.m + 1) * n3;
       const XYCfg c = xy_config(g.sh, sizeof(T));
       TileArgs a = tile_base(g, twiddles<T>(g), c.full);
       a.in = vr(ws, n3); a.out = vout; a.active = g.run;
-      a.dt = DotTask{g.basis, n3, bsv, g.st, g.dpart2, jh, dot_partials(g, sizeof(T)),
-                     stream_basis(g, sizeof(T), jh >= 0)};
+      const int cached = cached_instances(g.sh, sizeof(T), jh);
+      a.dt = DotTask{g.basis, n3, bsv, g.st, g.dpart2, jh, dot_partials(g.sh, sizeof(T)), slots_nt(g.B, cached), cached};
       if (qp) launch_qplane<T, true, LD_PLAIN, ST_DOTS>(a, 3 * g.sh.nz, g.B, s);
       else launch_tile<T, true, LD_PLAIN, ST_DOTS>(a, 3 * g.sh.nz, g.B, c.full.nthr, c.full.lds, s);
       return true;
@@ -788,13 +812,13 @@ static Status bench_gs_t(Group& g, int pass, int j, const T* x, int reps, float*
   std::memset(&fa, 0, sizeof(fa));
   if (pass == 3) {
     HIPCHK(hipMemcpyAsync(deps_of_mut<T>(g), x, sizeof(T) * g.sh.N, hipMemcpyDeviceToDevice, s));
-    if constexpr (std::is_same<T, float2>::value) fwd_upd = fuse_update(g, sizeof(T));
+    if constexpr (std::is_same<T, float2>::value) fwd_upd = fuse_update(g.sh, sizeof(T));
     if (fwd_upd) {
       const XYCfg c = xy_config(g.sh, sizeof(T));
       fa = tile_base(g, twiddles<T>(g), c.full);
       fa.in = vout; fa.vol = vr(deps_of_mut<T>(g), g.sh.N); fa.out = vr(g.wsP, n3); fa.active = g.run;
-      fa.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, j + 1, DotBlocks<T>::value,
-                         stream_basis(g, sizeof(T), true)};
+      const int cached = cached_instances(g.sh, sizeof(T), j + 1);
+      fa.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, j + 1, DotBlocks<T>::value, slots_nt(g.B, cached), cached};
     }
   }
   auto run_pass = [&]() {
@@ -861,11 +885,11 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
   const long long iss = (long long)(sizeof(GState) / sizeof(double));
   // the quarter-plane kernels and layout where the shape takes them
   const bool qp = quarter_planes(g, sizeof(T));
-  const int nblk = dot_partials(g, sizeof(T)), nq = 12 * g.sh.nz;
+  const int nblk = dot_partials(g.sh, sizeof(T)), nq = 12 * g.sh.nz;
   bool upd = false, upd_slots = false;
   if constexpr (std::is_same<T, float2>::value) {
-    upd = lock && fuse_update(g, sizeof(T));
-    upd_slots = !lock && fuse_update(g, sizeof(T));
+    upd = lock && fuse_update(g.sh, sizeof(T));
+    upd_slots = !lock && fuse_update(g.sh, sizeof(T));
   }
   if (upd_slots) {
     // instances at different steps (server slots): the same fused kernels, each
@@ -874,7 +898,7 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
     // the projections, so that a slot computes exactly what a lone solve does
     TileArgs a = tile_base(g, twiddles<T>(g), xy_config(g.sh, sizeof(T)).full);
     a.in = vin; a.vol = vr(deps_of<T>(g), g.sh.N); a.out = vr((T*)g.wsP, n3); a.active = g.run;
-    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, -1, nblk, 0};
+    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, -1, nblk, 0, 0};
     if constexpr (std::is_same<T, float2>::value) launch_qplane<T, false, LD_UPD_SLOT, ST_PLAIN>(a, 3 * g.sh.nz, g.B, s);
     const GivensTask gp{g.st, g.run, g.part, nq, 1};
     apply_stage<T>(g, 1, deps_of<T>(g), vin, vout, (T*)g.wsP, 1, transpose, refl, g.run, s, nullptr, 0, &gp, qp);
@@ -888,8 +912,8 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
     // blocks and runs the Givens step of column jh - 1 in one extra block
     TileArgs a = tile_base(g, twiddles<T>(g), xy_config(g.sh, sizeof(T)).full);
     a.in = vin; a.vol = vr(deps_of<T>(g), g.sh.N); a.out = vr((T*)g.wsP, n3); a.active = g.run;
-    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, jh, nblk,
-                      stream_basis(g, sizeof(T), true)};
+    const int cached = cached_instances(g.sh, sizeof(T), jh);
+    a.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, jh, nblk, slots_nt(g.B, cached), cached};
     // at step 0 the per-slot kernel loads slot 0 scaled (no update, as the
     // server's first step does), and no Givens step is pending
     if constexpr (std::is_same<T, float2>::value) {

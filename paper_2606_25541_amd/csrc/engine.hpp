@@ -171,6 +171,14 @@ void apply_stage(Group& g, int stage, const T* deps, VecRef in, VecRef out, T* w
 // whether the operator applies and Arnoldi steps of this group's shape take the
 // quarter-plane kernels (qplane_bx; PSFD_QUARTER_PLANES=0 turns them off)
 bool quarter_planes(const Group& g, size_t esz);
+// the kernels an Arnoldi step of this shape runs (jh: the lock-step step, < 0 for
+// a server's slots), from the shape and the environment's switches alone
+struct StepKernels {
+  bool quarter, dots, update;  // quarter planes; Gram-Schmidt work in their kernels
+  int partials;                // projection partials per value
+  int cached;                  // instances running at most for slots through the caches
+};
+StepKernels step_kernels(const Shape& sh, size_t esz, int jh);
 
 struct SolveStats {
   int iters = 0, outer = 0, cycles = 0, status = PSFD_OK;

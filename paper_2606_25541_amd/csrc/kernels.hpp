@@ -40,7 +40,8 @@ struct UpdateTask {
   double2* part;
   int j;
   int nblk;             // partials per value in dpart
-  int nt;               // read the slots nontemporally
+  int nt;               // read the slots past the caches: 0 no, 1 yes, 2 while more than `cached`
+  int cached;           // instances run
 };
 // The Gram-Schmidt projections of the new Arnoldi vector, left to the kernel
 // that writes it (ST_DOTS, inverse quarter planes or square planes): each block
@@ -55,7 +56,7 @@ struct DotTask {
   double2* part;
   int jh;               // >= 0: every running instance stands at step jh
   int nblk;             // partials per value in part
-  int nt;               // read the slots nontemporally (quarter planes)
+  int nt, cached;       // as in UpdateTask (quarter planes)
 };
 enum StoreOp { ST_PLAIN = 0, ST_AXPBY = 1, ST_DOTS = 2 };
 

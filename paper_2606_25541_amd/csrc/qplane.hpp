@@ -75,7 +75,8 @@ template <int NX> PSFD_D int qp_index(int kyq, int kx, int q) { return kyq * (4 
 // else one: more in flight costs registers, and with them resident blocks, which
 // hide the chains better (64 x 64 x 32, groups of 8 / 4 / 2 / 1: 33.9 / 32.7 / 31.7 /
 // 31.6 us a step, eight instances 119.6 / 114.5 / 110.6 / 111.8).
-// With nt the slots are read past the caches: see stream_basis.
+// With nt the slots are read past the caches: where the slots of the instances
+// that run exceed them (qp_past_caches; the limit is the launch's).
 template <class S> constexpr int qp_group() { return S::KT == 4 ? 2 : 1; }
 
 template <class S, class T, int KT, int G>
@@ -93,6 +94,16 @@ PSFD_D void qp_slots(const T* V, long long ldv, bool nt, int i0, int cnt, unsign
   }
 }
 
+// Whether the slots are read past the caches: mode 2 counts the launch's running
+// instances (their flags in `active`; the same answer in every lane).
+PSFD_D bool qp_past_caches(int mode, int cached, const int* active) {
+  if (mode < 2) return mode != 0;
+  const int nb = gridDim.y, lane = threadIdx.x & 63;
+  int n = 0;
+  for (int i = 0; i < nb; i += 64) n += __popcll(__ballot(i + lane < nb && active[min(i + lane, nb - 1)] != 0));
+  return n > cached;
+}
+
 // The Gram-Schmidt update of column cnt - 1 on this block's values wv of slot
 // cnt, in place: w - sum_{i<cnt} h_i s_i slot_i, stored back to the slot; this
 // block's ||slot||^2 goes to part[pidx]. h_i = s_i <slot_i, w> from the projection
@@ -100,8 +111,8 @@ PSFD_D void qp_slots(const T* V, long long ldv, bool nt, int i0, int cnt, unsign
 // same coefficients bit for bit; block 0 stores h and ||w||^2 before the update
 // for the Givens step.
 template <class S, class T, int KT>
-PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& slot, unsigned lane, int b, int pidx,
-                      long long poff) {
+PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& slot, unsigned lane, int b,
+                      int pidx, long long poff) {
   constexpr int NT = S::NT, NW = NT / 64, G = qp_group<S>();
   typedef typename real_of<T>::type R;
   __shared__ T hc[MAXM];
@@ -111,8 +122,9 @@ PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& sl
   GState& St = u.st[b];
   const T* sb = reinterpret_cast<const T*>(u.V) + (long long)b * u.bsv + poff;
   const double2* pb = u.dpart + (long long)b * PSTR * u.nblk;
+  const bool nt = qp_past_caches(u.nt, u.cached, a.active);
   T p[G][KT];
-  qp_slots<S>(sb, u.ldv, u.nt, 0, cnt, lane, p);
+  qp_slots<S>(sb, u.ldv, nt, 0, cnt, lane, p);
   for (int i = wave; i <= cnt; i += NW) {
     const double sc = St.sc[i];
     const double2 t = dots_total(pb + (long long)i * u.nblk, u.nblk);
@@ -127,7 +139,7 @@ PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& sl
   }
   __syncthreads();
   for (int i0 = 0; i0 < cnt; i0 += G) {
-    if (i0 > 0) qp_slots<S>(sb, u.ldv, u.nt, i0, cnt, lane, p);
+    if (i0 > 0) qp_slots<S>(sb, u.ldv, nt, i0, cnt, lane, p);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       if (i0 + g < cnt) {
@@ -163,7 +175,7 @@ PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& sl
 // as partial pidx of nblk (indices no block owns get zeros). p holds the first
 // group of slots (qp_slots before the transform).
 template <class S, class T, int KT, int G>
-PSFD_D void qp_dots(const TileArgs& a, int cnt, const T (&wv)[KT], T (&p)[G][KT], const T* sb, unsigned lane, int b,
+PSFD_D void qp_dots(const TileArgs& a, bool nt, int cnt, const T (&wv)[KT], T (&p)[G][KT], const T* sb, unsigned lane, int b,
                     int pidx) {
   constexpr int NW = S::NT / 64;
   static_assert(S::lds() >= (size_t)PSTR * NW * sizeof(double2), "partials fit the block's LDS");
@@ -173,7 +185,7 @@ PSFD_D void qp_dots(const TileArgs& a, int cnt, const T (&wv)[KT], T (&p)[G][KT]
   const int tid = threadIdx.x, wave = tid >> 6;
   __syncthreads();
   for (int i0 = 0; i0 < cnt; i0 += G) {
-    if (i0 > 0) qp_slots<S>(sb, d.ldv, d.nt, i0, cnt, lane, p);
+    if (i0 > 0) qp_slots<S>(sb, d.ldv, nt, i0, cnt, lane, p);
     // all G sums side by side (zeros for the slots past the last)
     T acc[G];
 #pragma unroll
@@ -317,11 +329,13 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY, WIDE>::NT)) k_qplane(Til
   constexpr int G = qp_group<S>();
   T p[DOTS ? G : 1][DOTS ? KT : 1];
   const T* sb = nullptr;
+  bool nt = false;
   if constexpr (DOTS) {
+    nt = qp_past_caches(a.dt.nt, a.dt.cached, a.active);
     sb = reinterpret_cast<const T*>(a.dt.V) + (long long)b * a.dt.bsv + poff;
     cnt = a.dt.jh + 1;
     if (a.dt.jh < 0) cnt = __builtin_amdgcn_readfirstlane(a.dt.st[b].j) + 1;
-    qp_slots<S>(sb, a.dt.ldv, a.dt.nt, 0, cnt, lane, p);
+    qp_slots<S>(sb, a.dt.ldv, nt, 0, cnt, lane, p);
   }
   const double* tab = a.tab + (long long)b * a.tab_stride;
   R ks = (R)1;
@@ -369,7 +383,7 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY, WIDE>::NT)) k_qplane(Til
         if constexpr (DOTS) va[i + NBL * j] = v;  // row 4 r + q: element k = i + NBL j of the thread
       }
     }
-  if constexpr (DOTS) qp_dots<S>(a, cnt, va, p, sb, lane, b, 4 * plane + q);
+  if constexpr (DOTS) qp_dots<S>(a, nt, cnt, va, p, sb, lane, b, 4 * plane + q);
 }
 
 // Whether a plane takes the quarter kernels: both sides 16 .. 256 and 1024 or

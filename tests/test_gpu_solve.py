@@ -342,3 +342,29 @@ def test_solve_deterministic_and_reusable():
     b, ob, ib = plan.psfd_solve(d)
     assert torch.equal(a, b) and torch.equal(oa, ob)
     assert ia == ib
+
+
+def test_batch_whose_instances_leave_matches_alone():
+    """Ten 64 x 64 x 32 mixed instances in lock-step at restart 16: early steps read the
+    basis through the caches, later ones past them, and as the instances of weak
+    contrast converge the later ones read through the caches again. The loads
+    differ, the arithmetic does not: fields and step counts equal the lone
+    solves' bitwise."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    layers, es = clips.mo_si_stack(40)
+    p = clips.Problem(nx=64, ny=64, nz=32, lx_nm=128.0, ly_nm=128.0, t_nm=60.0, theta_deg=6.0,
+                      phi_deg=15.0, pol=1, layers=layers, eps_sub=es)
+    ds = [torch.from_numpy(clips.contact_holes(64, 64, 32, 128.0, 128.0, 6, seed=220 + i) * (1.0 if i < 3 else 0.2)).to(dev)
+          for i in range(10)]
+    opts = dict(rtol=1e-8, precision="mixed", restart=16)
+    say("solve 10 x 64x64x32 mixed, restart 16, batch vs alone")
+    em, od, infos = api.psfd_solve_batch([p] * 10, ds, **opts)
+    plan = api.Plan(p, **opts)
+    for i in (0, 2, 9):
+        e, o, info = plan.psfd_solve(ds[i])
+        say("  instance", i, infos[i]["iters"], info["iters"])
+        assert info["status"] == 0 and infos[i]["status"] == 0
+        assert infos[i]["iters"] == info["iters"]
+        assert torch.equal(em[i], e) and torch.equal(od[i], o)
+    assert infos[9]["iters"] < infos[0]["iters"]
