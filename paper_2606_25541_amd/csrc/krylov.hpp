@@ -96,9 +96,9 @@ template <class R> PSFD_D R lane_sum(R v) {
 
 // Sum of the n projection partials of one value (n a multiple of 64) over a
 // wavefront in a fixed order: lane l takes partials l, l + 64, ..., then the
-// wavefront sum; 6 loads per lane are issued together. Every lane gets the sum.
-PSFD_D double2 dots_total(const double2* p, int n) {
-  constexpr int U = 6;
+// wavefront sum; U loads per lane are issued together. Every lane gets the sum,
+// the same bits for any U.
+template <int U = 6> PSFD_D double2 dots_total(const double2* p, int n) {
   const int lane = threadIdx.x & 63;
   double2 t = make_double2(0, 0);
   for (int k0 = 0; k0 < n; k0 += 64 * U) {

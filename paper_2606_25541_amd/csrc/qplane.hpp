@@ -50,6 +50,11 @@ template <class T, int LNX, int LNY, bool WIDE> struct QpShape {
   static constexpr int LKT = KT == 16 ? 4 : KT == 8 ? 3 : KT == 4 ? 2 : 1;
   static constexpr int LRM_ROWS = LKT, LRM_COLS = LKT < 3 ? LKT : 3;
   static constexpr int LRL = (LNY - 3) % LRM_COLS + 1, RL = 1 << LRL;  // last column pass: radix RL
+  // projection partials a lane of the update requests at once: all 12 of the wide
+  // shapes (768 partials at 64 planes; in two rounds of 6 the second waits for the
+  // first, 16 x 128 x 128 x 64 1909 -> 1880 us a step), else 6 (all at 32 planes; 12
+  // cost registers: 256 x 256 spills, 423 -> 444, four 64 x 64 x 64 116.8 -> 117.9)
+  static constexpr int DU = WIDE ? 12 : 6;
   static constexpr size_t lds() { return ((size_t)ROWS * (NX + 1) + NX + (NX == NY ? 1 : 2) * ROWS) * sizeof(T); }
   static_assert(KT * NT == ELEM && NT % NX == 0 && (1 << LKT) == KT && ROWS <= NT && RL <= KT, "quarter-plane split");
 };
@@ -127,7 +132,7 @@ PSFD_D void qp_update(const TileArgs& a, int cnt, T (&wv)[KT], const LaneBuf& sl
   qp_slots<S>(sb, u.ldv, nt, 0, cnt, lane, p);
   for (int i = wave; i <= cnt; i += NW) {
     const double sc = St.sc[i];
-    const double2 t = dots_total(pb + (long long)i * u.nblk, u.nblk);
+    const double2 t = dots_total<S::DU>(pb + (long long)i * u.nblk, u.nblk);
     if ((tid & 63) == 0) {
       if (i < cnt) {
         hc[i] = from_d<T>(cscale(t, sc * sc));

@@ -368,3 +368,51 @@ def test_batch_whose_instances_leave_matches_alone():
         assert infos[i]["iters"] == info["iters"]
         assert torch.equal(em[i], e) and torch.equal(od[i], o)
     assert infos[9]["iters"] < infos[0]["iters"]
+
+
+@pytest.mark.parametrize("shape", [(128, 128, 64), (256, 64, 64), (256, 256, 32)])
+def test_gram_schmidt_update_of_16_values_per_thread(shape, monkeypatch):
+    """The forward quarter-plane kernels whose threads hold 16 values (4096-value
+    quarters above 32 z planes, 16384-value ones) with the update fused: against the
+    separate passes (PSFD_FUSE_DOTS=0; fields to the conditioning times the
+    tolerance, within one restart cycle of the same step count), and bitwise the
+    same in a repeat, in a served slot, and in a lock-step batch of two, whose
+    slots are read past the caches from some step on."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    nx, ny, nz = shape
+    layers, es = clips.mo_si_stack(40)
+    p = clips.Problem(nx=nx, ny=ny, nz=nz, lx_nm=2.0 * nx, ly_nm=2.0 * ny, t_nm=60.0, theta_deg=6.0,
+                      phi_deg=15.0, pol=1, layers=layers, eps_sub=es)
+    ds = [torch.from_numpy(clips.contact_holes(nx, ny, nz, 2.0 * nx, 2.0 * ny, 6, seed=s)).to(dev) for s in (78, 79)]
+    say("solve %dx%dx%d mixed, update of 16 values per thread" % shape)
+    opts = dict(rtol=1e-9, precision="mixed", restart=8)
+    plan = api.Plan(p, **opts)
+    alone = [plan.psfd_solve(d) for d in ds]
+    e1, o1, i1 = alone[0]
+    e1b, o1b, i1b = plan.psfd_solve(ds[0])
+    assert i1["status"] == 0 and i1 == i1b and torch.equal(e1, e1b) and torch.equal(o1, o1b)
+    em, od, infos = api.psfd_solve_batch([p, p], ds, **opts)
+    for (e, o, i), eb, ob, ib in zip(alone, em, od, infos):
+        say("  batched", ib, "alone", i)
+        assert ib["status"] == 0 and ib["iters"] == i["iters"]
+        assert torch.equal(e, eb) and torch.equal(o, ob)
+    api.psfd_release_cached_workspaces()
+    srv = api.Server(hbm_budget=16 << 30, max_slots=2, **opts)
+    es_, os_ = torch.empty_like(e1), torch.empty_like(o1)
+    t = srv.submit(p, ds[0], es_, os_)
+    deadline = time.perf_counter() + 60
+    done = False
+    while not done and time.perf_counter() < deadline:
+        done, info, _ = srv.poll(t)
+        time.sleep(0.002)
+    srv.close()
+    assert done, "served request not finished within 60 s"
+    assert info["status"] == 0 and info["iters"] == i1["iters"]
+    assert torch.equal(e1, es_) and torch.equal(o1, os_)
+    monkeypatch.setenv("PSFD_FUSE_DOTS", "0")
+    e2, _, i2 = plan.psfd_solve(ds[0])
+    say("  fused", i1, "separate", i2)
+    assert i2["status"] == 0
+    assert abs(i1["iters"] - i2["iters"]) <= 8
+    assert rel(e1.cpu().numpy(), e2.cpu().numpy()) < 1e-7
