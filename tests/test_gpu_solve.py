@@ -416,3 +416,35 @@ def test_gram_schmidt_update_of_16_values_per_thread(shape, monkeypatch):
     assert i2["status"] == 0
     assert abs(i1["iters"] - i2["iters"]) <= 8
     assert rel(e1.cpu().numpy(), e2.cpu().numpy()) < 1e-7
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 8), (64, 64, 16), (128, 128, 16), (256, 256, 8), (64, 64, 4)])
+def test_served_slot_equals_lone_solve_with_separate_update(shape):
+    """Mixed solves below 32 z planes: the projections in the inverse kernel, the update
+    a pass of its own, the Givens step beside it. A served slot runs the same
+    arithmetic as the lone solve: step counts, fields and orders are bitwise the
+    same."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    nx, ny, nz = shape
+    layers, es = clips.mo_si_stack(40)
+    p = clips.Problem(nx=nx, ny=ny, nz=nz, lx_nm=2.0 * nx, ly_nm=2.0 * ny, t_nm=60.0, theta_deg=6.0,
+                      phi_deg=15.0, pol=1, layers=layers, eps_sub=es)
+    d = torch.from_numpy(clips.contact_holes(nx, ny, nz, 2.0 * nx, 2.0 * ny, 6, seed=78)).to(dev)
+    say("solve %dx%dx%d mixed, served and alone" % shape)
+    opts = dict(rtol=1e-9, precision="mixed", restart=8)
+    e1, o1, i1 = api.Plan(p, **opts).psfd_solve(d)
+    srv = api.Server(hbm_budget=8 << 30, max_slots=2, **opts)
+    e2, o2 = torch.empty_like(e1), torch.empty_like(o1)
+    t = srv.submit(p, d, e2, o2)
+    deadline = time.perf_counter() + 60
+    done = False
+    while not done and time.perf_counter() < deadline:
+        done, info, _ = srv.poll(t)
+        time.sleep(0.002)
+    srv.close()
+    assert done, "served request not finished within 60 s"
+    say("  alone", i1, "served", info, "rel", rel(e2.cpu().numpy(), e1.cpu().numpy()))
+    assert i1["status"] == 0 and info["status"] == 0
+    assert info["iters"] == i1["iters"]
+    assert torch.equal(e1, e2) and torch.equal(o1, o2)
