@@ -249,6 +249,8 @@ typedef struct {
   int32_t dots_in_inverse;   /* the inverse transverse kernel also forms the projections */
   int32_t update_in_forward; /* the forward one also does the previous column's update (lock-step
                                 solves: at steps >= 1; the last column of a cycle takes none) */
+  int32_t givens_launch;     /* a lock-step step >= 1 runs the previous column's Givens step in a launch
+                                of its own (else inside a kernel of the apply) */
   int32_t partials;          /* partial sums per projection */
   int32_t cached_instances;  /* quarter planes read the basis through the caches while at most this
                                 many instances of a lock-step group run, past them beyond */

@@ -55,7 +55,7 @@ class psfd_info(C.Structure):
 
 class psfd_step_kernels(C.Structure):
     _fields_ = [("quarter_planes", C.c_int32), ("dots_in_inverse", C.c_int32), ("update_in_forward", C.c_int32),
-                ("partials", C.c_int32), ("cached_instances", C.c_int32)]
+                ("givens_launch", C.c_int32), ("partials", C.c_int32), ("cached_instances", C.c_int32)]
 
 
 class psfd_iso_problem(C.Structure):

@@ -228,6 +228,7 @@ int psfd_step_info(int32_t nx, int32_t ny, int32_t nz, int precision, int step, 
   out->quarter_planes = k.quarter;
   out->dots_in_inverse = k.dots;
   out->update_in_forward = k.update;
+  out->givens_launch = k.givens_launch;
   out->partials = k.partials;
   out->cached_instances = k.cached;
   return PSFD_OK;

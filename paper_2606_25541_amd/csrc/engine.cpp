@@ -456,12 +456,15 @@ void apply_stage(Group& g, int stage, const T* deps, VecRef in, VecRef out, T* w
   if (stage == 0) {
     // forward: w = FFT_xy(k0^2 delta_eps x)
     if (qp) {
-      // a pending Givens step takes a launch of its own first
-      if (gt) krylov_givens(gt->st, gt->run, gt->part, g.B, s);
       TileArgs a = tile_base(g, tw, c.full);
       a.in = in; a.vol = vr(deps, sh.N); a.out = wsr; a.active = active;
       a.in_scale = in_scale; a.scale_stride = scale_stride;
-      launch_qplane<T, false, LD_VX, ST_PLAIN>(a, np, g.B, s);
+      if (gt) {
+        a.gv = *gt;
+        launch_qplane<T, false, LD_VX_GIV, ST_PLAIN>(a, np, g.B, s);
+      } else {
+        launch_qplane<T, false, LD_VX, ST_PLAIN>(a, np, g.B, s);
+      }
     } else if (c.fused) {
       TileArgs a = tile_base(g, tw, c.full);
       a.in = in; a.vol = vr(deps, sh.N); a.out = wsr; a.active = active;
@@ -695,6 +698,21 @@ template <class T> static T* deps_of_mut(Group& g);
 template <> float2* deps_of_mut<float2>(Group& g) { return g.deps32; }
 template <> double2* deps_of_mut<double2>(Group& g) { return g.deps64; }
 
+// Whether the Arnoldi steps of a shape run the quarter-plane kernels: where its
+// applies do, but for FP64 64 x 64 planes at 32 and 64 z planes. One block of 512
+// threads per plane fills the chip there as well, and the quarter combine costs the
+// FP64 pencil 9 % (one block per CU, so nothing overlaps it) and batches beyond the
+// caches more. us a step, GMRES(8), one block per plane / quarter planes: 64 x 64 x 32
+// 66.0 / 65.6 alone, 646 / 659 for 16 instances; 64 x 64 x 64 84.8 / 85.5 and 1045 /
+// 1090. At 8 planes 53.2 / 46.2, and at 128, where the natural layout has no
+// compile-time pencil, 142.6 / 133.8. (By the shape alone: a solve takes the same
+// arithmetic by itself, in a batch and in a server's slot.)
+static bool step_quarter_planes(const Shape& sh, size_t esz) {
+  if (!quarter_planes(sh, esz)) return false;
+  const XYCfg c = xy_config(sh, esz);
+  return !(esz == 16 && c.fused && tile_is_plane(tile_shape(sh, c.full), esz) && (sh.nz == 32 || sh.nz == 64));
+}
+
 // Whether the forward transverse kernel of an Arnoldi step also does the
 // Gram-Schmidt update of the previous column: the quarter-plane kernels that
 // carry it (qplane_gs), with the projections in the inverse kernel, which also
@@ -750,9 +768,11 @@ static int slots_nt(int B, int cached) { return B <= cached ? 0 : cached < 1 ? 1
 
 StepKernels step_kernels(const Shape& sh, size_t esz, int jh) {
   StepKernels k;
-  k.quarter = quarter_planes(sh, esz);
+  k.quarter = step_quarter_planes(sh, esz);
   k.dots = esz == 8 && fuse_dots(sh, esz);
   k.update = esz == 8 && fuse_update(sh, esz);
+  const XYCfg c = xy_config(sh, esz);
+  k.givens_launch = !k.quarter && !(c.fused && tile_is_plane(tile_shape(sh, c.full), esz));
   k.partials = dot_partials(sh, esz);
   k.cached = k.quarter && k.dots ? cached_instances(sh, esz, jh) : INT_MAX;
   return k;
@@ -806,7 +826,7 @@ static Status bench_gs_t(Group& g, int pass, int j, const T* x, int reps, float*
   // pass 3: the forward transverse stage of step j + 1 carrying the update of
   // column j where the shape allows it (else the plain forward stage); the
   // contrast is the first N values of x
-  const bool qp = quarter_planes(g, sizeof(T));
+  const bool qp = step_quarter_planes(g.sh, sizeof(T));
   bool fwd_upd = false;
   TileArgs fa;
   std::memset(&fa, 0, sizeof(fa));
@@ -884,7 +904,7 @@ bool arnoldi_step(Group& g, int transpose, int refl, hipStream_t s, int jh, cons
   const double* isc = &g.st[0].inv_norm;
   const long long iss = (long long)(sizeof(GState) / sizeof(double));
   // the quarter-plane kernels and layout where the shape takes them
-  const bool qp = quarter_planes(g, sizeof(T));
+  const bool qp = step_quarter_planes(g.sh, sizeof(T));
   const int nblk = dot_partials(g.sh, sizeof(T)), nq = 12 * g.sh.nz;
   bool upd = false, upd_slots = false;
   if constexpr (std::is_same<T, float2>::value) {

@@ -163,7 +163,7 @@ void apply_op(Group& g, const T* deps, VecRef in, VecRef out, T* ws, int kmode, 
               const GivensTask* gt = nullptr);
 // one of the three launches of apply_op: 0 transverse forward, 1 z-pencil, 2 transverse inverse.
 // qp: the quarter-plane kernels and layout (all three stages of one apply alike;
-// only where quarter_planes holds; a gt of stage 0 then takes a launch of its own)
+// only where quarter_planes holds)
 template <class T>
 void apply_stage(Group& g, int stage, const T* deps, VecRef in, VecRef out, T* ws, int kmode, int transpose,
                  int refl, const int* active, hipStream_t s, const double* in_scale = nullptr,
@@ -175,6 +175,7 @@ bool quarter_planes(const Group& g, size_t esz);
 // a server's slots), from the shape and the environment's switches alone
 struct StepKernels {
   bool quarter, dots, update;  // quarter planes; Gram-Schmidt work in their kernels
+  bool givens_launch;          // the Givens step of the column before in a launch of its own
   int partials;                // projection partials per value
   int cached;                  // instances running at most for slots through the caches
 };

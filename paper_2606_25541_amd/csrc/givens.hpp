@@ -10,22 +10,30 @@ namespace psfd {
 
 // ||w||^2 from the nblk (<= RED_BLOCKS) norm partials of one instance, in two
 // halves for callers with barriers of their own between them. norm_wave_sums:
-// the first GIVENS_THREADS threads take partials tid, tid + 256, ... in order
-// and leave their four wavefront sums in gs (LDS; the other threads do
-// nothing). norm_total, after a barrier: the four sums in order.
-PSFD_D void norm_wave_sums(const double2* pb, int nblk, double2* gs) {
-  constexpr int PK = RED_BLOCKS / GIVENS_THREADS;
+// wavefront w of GIVENS_THREADS / 64 takes partials 64 w + lane, + 256, ... in order
+// and leaves its sum in gs (LDS). A block of NT < GIVENS_THREADS threads gives each
+// of its wavefronts several of these; further threads do nothing. norm_total,
+// after a barrier: the four sums in order. So every caller gets the same bits.
+template <int NT = GIVENS_THREADS> PSFD_D void norm_wave_sums(const double2* pb, int nblk, double2* gs) {
+  constexpr int PK = RED_BLOCKS / GIVENS_THREADS, W = NT < GIVENS_THREADS ? NT / 64 : GIVENS_THREADS / 64;
+  constexpr int VW = GIVENS_THREADS / 64 / W;  // sums per wavefront
+  static_assert(NT % 64 == 0 && VW * W * 64 == GIVENS_THREADS, "whole wavefronts");
   const int tid = threadIdx.x;
-  if (tid < GIVENS_THREADS) {
-    double2 pv[PK];
-    double2 acc = make_double2(0, 0);
+  if (tid < 64 * W) {
+    double2 pv[VW][PK];
 #pragma unroll
-    for (int k = 0; k < PK; ++k) pv[k] = pb[min(tid + k * GIVENS_THREADS, nblk - 1)];
+    for (int v = 0; v < VW; ++v)
 #pragma unroll
-    for (int k = 0; k < PK; ++k)
-      if (tid + k * GIVENS_THREADS < nblk) acc = cadd(acc, pv[k]);
-    const double re = lane_sum(acc.x), im = lane_sum(acc.y);
-    if ((tid & 63) == 0) gs[tid >> 6] = make_double2(re, im);
+      for (int k = 0; k < PK; ++k) pv[v][k] = pb[min(tid + 64 * W * v + k * GIVENS_THREADS, nblk - 1)];
+#pragma unroll
+    for (int v = 0; v < VW; ++v) {
+      double2 acc = make_double2(0, 0);
+#pragma unroll
+      for (int k = 0; k < PK; ++k)
+        if (tid + 64 * W * v + k * GIVENS_THREADS < nblk) acc = cadd(acc, pv[v][k]);
+      const double re = lane_sum(acc.x), im = lane_sum(acc.y);
+      if ((tid & 63) == 0) gs[(tid >> 6) + W * v] = make_double2(re, im);
+    }
   }
 }
 PSFD_D double norm_total(const double2* gs) {
@@ -34,12 +42,12 @@ PSFD_D double norm_total(const double2* gs) {
   return t.x;
 }
 
-// Both halves with their barriers: every thread of the block must call it, and
-// the block must have at least GIVENS_THREADS threads; all of them get the total.
-PSFD_D double norm_from_partials(const double2* pb, int nblk) {
+// Both halves with their barriers: every thread of the block (of at least NT
+// threads) must call it; all of them get the total.
+template <int NT = GIVENS_THREADS> PSFD_D double norm_from_partials(const double2* pb, int nblk) {
   __shared__ double2 gsm[GIVENS_THREADS / 64];
   __shared__ double gtot;
-  norm_wave_sums(pb, nblk, gsm);
+  norm_wave_sums<NT>(pb, nblk, gsm);
   __syncthreads();
   if (threadIdx.x == 0) gtot = norm_total(gsm);
   __syncthreads();
@@ -63,14 +71,14 @@ PSFD_D double inv_norm_of(double wn2) {
 // partials, this column's Givens inputs, the scalars), so the task pays one
 // memory latency; the rotations of the earlier columns are staged in LDS, so
 // the single-thread recurrence reads no global memory. Every thread of the
-// block must call it (blockDim >= GIVENS_THREADS).
+// block must call it (at least NT of them).
 // PROJ: the caller passes this thread's projection hp (h_t of the column), ||w||^2
 // before the update (wn2in_p) and after it (wn2_p) instead of the state and the
 // norm partials, and the column's slot j + 1 keeps w (raw_last = j + 1).
-template <bool PROJ>
+template <bool PROJ, int NT = GIVENS_THREADS>
 PSFD_D void givens_impl(GState* st, int* run, const double2* part, int nblk, int b, double2 hp, double wn2in_p,
                         double wn2_p) {
-  static_assert(GIVENS_THREADS > MAXM, "one thread per Hessenberg row");
+  static_assert(NT > MAXM && GIVENS_THREADS > MAXM, "one thread per Hessenberg row");
   __shared__ double2 col[MAXM + 1], snl[MAXM], gj_s;
   __shared__ double csl[MAXM];
   const int tid = threadIdx.x;
@@ -85,7 +93,7 @@ PSFD_D void givens_impl(GState* st, int* run, const double2* part, int nblk, int
   asm volatile("" ::"v"(hv.x), "v"(hv.y), "v"(gv.x), "v"(gv.y), "v"(snv.x), "v"(snv.y), "v"(csv));
   asm volatile("" ::"s"(thr), "s"(wn2in), "s"(beta), "s"(target), "s"(m), "s"(iters), "s"(ncancel));
   if (!runb) return;
-  const double wn2 = PROJ ? wn2_p : norm_from_partials(part + (long long)b * nblk, nblk);
+  const double wn2 = PROJ ? wn2_p : norm_from_partials<NT>(part + (long long)b * nblk, nblk);
   const bool cancel = wn2 < thr * wn2in;
   if (tid <= j) col[tid] = make_double2((tid == j ? 1.0 : 0.0) - hv.x, -hv.y);
   if (tid < j) { csl[tid] = csv; snl[tid] = snv; }
@@ -137,8 +145,8 @@ PSFD_D void givens_impl(GState* st, int* run, const double2* part, int nblk, int
   if (tid <= j) S.H[tid][j] = col[tid];
 }
 
-PSFD_D void givens_task(GState* st, int* run, const double2* part, int nblk, int b) {
-  givens_impl<false>(st, run, part, nblk, b, make_double2(0, 0), 0.0, 0.0);
+template <int NT = GIVENS_THREADS> PSFD_D void givens_task(GState* st, int* run, const double2* part, int nblk, int b) {
+  givens_impl<false, NT>(st, run, part, nblk, b, make_double2(0, 0), 0.0, 0.0);
 }
 
 }  // namespace psfd

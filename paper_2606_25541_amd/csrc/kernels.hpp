@@ -4,14 +4,15 @@
 
 namespace psfd {
 
-enum LoadOp { LD_PLAIN = 0, LD_VX = 1, LD_INJECT = 2, LD_VXE = 3, LD_INJECT_T = 4, LD_UPD_VX = 5, LD_UPD_SLOT = 6 };
+enum LoadOp { LD_PLAIN = 0, LD_VX = 1, LD_INJECT = 2, LD_VXE = 3, LD_INJECT_T = 4, LD_UPD_VX = 5, LD_UPD_SLOT = 6, LD_VX_GIV = 7 };
 
 struct GState;
 // The Givens step of the previous Arnoldi step, left to an apply kernel of
 // this one: an extra block of the kernel runs it (see givens_task), and the
 // other blocks take the scale of the step's input vector from the same norm
 // partials (nblk per instance in part, instance stride nblk) instead of in_scale.
-// The kernel's blocks must have at least GIVENS_THREADS threads.
+// The kernel's blocks must have at least GIVENS_THREADS threads (the quarter-plane
+// kernels any).
 struct GivensTask {
   GState* st;
   int* run;
@@ -79,7 +80,7 @@ struct TileArgs {
   const int* active;     // optional per-instance flags (0 = skip)
   const double* in_scale;  // LD_VX, optional: in scaled by in_scale[b * scale_stride] on load (in is not modified)
   long long scale_stride;
-  GivensTask gv;           // LD_VX square planes, optional (gv.st null: none)
+  GivensTask gv;           // LD_VX_GIV; LD_VX square planes, optional (gv.st null: none)
   DotTask dt;              // ST_DOTS
   UpdateTask up;           // LD_UPD_VX
 };
@@ -133,9 +134,9 @@ template <class T>
 void launch_pencil(const PencilArgs& a, int nbatch, int nthr, size_t lds, hipStream_t s);
 // Quarter-plane transverse kernels of the operator apply (planes of 16 .. 256 on
 // both sides, of 1024 and more values, whose quarter fits LDS): forward (LD_VX, ST_PLAIN) into the
-// quarter-plane layout, inverse (LD_PLAIN, ST_PLAIN or ST_AXPBY) from it, and
-// where qplane_gs holds LD_UPD_VX, LD_UPD_SLOT and ST_DOTS;
-// nplanes = 3 nz, no GivensTask. The pencil between them runs with PencilArgs::yq.
+// quarter-plane layout (LD_VX_GIV: with a GivensTask), inverse (LD_PLAIN, ST_PLAIN
+// or ST_AXPBY) from it, and where qplane_gs holds LD_UPD_VX, LD_UPD_SLOT and
+// ST_DOTS; nplanes = 3 nz. The pencil between them runs with PencilArgs::yq.
 template <class T, bool INV, int LD, int ST>
 void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s);
 // Columns of the quarter-layout pencil blocks of a shape; 0: the shape takes

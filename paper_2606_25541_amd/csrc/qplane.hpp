@@ -28,6 +28,7 @@
 
 #include "kernels.hpp"
 #include "krylov.hpp"
+#include "givens.hpp"
 #include "fft_lds.hpp"
 #include "regfft.hpp"
 
@@ -235,13 +236,25 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY, WIDE>::NT)) k_qplane(Til
   static_assert(!INV || LD == LD_PLAIN, "inverse: plain load");
   constexpr bool UPD = LD == LD_UPD_VX || LD == LD_UPD_SLOT;  // Gram-Schmidt update on load
   constexpr bool DOTS = ST == ST_DOTS;
-  static_assert(INV || ((LD == LD_VX || UPD) && ST == ST_PLAIN), "forward: contrast multiply, plain store");
+  constexpr bool GIV = LD == LD_VX_GIV;  // with the pending Givens step
+  static_assert(INV || ((LD == LD_VX || GIV || UPD) && ST == ST_PLAIN), "forward: contrast multiply, plain store");
   extern __shared__ double2 smem_d[];
   T* lds = reinterpret_cast<T*>(smem_d);
   T* twx = lds + QR * P;  // W_nx^k, k < nx
   T* twr = twx + NX;      // W_(ny/4)^k, k < ny / 4
   T* twq = twr + QR;      // W_ny^(q k), k < ny / 4 (square planes: in twx)
   const int b = blockIdx.y;
+  // the Givens step of the column before in the extra last block of the grid; the
+  // others scale the input by the norm they sum from the same partials, bitwise the
+  // task's (as a launch of its own it costs a step more: GMRES(8)
+  // 128 x 128 x 16 FP64 96.0 -> 92.6 us, 64 x 64 x 8 FP64 48.5 -> 46.2, 64 x 64 x 16
+  // mixed 35.6 -> 33.1, 128 x 128 x 64 FP64 at restart 30 467 -> 462.5)
+  if constexpr (GIV) {
+    if (blockIdx.x == gridDim.x - 1) {
+      givens_task<NT>(a.gv.st, a.gv.run, a.gv.part, a.gv.nblk, b);
+      return;
+    }
+  }
   if (a.active && !a.active[b]) return;
   // block order: with 8 | nz, XCD x (= hw mod 8) takes the planes z = x mod 8 of
   // all three components and their four quarters, so the three blocks that read
@@ -346,6 +359,8 @@ __global__ void __launch_bounds__((QpShape<T, LNX, LNY, WIDE>::NT)) k_qplane(Til
   R ks = (R)1;
   // LD_UPD_*: an updated vector enters unscaled (the pencil kernel scales it)
   if constexpr (UPD) ks = (R)tab[TS_K0SQ] * (LD == LD_UPD_SLOT && !upd ? (R)a.up.st[b].inv_norm : (R)1);
+  else if constexpr (GIV)
+    ks = (R)tab[TS_K0SQ] * (R)inv_norm_of(norm_from_partials<NT>(a.gv.part + (long long)b * a.gv.nblk, a.gv.nblk));
   else if constexpr (!INV) ks = (R)tab[TS_K0SQ] * (a.in_scale ? (R)a.in_scale[(long long)b * a.scale_stride] : (R)1);
   if (tid < NX) twx[tid] = tw0;
   if (tid < QR) twr[tid] = tw1;
@@ -415,13 +430,14 @@ constexpr bool qplane_gs_fits(int lnx, int lny, size_t esz) {
 
 template <class T, bool INV, int LD, int ST>
 void launch_qplane(const TileArgs& a, int nplanes, int nbatch, hipStream_t s) {
+  constexpr bool GIV = LD == LD_VX_GIV;
   auto go = [&](auto kern, int nt, size_t l) {
     if (l > 65536)
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)l);
-    hipLaunchKernelGGL(kern, dim3(4 * nplanes, nbatch), dim3(nt), l, s, a);
+    hipLaunchKernelGGL(kern, dim3(4 * nplanes + (GIV ? 1 : 0), nbatch), dim3(nt), l, s, a);
   };
   bool done = false;
-  if (!a.gv.st && nplanes == 3 * a.nz) {
+  if ((a.gv.st != nullptr) == GIV && nplanes == 3 * a.nz) {
     auto shape = [&](auto lx, auto ly) {
       constexpr int LX = decltype(lx)::value, LY = decltype(ly)::value;
       constexpr bool GS = ST == ST_DOTS || LD == LD_UPD_VX || LD == LD_UPD_SLOT;

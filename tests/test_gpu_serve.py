@@ -404,3 +404,47 @@ def test_iteration_limit_with_restarts_without_residual(monkeypatch):
     for e, o, i in res.values():
         assert i == i0
         assert torch.equal(e, e0) and torch.equal(o, o0)
+
+
+@pytest.mark.parametrize("shape,prec", [((64, 64, 32), "fp64"), ((64, 64, 8), "fp64"), ((32, 32, 32), "fp64"),
+                                        ((128, 128, 8), "fp64"), ((256, 16, 16), "fp64"), ((32, 32, 32), "mixed"),
+                                        ((64, 64, 16), "mixed"), ((16, 64, 8), "mixed"), ((128, 128, 16), "mixed"),
+                                        ((128, 128, 128), "mixed"), ((256, 256, 8), "mixed")])
+def test_givens_step_in_the_forward_quarter_kernel(shape, prec):
+    """Lock-step solves whose update is a pass of its own: the Givens step of the column
+    before runs in an extra block of the forward quarter-plane kernel, whose other
+    blocks (64 to 1024 threads) sum the norm partials themselves for the scale of
+    the input. A served slot runs it in the update pass and reads the scale. Two
+    instances in a batch, one of weaker contrast that converges cycles earlier,
+    each alone, and one served: bitwise the same."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    nx, ny, nz = shape
+    layers, es = clips.mo_si_stack(20)
+    p = clips.Problem(nx=nx, ny=ny, nz=nz, lx_nm=2.0 * nx, ly_nm=2.0 * ny, t_nm=30.0, theta_deg=6.0, phi_deg=20.0,
+                      pol=1, layers=layers, eps_sub=es)
+    de = clips.manhattan(nx, ny, nz, p.lx_nm, p.ly_nm, seed=310)
+    ds = [torch.from_numpy(d).to(dev) for d in (de, 0.25 * de)]
+    opts = dict(rtol=1e-9, precision=prec, restart=8)
+    say("givens step in the forward quarter kernel", shape, prec)
+    em, od, infos = api.psfd_solve_batch([p, p], ds, **opts)
+    api.psfd_release_cached_workspaces()
+    plan = api.Plan(p, **opts)
+    for d, e, o, inf in zip(ds, em, od, infos):
+        e1, o1, i1 = plan.psfd_solve(d)
+        say("  batched", inf, "alone", i1)
+        assert inf["status"] == 0 and inf["iters"] == i1["iters"]
+        assert torch.equal(e, e1) and torch.equal(o, o1)
+    assert infos[1]["iters"] < infos[0]["iters"]
+    srv = api.Server(hbm_budget=16 << 30, max_slots=2, **opts)
+    e2, o2 = torch.empty_like(em[0]), torch.empty_like(od[0])
+    t = srv.submit(p, ds[0], e2, o2)
+    deadline = time.perf_counter() + 60
+    done = False
+    while not done and time.perf_counter() < deadline:
+        done, info, _ = srv.poll(t)
+        time.sleep(0.002)
+    srv.close()
+    assert done, "served request not finished within 60 s"
+    assert info["status"] == 0 and info["iters"] == infos[0]["iters"]
+    assert torch.equal(em[0], e2) and torch.equal(od[0], o2)

@@ -59,6 +59,26 @@ def test_gram_schmidt_kernels_by_shape(shape, want, monkeypatch):
     assert (k.dots_in_inverse, k.update_in_forward, k.partials) == (0, 0, 256)
 
 
+@pytest.mark.parametrize("shape", [(64, 64, 32), (64, 64, 64), (64, 64, 8), (128, 128, 8), (128, 128, 16), (64, 64, 4),
+                                   (32, 32, 32), (256, 64, 16), (128, 128, 128)])
+def test_pending_givens_step_takes_no_launch(shape):
+    """Square planes and quarter planes carry the Givens step of the column before in
+    a kernel of the apply, in both precisions; row and column strips do not."""
+    for precision in (0, 1):
+        assert info(*shape, step=3, precision=precision).givens_launch == 0
+    assert info(16, 8, 32, 3).givens_launch == 1
+
+
+def test_fp64_square_planes_keep_one_block_per_plane():
+    """FP64 steps of 64 x 64 planes: one block per plane at 32 and 64 z planes, quarter
+    planes elsewhere and in FP32."""
+    for nz in (8, 16, 32, 64, 128):
+        assert info(64, 64, nz, 3, precision=0).quarter_planes == (nz not in (32, 64))
+        assert info(64, 64, nz, 3).quarter_planes == 1
+    assert info(64, 128, 32, 3, precision=0).quarter_planes == 1
+    assert info(128, 128, 64, 3, precision=0).quarter_planes == 1
+
+
 def test_step_info_rejects_bad_arguments():
     from paper_2606_25541_amd import _lib as L
     lib, k = L.lib(), L.psfd_step_kernels()
