@@ -822,10 +822,11 @@ static Status bench_gs_t(Group& g, int pass, int j, const T* x, int reps, float*
   VecRef vout;
   std::memset(&vout, 0, sizeof(vout));
   vout.base = V; vout.bstride = bsv; vout.jstride = n3; vout.joff = j + 1;
-  if (pass == 2) HIPCHK(hipMemcpyAsync(g.wsP, x, sizeof(T) * n3, hipMemcpyDeviceToDevice, s));
+  if (pass >= 2) HIPCHK(hipMemcpyAsync(g.wsP, x, sizeof(T) * n3, hipMemcpyDeviceToDevice, s));
   // pass 3: the forward transverse stage of step j + 1 carrying the update of
-  // column j where the shape allows it (else the plain forward stage); the
-  // contrast is the first N values of x
+  // column j where the shape allows it (else the plain forward stage), from the
+  // partials an inverse stage leaves, as many as in a solve; the contrast is the
+  // first N values of x
   const bool qp = step_quarter_planes(g.sh, sizeof(T));
   bool fwd_upd = false;
   TileArgs fa;
@@ -837,8 +838,10 @@ static Status bench_gs_t(Group& g, int pass, int j, const T* x, int reps, float*
       const XYCfg c = xy_config(g.sh, sizeof(T));
       fa = tile_base(g, twiddles<T>(g), c.full);
       fa.in = vout; fa.vol = vr(deps_of_mut<T>(g), g.sh.N); fa.out = vr(g.wsP, n3); fa.active = g.run;
+      arnoldi_inverse<T>(g, vout, j, s, qp);
       const int cached = cached_instances(g.sh, sizeof(T), j + 1);
-      fa.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, j + 1, DotBlocks<T>::value, slots_nt(g.B, cached), cached};
+      fa.up = UpdateTask{V, n3, bsv, g.st, g.dpart2, g.part, j + 1, dot_partials(g.sh, sizeof(T)),
+                         slots_nt(g.B, cached), cached};
     }
   }
   auto run_pass = [&]() {
