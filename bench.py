@@ -182,6 +182,16 @@ def sec_fp64(ctx, args, out):
     log("bench: line/space 32x32x32", out["line_space_G1_fp64"])
 
 
+def gram_schmidt_in_transforms(prob):
+    """Whether an FP32 step of this grid forms its projections in the inverse transverse kernel and does
+    the previous column's update in the forward one (the library's own rules and switches)."""
+    import ctypes as C
+    from paper_2606_25541_amd import _lib
+    k = _lib.psfd_step_kernels()
+    _lib.check(_lib.lib().psfd_step_info(prob.nx, prob.ny, prob.nz, _lib.PSFD_MIXED, 1, C.byref(k)), "psfd_step_info")
+    return bool(k.dots_in_inverse), bool(k.update_in_forward)
+
+
 def sec_apply(ctx, args, out):
     """Operator applies/s and per-stage bandwidth, timed with HIP events on the launch stream."""
     import ctypes as C
@@ -230,15 +240,13 @@ def sec_apply(ctx, args, out):
     # kernels of the Arnoldi steps of one restart cycle (columns j = 0 .. m-1) on FP32 basis vectors,
     # through psfd_bench_gram_schmidt: the projections read v_0..v_j and w, (j + 2) 3N complex64; the
     # update also writes w, (j + 3) 3N; the step's inverse transverse kernel reads the workspace and
-    # writes w, 2 3N, and where it also forms the projections (FP32 128 x 128 planes) reads v_0..v_j
+    # writes w, 2 3N, and where it also forms the projections (gram_schmidt_in_transforms) reads v_0..v_j
     # as well, (j + 3) 3N, and no separate projection pass runs
     # The forward stage of step j + 1 (pass 3) reads the slot, the contrast and writes the workspace,
-    # 7N; where it also does the update of column j (FP32 128 x 128 planes, lock-step solves) it reads
+    # 7N; where it also does the update of column j (lock-step solves) it reads
     # v_0..v_j too and writes the slot back, (j + 2) 3N + 7N
     m = args.restart
-    sq128 = prob.nx == prob.ny == 128
-    fused = sq128 and 3 * prob.nz <= 256 and os.environ.get("PSFD_FUSE_DOTS", "1") != "0"
-    fused_upd = sq128 and os.environ.get("PSFD_FUSE_UPDATE", "1") != "0"
+    fused, fused_upd = gram_schmidt_in_transforms(prob)
     x32 = x.to(torch.complex64)
     gs = {}
     for pname, pas, nvec in (("projections", 0, lambda j: j + 2), ("update", 1, lambda j: j + 3),

@@ -86,3 +86,20 @@ def test_step_info_rejects_bad_arguments():
     assert lib.psfd_step_info(64, 64, 32, 2, 0, C.byref(k)) == L.PSFD_ERR_INVALID_ARG
     assert lib.psfd_step_info(64, 64, 32, 1, -2, C.byref(k)) == L.PSFD_ERR_INVALID_ARG
     assert lib.psfd_step_info(48, 64, 32, 1, 0, C.byref(k)) == L.PSFD_ERR_UNSUPPORTED_SIZE
+
+
+@pytest.mark.parametrize("shape,want", [((64, 64, 32), (True, True)), ((256, 64, 32), (True, True)),
+                                        ((256, 256, 64), (True, True)), ((128, 128, 16), (True, False)),
+                                        ((128, 128, 128), (False, False))])
+def test_benchmark_counts_the_kernels_that_run(shape, want, monkeypatch):
+    """bench.py counts the bytes of the step's kernels by the library's rules, on every
+    grid and with the projections switched off."""
+    import os
+    import sys
+    from types import SimpleNamespace
+    sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    import bench
+    prob = SimpleNamespace(nx=shape[0], ny=shape[1], nz=shape[2])
+    assert bench.gram_schmidt_in_transforms(prob) == want
+    monkeypatch.setenv("PSFD_FUSE_DOTS", "0")
+    assert bench.gram_schmidt_in_transforms(prob) == (False, False)
