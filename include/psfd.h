@@ -385,8 +385,10 @@ int psfd_diff_plan_create(const psfd_diff_problem* prob, psfd_diff_plan** out);
 void psfd_diff_plan_destroy(psfd_diff_plan* plan);
 /* y = A x or D A x (precond); d_deps [ncz][ny][nx], d_x, d_y [3][nz_ext][ny][nx],
  * all of dtype (PSFD_C64: FP32 arithmetic, PSFD_C128: FP64), device; d_y must not
- * alias d_x. A workspace of one field and the contrast planes of another of dtype
- * is allocated at the first call of each dtype and kept with the plan.
+ * alias d_x. A workspace of one field of dtype is allocated at the first call of
+ * each dtype and kept with the plan, and the contrast planes of another at the
+ * first one with precond (where they cannot be had, out of memory or on a
+ * capturing stream, the kernels of run-time shape, which need none, run).
  * PSFD_DIFF_CT=0 in the environment selects the kernels of run-time shape.
  * Asynchronous on stream. */
 int psfd_diff_apply(psfd_diff_plan* plan, const void* d_deps, const void* d_x, void* d_y, int dtype, int precond,

@@ -18,13 +18,13 @@ Status diff_solve(psfd_diff_plan* p, const void* deps, void* e, void* orders, co
 // ---- kernels with compile-time shapes (k_diffz.hip) --------------------------
 // Transverse FFT of planes: in, out [planes][ny][nx]. Forward: planes 0 .. 3 pe - 1,
 // and, launched with 3 ncz planes more, the spectra of V x (V = k0sq deps) of the
-// contrast planes into the planes of `out` after the field. Inverse with deps: out
+// contrast planes into `aux`, [3][ncz][ny][nx]. Inverse with deps: out
 // = IFFT in - V x on the contrast planes.
 struct DiffPlaneArgs {
   const void* in;
   void* out;
   const void* deps;  // [ncz][ny][nx], or null
-  const void* x;     // inverse: the operand of V x
+  void* aux;         // forward: receives the spectra of V x; inverse: x, the operand of V x (read)
   int pe, zc0, ncz;
   double k0sq;
   const void* tw;    // twiddles of every length (length n at offset n)

@@ -33,6 +33,8 @@ struct psfd_diff_plan {
   double* zt = nullptr;      // [kappa_d (nz_ext)][kappa (nz_ext)][inv_s (2 nz_ext)]
   void* ws32 = nullptr;      // apply workspaces (3 N_ext values)
   void* ws64 = nullptr;
+  void* vx32 = nullptr;      // spectra of V x on the contrast planes (damped applies)
+  void* vx64 = nullptr;
   psfd::GmresWs gm;          // small buffers of its solves
   void* plane = nullptr;     // 3 planes of the readout, complex128
   std::vector<void*> owned;
@@ -348,22 +350,43 @@ bool env_flag(const char* name) {
   return !e || std::atoi(e) != 0;
 }
 
+// The buffer of the damped compile-time apply, allocated at the first such apply
+// of a dtype. Null where it cannot be had (no memory, or the stream is capturing
+// and none was allocated before): the run-time kernels need none.
+template <class T> T* damp_ws(psfd_diff_plan* P, hipStream_t s) {
+  void*& w = sizeof(T) == 8 ? P->vx32 : P->vx64;
+  if (!w) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone ||
+        hipMalloc(&w, (size_t)(3 * P->se.nxny * P->p.ncz) * sizeof(T)) != hipSuccess) {
+      (void)hipGetLastError();
+      w = nullptr;
+      return nullptr;
+    }
+    P->owned.push_back(w);
+  }
+  return (T*)w;
+}
+
 template <class T>
 Status apply_t(psfd_diff_plan* P, const T* deps, const T* x, T* y, int precond, hipStream_t s) {
   const Shape& se = P->se;
   T* ws = (T*)(sizeof(T) == 8 ? P->ws32 : P->ws64);
   const int np = 3 * se.nz;
-  if (diff_ct_shape<T>(se.nx, se.ny, se.nz) && env_flag("PSFD_DIFF_CT")) {
-    const bool damp = precond == PSFD_PRECOND_DAMPING;
+  const bool damp = precond == PSFD_PRECOND_DAMPING;
+  bool ct = diff_ct_shape<T>(se.nx, se.ny, se.nz) && env_flag("PSFD_DIFF_CT");
+  T* vx = nullptr;
+  if (ct && damp) ct = (vx = damp_ws<T>(P, s)) != nullptr;
+  if (ct) {
     const double k0 = 2.0 * 3.14159265358979323846 / P->p.base.wavelength_nm;
     const void* tw = sizeof(T) == 8 ? (const void*)P->gb->dc->tw32 : (const void*)P->gb->dc->tw64;
-    DiffPlaneArgs f{x, ws, damp ? deps : nullptr, nullptr, se.nz, P->p.zc0, P->p.ncz, k0 * k0, tw};
+    DiffPlaneArgs f{x, ws, damp ? deps : nullptr, vx, se.nz, P->p.zc0, P->p.ncz, k0 * k0, tw};
     launch_diff_plane<T, false>(f, se.nx, se.ny, np + (damp ? 3 * P->p.ncz : 0), s);
     TabLayout L{se.nx, se.ny};
-    DiffZcolArgs z{se.nx, se.ny, ws, ws + se.n3, P->p.zc0, P->p.ncz, P->gb->tab + L.off_kx(), P->gb->tab + L.off_ky(),
+    DiffZcolArgs z{se.nx, se.ny, ws, vx, P->p.zc0, P->p.ncz, P->gb->tab + L.off_kx(), P->gb->tab + L.off_ky(),
                    P->zt, P->p.base.eps_bg * k0 * k0, tw};
     launch_diff_zcol<T>(z, se.nz, damp, s);
-    DiffPlaneArgs b{ws, y, damp ? nullptr : deps, x, se.nz, P->p.zc0, P->p.ncz, k0 * k0, tw};
+    DiffPlaneArgs b{ws, y, damp ? nullptr : deps, const_cast<T*>(x), se.nz, P->p.zc0, P->p.ncz, k0 * k0, tw};
     launch_diff_plane<T, true>(b, se.nx, se.ny, np, s);
     DCHK(hipGetLastError());
     return Status();
@@ -375,7 +398,7 @@ Status apply_t(psfd_diff_plan* P, const T* deps, const T* x, T* y, int precond, 
   const double k0 = 2.0 * 3.14159265358979323846 / P->p.base.wavelength_nm;
   hipLaunchKernelGGL(k_diff_vx<T>, dim3((unsigned)((3 * nc + 255) / 256)), dim3(256), 0, s, deps, x, y, plane, nc,
                      (long long)P->p.zc0, se.N, k0 * k0);
-  if (precond == PSFD_PRECOND_DAMPING) {
+  if (damp) {
     transverse<T, false>(*P, se, np, y, ws, s);
     launch_diff_pencil<T>(*P, ws, DMODE_DAMP, s);
     transverse<T, true>(*P, se, np, ws, y, s);
@@ -481,8 +504,7 @@ void diff_destroy(psfd_diff_plan* p) { delete p; }
 static Status ensure_ws(psfd_diff_plan* P, int dtype) {
   void*& w = dtype == PSFD_C64 ? P->ws32 : P->ws64;
   if (!w) {
-    // a field, and the transverse spectra of V x on the contrast planes
-    DCHK(hipMalloc(&w, (size_t)(P->se.n3 + 3 * P->se.nxny * P->p.ncz) * (dtype == PSFD_C64 ? 8 : 16)));
+    DCHK(hipMalloc(&w, (size_t)P->se.n3 * (dtype == PSFD_C64 ? 8 : 16)));
     P->owned.push_back(w);
   }
   return Status();

@@ -62,7 +62,7 @@ __global__ void __launch_bounds__((DpShape<LNX, LNY>::NT)) k_diff_plane(DiffPlan
 #pragma unroll
     for (int k = 0; k < KT; ++k) vb[k] = dp[tid + k * NT];
     if constexpr (INV) {
-      const T* xp = (const T*)a.x + (long long)plane * N;
+      const T* xp = (const T*)a.aux + (long long)plane * N;
 #pragma unroll
       for (int k = 0; k < KT; ++k) xa[k] = xp[tid + k * NT];
     }
@@ -88,7 +88,7 @@ __global__ void __launch_bounds__((DpShape<LNX, LNY>::NT)) k_diff_plane(DiffPlan
   lds_fft_tab_regout<T, INV, true, KT, Cols, false, S::LKT>(lds, Cols(), twy, tid, res);
   // butterfly i, output j: row (tid / nx + TS i) + PL j, plane element
   // tid + (i + NBL j) NT, one of the thread's own loaded ones
-  T* out = (T*)a.out + (long long)blockIdx.x * N;
+  T* out = !INV && kc >= 0 ? (T*)a.aux + (long long)((int)blockIdx.x - np) * N : (T*)a.out + (long long)blockIdx.x * N;
 #pragma unroll
   for (int i = 0; i < S::NBL; ++i)
 #pragma unroll

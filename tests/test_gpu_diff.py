@@ -177,3 +177,58 @@ def test_green_function_solve_takes_fewer_steps_on_a_small_clip():
     its["ls"] = li["iters"]
     say("iterations", its)
     assert its["ls"] < min(its["none"], its["damping"])
+
+
+def test_diff_workspace_by_the_applies_in_use():
+    """64 x 64 x 128 FP64 with 64 contrast planes: an undamped apply allocates one field
+    (25.2 MB) and no more, the damped one the contrast planes of another (12.6 MB)
+    once. A plan used without damping so far still takes a damped apply into a
+    captured graph: without the extra planes, through the kernels of run-time
+    shape, the same result to FP64 rounding on every replay."""
+    from paper_2606_25541_amd import api
+    dev = device()
+    nx, ny, nz, pe = 64, 64, 64, 128
+    p = problem(nx, ny, nz, 128.0, 60.0, pol=0, pairs=4)
+    zc0 = (pe - nz) // 2
+    g = torch.Generator(device=dev).manual_seed(3)
+    x = torch.randn((3, pe, ny, nx), dtype=torch.complex128, device=dev, generator=g)
+    d = torch.from_numpy(clips.manhattan(nx, ny, nz, p.lx_nm, p.ly_nm, seed=7)).to(dev)
+    y = torch.empty_like(x)
+    field, extra, page = x.numel() * 16, 3 * nz * ny * nx * 16, 4 << 20
+
+    def used():
+        torch.cuda.synchronize()
+        return -torch.cuda.mem_get_info()[0]
+
+    warm = api.DiffPlan(p, pe, zc0, nz, 16)  # every kernel's module is loaded before anything is measured
+    warm.apply(d, x, y)
+    warm.apply(d, x, y, precond="damping")
+    ref = y.clone()
+    plan = api.DiffPlan(p, pe, zc0, nz, 16)
+    u0 = used()
+    plan.apply(d, x, y)
+    u1 = used()
+    say("diff workspace: undamped", u1 - u0, "of", field)
+    assert u1 - u0 <= field + page
+    graph = torch.cuda.CUDAGraph()
+    out = torch.empty_like(x)
+    with torch.cuda.graph(graph):
+        plan.apply(d, x, out, precond="damping")
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        # rounding of an undamped field that the damping then lowers by up to k_max^2 / k_bg^2 (150
+        # on this grid): 2.2e-16 x 150 x 20 radix passes
+        assert rel(out.cpu().numpy(), ref.cpu().numpy()) < 1e-12
+        plan.apply(d, x, y)
+        torch.cuda.synchronize()
+    u2 = used()
+    plan.apply(d, x, y, precond="damping")
+    u3 = used()
+    say("  damped", u3 - u2, "of", extra)
+    assert u3 - u2 <= extra + page
+    assert torch.equal(y, ref)
+    u4 = used()  # (torch's own comparison above allocates)
+    plan.apply(d, x, y, precond="damping")
+    assert used() - u4 <= page
