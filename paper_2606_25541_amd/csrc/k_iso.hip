@@ -259,12 +259,12 @@ PSFD_D void z_block(unsigned hw, unsigned nbx, int ny, int& ky, unsigned& bx) {
   ky = r & 1 ? (r + 1) >> 1 : (r ? 2 * ny - (r >> 1) : 0);
 }
 
-// Each thread owns the table products of points tid + i nthr (i < ZPT) and
-// loads their six table entries before the forward z FFT, so that the loads
-// are in flight while the FFT runs; points beyond ZPT nthr (not met by the
-// launch shapes used) load theirs after it.
-// (ZPT: 2 points per thread in FP32; none in FP64, where the prefetched
-// entries and the FFT registers do not fit together without spills)
+// Table products of the pass-by-pass kernel of run-time shape (k_iso_zmul). In FP32
+// each thread owns points tid + i nthr (i < ZPT = 2, all the points of a launch)
+// and loads their six entries before the forward z FFT, so that the loads are in
+// flight while the FFT runs. In FP64 the prefetched entries and the FFT registers
+// do not fit together without spills: ZPT = 0, every point loads its entries after
+// the FFT.
 template <class T> struct Zpt { static constexpr int v = sizeof(T) == 8 ? 2 : 0; };
 // values per thread in the z FFT passes (the block has at least els / ZFE threads)
 constexpr int ZFE = 8;
@@ -341,9 +341,8 @@ __global__ void k_iso_zmul(IsoZ a) {
 }
 
 // The pass-by-pass kernel with the shape fixed at compile time (FFT length 2^LZ2, LB
-// columns, NT threads; FP64, nz = 64): every global load of a thread is issued before its
-// first LDS write, the twiddles are staged in LDS so that no FFT pass waits on
-// the vector-memory counter of the table entries in flight, and the FFT index
+// columns, NT threads; FP64, nz = 64): every load of a thread's data is issued
+// before its first LDS write, the twiddles are staged in LDS, and the FFT index
 // arithmetic folds to constants.
 template <class T, int LZ2, int LB, int NT>
 __global__ void __launch_bounds__(NT) k_iso_zmul_ct(IsoZ a) {
@@ -371,13 +370,6 @@ __global__ void __launch_bounds__(NT) k_iso_zmul_ct(IsoZ a) {
     const int iz = r / 3, c = r - 3 * iz;
     v[k] = w[(long long)(c * NZ + iz) * a.plane + col + li];
   }
-  constexpr int ZPT = Zpt<T>::v;
-  T tt[ZPT > 0 ? ZPT : 1][6];
-#pragma unroll
-  for (int i = 0; i < ZPT; ++i) {
-    const int pt = tid + i * NT;
-    if (pt < NPTS) zmul_entries(tb, kx0 + (pt & (LB - 1)), ky, pt >> LLB, nx, a.ny, NZ, a.nxp, tt[i]);
-  }
   if (tid < 2 * NZ) twl[tid] = tw0;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -388,12 +380,7 @@ __global__ void __launch_bounds__(NT) k_iso_zmul_ct(IsoZ a) {
   __syncthreads();
   typedef FftCT<LZ2, NSQ, 1, NSQ, NT> D;
   lds_fft_tab<T, false, true, ZFE, D, true, false>(lds, D(), twl, tid);
-#pragma unroll
-  for (int i = 0; i < ZPT; ++i) {
-    const int pt = tid + i * NT;
-    if (pt < NPTS) zmul_point(lds + (pt >> LLB) * NSQ + (pt & (LB - 1)), LB, tt[i]);
-  }
-  for (int pt = tid + ZPT * NT; pt < NPTS; pt += NT) {
+  for (int pt = tid; pt < NPTS; pt += NT) {
     T t[6];
     zmul_entries(tb, kx0 + (pt & (LB - 1)), ky, pt >> LLB, nx, a.ny, NZ, a.nxp, t);
     zmul_point(lds + (pt >> LLB) * NSQ + (pt & (LB - 1)), LB, t);
@@ -784,17 +771,18 @@ template <class T> const T* tab_of(psfd_iso_plan* p);
 template <> const double2* tab_of<double2>(psfd_iso_plan* p) { return p->ptab64; }
 template <> const float2* tab_of<float2>(psfd_iso_plan* p) { return p->ptab32; }
 
-// adjacent kx per z-pencil block: at most the cap below, the three padded z
-// sequences of all of them within 64 KB of LDS and at most ZFE values per
-// thread of 1024
 static int env_int_iso(const char* name, int dflt) {
   const char* e = std::getenv(name);
   return e ? std::atoi(e) : dflt;
 }
 
+// adjacent kx per block of the pass-by-pass kernels (the register kernel takes 16):
+// at most the cap below, the three padded z sequences of all of them within 64 KB
+// of LDS and at most ZFE values per thread of 1024. FP64: 4, the best of 16, 8 and
+// 4 at 128 x 128 x 64 (more blocks per CU to cover the FFT barriers). FP32: 8;
+// only grids of fewer than 8 columns or planes reach it, all of one block's
+// latency. PSFD_ISO_ZLB overrides (sweeps).
 template <class T> int z_lb(int nz, int nx) {
-  // measured at 128 x 128 x 64 (widths 16, 8, 4): 8 in FP32, 4 in FP64 (more
-  // blocks per CU to cover the FFT barriers); PSFD_ISO_ZLB overrides (sweeps)
   static const int cap = [] {
     const char* e = std::getenv("PSFD_ISO_ZLB");
     const int dflt = sizeof(T) == 8 ? 8 : 4;
