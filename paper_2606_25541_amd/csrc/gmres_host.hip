@@ -1,9 +1,16 @@
 // Host-driven restarted GMRES (Saad & Schultz): classical Gram-Schmidt with the
 // projections and ||w||^2 from one launch and the new norm by Pythagoras (a
-// second pass where the update leaves less than `cancel` of the norm), Givens
-// rotations and the small triangular solve on the host. Reductions run in a
-// fixed order (block partials, then one wavefront per sum), so a solve is
-// deterministic.
+// second pass where the update leaves less than `cancel` of the norm, its norm by
+// Pythagoras from its own projections too), Givens rotations and the small
+// triangular solve on the host. Reductions run in a fixed order (block partials,
+// then one wavefront per sum), so a solve is deterministic.
+//
+// The norm by difference is off by eps / (2 c^2), c what a pass leaves of the norm.
+// One pass is trusted for c >= `cancel`. After a second pass c is near 1 again
+// unless w lies in the span of the basis to rounding (twice is enough: Giraud,
+// Langou, Rozloznik, van den Eshof 2005), and then hn is rounding noise of the
+// first pass or 0 however it is formed: the rotation takes |g_(j+1)| below any
+// tolerance, the cycle ends, and the restart's residual b - A x decides.
 //
 // A step runs on the device alone: the step kernel sums the partials, forms the
 // norm and scale the update takes, and writes them to mapped host memory; the

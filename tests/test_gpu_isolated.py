@@ -366,3 +366,53 @@ def test_iso_solve_steps_match_a_plain_gmres(shape, second_pass, monkeypatch):
             xr = xr + y[i, 0].item() * V[i]
     say("  steps", info["iters"], "plain", steps)
     assert abs(info["iters"] - steps) <= 1
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("voxels", [1, 2])
+@pytest.mark.parametrize("shape", [(2, 2, 2), (16, 32, 32), (32, 64, 64)])
+def test_isolated_solve_through_a_breakdown(shape, voxels, precision):
+    """Contrast on one or two voxels: I - K V differs from the identity by rank 3 per
+    voxel, so the Krylov space is exhausted after 3 voxels + 1 steps and the last new
+    vector lies in the span of the basis: both Gram-Schmidt passes cancel to
+    rounding (the second one's norm, a difference, may be 0), the cycle ends there,
+    and the residual b - A x confirms the tolerance. Against the exact solution:
+    u = b - K(V u) off the voxels, and on them a dense system of 3 voxels
+    unknowns, whose matrix the operator itself gives column by column."""
+    dev = device()
+    spacing, eps = (2.0, 2.0, 2.0), 1.0
+    plan = iso_plan(shape, spacing, eps)
+    de = np.zeros(shape, complex)
+    at = [(0, 0, 0), (1, 1, 1)][:voxels]
+    for i, v in enumerate(at):
+        de[v] = -0.3 + 0.1 * i + 0.06j
+    d = torch.from_numpy(de).to(dev)
+    b = clips.random_complex((3,) + shape, seed=41)
+    bt = torch.from_numpy(b).to(dev)
+    say("isolated solve through a breakdown", shape, voxels, precision)
+    rtol = 1e-12 if precision == "fp64" else 1e-10
+    u, info = plan.solve(d, bt, rtol=rtol, restart=30, max_iters=60, precision=precision)
+    say("  info", info)
+    assert info["status"] == 0 and info["rel_residual"] <= rtol
+    rank = 3 * voxels
+    if precision == "fp64":
+        assert info["iters"] <= rank + 1
+    # columns of A = I - K V for the unknowns on the voxels
+    cols = []
+    for c in range(3):
+        for v in at:
+            e = torch.zeros((3,) + shape, dtype=torch.complex128, device=dev)
+            e[(c,) + v] = 1.0
+            cols.append(plan.apply(d, e).cpu().numpy())
+    sel = [(c,) + v for c in range(3) for v in at]
+    M = np.array([[col[s] for col in cols] for s in sel])
+    us = np.linalg.solve(M, np.array([b[s] for s in sel]))
+    ref = b.copy()
+    for s, x, col in zip(sel, us, cols):
+        e = np.zeros((3,) + shape, complex)
+        e[s] = 1.0
+        ref = ref - x * (col - e)  # u = b + K V u
+    err = np.linalg.norm(u.cpu().numpy() - ref) / np.linalg.norm(ref)
+    say("  rel err", err)
+    # the tolerance times the conditioning of a 3 x 3 or 6 x 6 perturbation of the identity of norm < 1
+    assert err <= 10 * rtol
