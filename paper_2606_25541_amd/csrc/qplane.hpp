@@ -37,11 +37,12 @@ namespace psfd {
 // Threads and values per thread of a block. FP32: 16 values on quarters of more
 // than 4096 values (256 x 256: 1024 threads), 4 at 1024 (256 threads shorten the
 // chain that bounds them: 64 x 64 x 32 apply 18.9 -> 18.0 us against 8), else 8. At
-// 4096 values 8 against 16: apply 256 x 64 x 16 28.2 -> 26.9 us, 128 x 128 x 16 25.1 ->
-// 23.8, 128 x 128 x 32 36.6 -> 36.3, 128 x 128 x 64 51.9 -> 52.2, 256 x 64 x 64 52.4 ->
-// 53.3; with the Gram-Schmidt work a step at 128 x 128 x 8 43.1 -> 41.3, at 32 planes
-// 66.3 alike, at 64 103.7 -> 105.7: WIDE (16) above 32 planes, where the blocks
-// are enough to fill the chip. FP64: 8. At least one thread per column and one wavefront. No pass
+// 4096 values 16 above 32 planes (WIDE), where the blocks are enough to fill the
+// chip, 8 up to there; 8 against 16 values: apply 256 x 64 x 16 26.9 against 28.2 us,
+// 128 x 128 x 16 23.8 against 25.1, 128 x 128 x 32 36.3 against 36.6, 256 x 64 x 64 53.3
+// against 52.4; with the Gram-Schmidt work a step at 128 x 128 x 8 41.3 against 43.1,
+// at 32 planes 66.3 alike, at 64 105.7 against 103.7 (the plain apply of 128 x 128 x 64
+// is level). FP64: 8. At least one thread per column and one wavefront. No pass
 // takes a radix above the values of a thread.
 template <class T, int LNX, int LNY, bool WIDE> struct QpShape {
   static constexpr int NX = 1 << LNX, NY = 1 << LNY, ROWS = NY / 4, ELEM = ROWS * NX;
