@@ -301,8 +301,8 @@ def sec_apply(ctx, args, out):
                        "bytes_per_launch": bytes_d, "us_per_launch": us_d,
                        "kernel_source_hash": kernel_source_hash(),
                        "per_step_us": {k: round(v[1], 2) for k, v in cand.items()}}
-    # the device's own copy of 256 MiB (read + write, best of five): the practical streaming
-    # ceiling, against which the fraction is also given
+    # the device's own copy of 256 MiB (read + write, best of five), against which the fraction is also
+    # given; its 512 MiB do not stay in the 256 MB Infinity Cache, where smaller sets go faster
     ca = torch.empty(64 << 20, dtype=torch.float32, device=dev).fill_(1.0)
     cb = torch.empty_like(ca)
     cb.copy_(ca)
